@@ -72,7 +72,7 @@ __global__ void k_async_init(AsyncCtl *ctl, LevelCounters *lc) {
 }
 
 template <int G, uint32_t LS>
-__global__ __launch_bounds__(kExpandBlock) void k_explore_async(TableView t, ModelView m, uint32_t *queue,
+__global__ __launch_bounds__(kExpandBlock, LS == 8 ? 4 : 1) void k_explore_async(TableView t, ModelView m, uint32_t *queue,
                                                                 LevelCounters *lc, AsyncCtl *ctl,
                                                                 uint32_t limit, uint32_t tcap) {
     extern __shared__ uint32_t smem[];

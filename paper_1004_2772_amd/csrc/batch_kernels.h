@@ -41,7 +41,7 @@ __device__ __forceinline__ uint32_t find_slot_by_tile(const uint32_t *begin, uin
 
 // ---- host-driven step ---------------------------------------------------
 template <int G, uint32_t LS>
-__global__ __launch_bounds__(kExpandBlock) void k_expand_multi(const BatchSlot *__restrict__ slots,
+__global__ __launch_bounds__(kExpandBlock, LS == 8 ? 4 : 1) void k_expand_multi(const BatchSlot *__restrict__ slots,
                                                                const uint32_t *__restrict__ begin,
                                                                uint32_t n_slots, uint32_t total_tiles,
                                                                uint32_t tcap) {

@@ -296,19 +296,37 @@ __device__ __forceinline__ void write_row(const Group<G> &g, uint32_t *row, cons
     }
 }
 
+// Row compare by the group, up to four pieces per lane in flight at once
+// (pieces past the row's end are read as its last one).
 template <int G, class Vec>
 __device__ __forceinline__ bool row_equals(const Group<G> &g, const uint32_t *row, const Vec &v,
                                            uint32_t W) {
     uint32_t diff = 0;
     if ((W & 1u) == 0) {
         const uint64_t *r2 = reinterpret_cast<const uint64_t *>(row);
-        for (uint32_t j = g.sub; j < W / 2; j += G) {
-            const uint64_t x = ld_coherent(r2 + j);
-            diff |= ((uint32_t)x ^ v.get(2 * j)) | ((uint32_t)(x >> 32) ^ v.get(2 * j + 1));
+        const uint32_t last = W / 2 - 1;
+        for (uint32_t j0 = g.sub; j0 <= last; j0 += 4 * G) {
+            uint64_t x[4];
+#pragma unroll
+            for (uint32_t k = 0; k < 4; ++k)
+                x[k] = ld_coherent(r2 + min(j0 + k * G, last));
+#pragma unroll
+            for (uint32_t k = 0; k < 4; ++k) {
+                const uint32_t j = min(j0 + k * G, last);
+                diff |= ((uint32_t)x[k] ^ v.get(2 * j)) | ((uint32_t)(x[k] >> 32) ^ v.get(2 * j + 1));
+            }
         }
     } else {
-        for (uint32_t i = g.sub; i < W; i += G)
-            diff |= ld_coherent(row + i) ^ v.get(i);
+        const uint32_t last = W - 1;
+        for (uint32_t j0 = g.sub; j0 <= last; j0 += 4 * G) {
+            uint32_t x[4];
+#pragma unroll
+            for (uint32_t k = 0; k < 4; ++k)
+                x[k] = ld_coherent(row + min(j0 + k * G, last));
+#pragma unroll
+            for (uint32_t k = 0; k < 4; ++k)
+                diff |= x[k] ^ v.get(min(j0 + k * G, last));
+        }
     }
     return g.all(diff == 0);
 }
@@ -467,15 +485,52 @@ __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_wave_barrier();
 }
 
+// The three cooperative accesses below move up to 64 random lines or rows
+// for a wavefront.  What bounds them is the latency of a random access, so
+// each issues all its loads before it uses the first.  A lane without an
+// entry of its own reads the list's last entry again (the same line, in
+// cache) instead of branching around its load: a load under a divergent
+// branch is waited for before the next one is issued, which made a snapshot
+// of 64 lines four round trips and a compare of 64 rows eight.  Measured with
+// the loads branched around and together: a table of 2^28 slots built from
+// 2^26 rows of 16 words 5.24 and 4.87 ms, the 12-process search to 2^27
+// states 24.6 and 22.6 ms, the 64-model batch 11.3 and 10.3 ms.
+
+// One part of a line snapshot: the lines of ranks [0, nn) by NQ load
+// instructions of LPQ lines each.
+template <uint32_t LS, bool CL, uint32_t NQ>
+__device__ __forceinline__ void coop_line_part(WaveScratch<LS> *ws, const uint64_t *bucket, uint32_t nn) {
+    constexpr uint32_t C = LS / 2, CS = line_shift<LS>() - 1, LPQ = 64 / C;
+    const uint32_t lane = __lane_id(), c = lane & (C - 1);
+    uint4 x[NQ];
+    uint32_t r[NQ];
+#pragma unroll
+    for (uint32_t q = 0; q < NQ; ++q) {
+        r[q] = min(q * LPQ + (lane >> CS), nn - 1);
+        x[q] = ld_line16<CL>(reinterpret_cast<const uint4 *>(bucket + (uint64_t)ws->idx[r[q]] * LS) + c);
+    }
+#pragma unroll
+    for (uint32_t q = 0; q < NQ; ++q) {
+        const uint64_t s0 = ((uint64_t)x[q].y << 32) | x[q].x;
+        const uint64_t s1 = ((uint64_t)x[q].w << 32) | x[q].z;
+        const uint64_t mk = ws->key[r[q]];
+        const uint32_t b = (uint32_t)(s0 == 0) | ((uint32_t)(s1 == 0) << 1) |
+                           ((uint32_t)((s0 & ~kDone) == mk) << 2) |
+                           ((uint32_t)((s1 & ~kDone) == mk) << 3) |
+                           ((uint32_t)(s0 >> 62) & 1u) << 4 | (((uint32_t)(s1 >> 62) & 1u) << 5);
+        ws->res[r[q] * C + c] = (uint8_t)b;   // lanes of one entry write the same byte
+    }
+}
+
 // Masks (bit i = slot i of the line) of empty, memo-matching and done slots
-// for every lane with `need`; other lanes only help.  Wavefront-uniform call.
-// C = LS/2 helper lanes per line, 64/C lines per load instruction, C rounds.
+// for every lane with `need`; other lanes only help.  Wavefront-uniform call
+// with at least one such lane.  C = LS/2 helper lanes per line, 64/C lines
+// per load instruction, C instructions (one when the lines fit it).
 template <uint32_t LS, bool CL = false>
 __device__ __forceinline__ void coop_line_masks(WaveScratch<LS> *ws, const uint64_t *bucket, bool need,
                                                 uint32_t line, uint64_t memo, uint32_t &empty,
                                                 uint32_t &match, uint32_t &done) {
-    constexpr uint32_t C = LS / 2, CS = line_shift<LS>() - 1, LPQ = 64 / C;
-    const uint32_t lane = __lane_id();
+    constexpr uint32_t C = LS / 2, LPQ = 64 / C;
     const uint64_t nmask = __ballot(need);
     const uint32_t nn = (uint32_t)__popcll(nmask);
     const uint32_t rank = mbcnt(nmask);
@@ -484,28 +539,10 @@ __device__ __forceinline__ void coop_line_masks(WaveScratch<LS> *ws, const uint6
         ws->key[rank] = memo;
     }
     wave_lds_sync();
-    const uint32_t c = lane & (C - 1);
-    uint4 x[C];
-#pragma unroll
-    for (uint32_t q = 0; q < C; ++q) {
-        const uint32_t i = q * LPQ + (lane >> CS);
-        if (i < nn)
-            x[q] = ld_line16<CL>(reinterpret_cast<const uint4 *>(bucket + (uint64_t)ws->idx[i] * LS) + c);
-    }
-#pragma unroll
-    for (uint32_t q = 0; q < C; ++q) {
-        const uint32_t i = q * LPQ + (lane >> CS);
-        if (i < nn) {
-            const uint64_t s0 = ((uint64_t)x[q].y << 32) | x[q].x;
-            const uint64_t s1 = ((uint64_t)x[q].w << 32) | x[q].z;
-            const uint64_t mk = ws->key[i];
-            const uint32_t b = (uint32_t)(s0 == 0) | ((uint32_t)(s1 == 0) << 1) |
-                               ((uint32_t)((s0 & ~kDone) == mk) << 2) |
-                               ((uint32_t)((s1 & ~kDone) == mk) << 3) |
-                               ((uint32_t)(s0 >> 62) & 1u) << 4 | (((uint32_t)(s1 >> 62) & 1u) << 5);
-            ws->res[i * C + c] = (uint8_t)b;
-        }
-    }
+    if (nn > LPQ)
+        coop_line_part<LS, CL, C>(ws, bucket, nn);
+    else
+        coop_line_part<LS, CL, 1>(ws, bucket, nn);
     wave_lds_sync();
     if (need) {
         const uint32_t *r = reinterpret_cast<const uint32_t *>(ws->res) + rank * (C / 4);
@@ -558,13 +595,58 @@ __device__ __forceinline__ void coop_write_rows(WS *ws, const uint32_t *smem, ui
     wave_lds_sync();
 }
 
+// One part of a row compare: ranks [i0, i0 + 8 * NB), eight lanes per row,
+// NB loads in flight per lane; result byte 1 = this lane's pieces differ.
+template <uint32_t NB, class Vec, class WS>
+__device__ __forceinline__ void coop_rows_part(WS *ws, const uint32_t *smem, const uint32_t *data, uint32_t W,
+                                               uint32_t i0, uint32_t ng) {
+    const uint32_t lane = __lane_id(), c = lane & 7u;
+    uint32_t r[NB], slot[NB], diff[NB];
+#pragma unroll
+    for (uint32_t q = 0; q < NB; ++q) {
+        r[q] = min(i0 + 8 * q + (lane >> 3), ng - 1);
+        slot[q] = ws->idx[r[q]];
+        diff[q] = 0;
+    }
+    if ((W & 1u) == 0) {
+        for (uint32_t j0 = 0; j0 < W / 2; j0 += 8) {
+            const uint32_t j = min(j0 + c, W / 2 - 1);   // past the end: the last piece again
+            uint64_t x[NB];
+#pragma unroll
+            for (uint32_t q = 0; q < NB; ++q)
+                x[q] = ld_coherent(reinterpret_cast<const uint64_t *>(data + (uint64_t)slot[q] * W) + j);
+#pragma unroll
+            for (uint32_t q = 0; q < NB; ++q) {
+                const Vec v = Vec::decode(smem, make_uint2(ws->desc[r[q]], ws->aux[r[q]]));
+                diff[q] |= ((uint32_t)x[q] ^ v.get(2 * j)) | ((uint32_t)(x[q] >> 32) ^ v.get(2 * j + 1));
+            }
+        }
+    } else {
+        for (uint32_t j0 = 0; j0 < W; j0 += 8) {
+            const uint32_t j = min(j0 + c, W - 1);
+            uint32_t x[NB];
+#pragma unroll
+            for (uint32_t q = 0; q < NB; ++q)
+                x[q] = ld_coherent(data + (uint64_t)slot[q] * W + j);
+#pragma unroll
+            for (uint32_t q = 0; q < NB; ++q) {
+                const Vec v = Vec::decode(smem, make_uint2(ws->desc[r[q]], ws->aux[r[q]]));
+                diff[q] |= x[q] ^ v.get(j);
+            }
+        }
+    }
+#pragma unroll
+    for (uint32_t q = 0; q < NB; ++q)
+        ws->res[r[q] * 8 + c] = diff[q] != 0;   // lanes of one entry write the same byte
+}
+
 // Compare the stored rows of every lane with `go` against its vector;
-// returns equality for those lanes.  Same layout as coop_write_rows.
+// returns equality for those lanes.  Wavefront-uniform call with at least
+// one such lane; same layout as coop_write_rows.
 template <class Vec, class WS>
 __device__ __forceinline__ bool coop_rows_equal(WS *ws, const uint32_t *smem,
                                                 const uint32_t *data, uint32_t W, bool go,
                                                 uint32_t slot, uint2 d) {
-    const uint32_t lane = __lane_id();
     const uint64_t gm = __ballot(go);
     const uint32_t ng = (uint32_t)__popcll(gm);
     const uint32_t rank = mbcnt(gm);
@@ -574,26 +656,8 @@ __device__ __forceinline__ bool coop_rows_equal(WS *ws, const uint32_t *smem,
         ws->aux[rank] = d.y;
     }
     wave_lds_sync();
-    const uint32_t c = lane & 7u;
-    for (uint32_t i0 = 0; i0 < ng; i0 += 8) {
-        const uint32_t i = i0 + (lane >> 3);
-        uint32_t diff = 0;
-        if (i < ng) {
-            const Vec v = Vec::decode(smem, make_uint2(ws->desc[i], ws->aux[i]));
-            const uint32_t *row = data + (uint64_t)ws->idx[i] * W;
-            if ((W & 1u) == 0) {
-                const uint64_t *r2 = reinterpret_cast<const uint64_t *>(row);
-                for (uint32_t j = c; j < W / 2; j += 8) {
-                    const uint64_t x = ld_coherent(r2 + j);
-                    diff |= ((uint32_t)x ^ v.get(2 * j)) | ((uint32_t)(x >> 32) ^ v.get(2 * j + 1));
-                }
-            } else {
-                for (uint32_t j = c; j < W; j += 8)
-                    diff |= ld_coherent(row + j) ^ v.get(j);
-            }
-            ws->res[i * 8 + c] = diff != 0;
-        }
-    }
+    for (uint32_t i0 = 0; i0 < ng; i0 += 32)
+        coop_rows_part<4, Vec>(ws, smem, data, W, i0, ng);
     wave_lds_sync();
     bool eq = false;
     if (go) {
@@ -623,8 +687,9 @@ __device__ __forceinline__ void find_or_put_wave(const TableView &t, WaveScratch
     const uint32_t start = (uint32_t)h & (LS - 1);
     const uint32_t step = probe_step(h, t.probe);
     uint32_t line = (uint32_t)(h >> line_shift<LS>()) & t.line_mask;
-    uint32_t rounds = 0, cand = 0, empty = 0, donem = 0;
+    uint32_t rounds = 0, cand = 0, empty = 0, donem = 0, slot = 0;
     bool have_line = false, finished = !active;
+    bool matched = false;   // `slot` holds a done match whose row is still to be compared
     out_slot = kNoSlot;
     out_code = kFull;
 
@@ -648,10 +713,13 @@ __device__ __forceinline__ void find_or_put_wave(const TableView &t, WaveScratch
             }
         }
         // ---- next candidate in walk order ---------------------------------
-        uint32_t kind = 0, slot = 0;     // kind: 0 none, 1 empty, 2 match
-        bool known_done = false;
+        uint32_t kind = 0;     // 0 none, 1 empty, 2 match
+        bool known_done = matched;
         if (!finished) {
-            if (cand == 0) {
+            if (matched) {
+                kind = 2;
+                matched = false;
+            } else if (cand == 0) {
                 have_line = false;
                 ++rounds;
                 line = next_line(line, rounds, step, t.probe, t.line_mask);
@@ -664,9 +732,10 @@ __device__ __forceinline__ void find_or_put_wave(const TableView &t, WaveScratch
             }
         }
         // ---- claim phase, with the compare of matches already seen DONE ----
-        // Rows of slots the snapshot showed DONE are compared while the
-        // claims are in flight: their loads are issued after that snapshot
-        // completed, behind the acquire below, and DONE never goes away.
+        // Rows of slots seen DONE (in the snapshot, or by the last
+        // iteration's claim or wait) are compared while the claims are in
+        // flight: their loads are issued after that observation completed,
+        // behind the acquire below, and DONE never goes away.
         const bool early = kind == 2 && known_done;
         const uint64_t em = __ballot(early);
         if (em)
@@ -704,35 +773,28 @@ __device__ __forceinline__ void find_or_put_wave(const TableView &t, WaveScratch
                 out_slot = slot;
                 out_code = kNew;
                 finished = true;
-            }
-        }
-        // ---- wait phase (only slots not yet seen done) ----------------------
-        if (kind == 2 && !known_done) {
-            uint64_t cur = ld_coherent(t.bucket + slot);
-            if (!(cur & kDone)) {
-                ++cnt.waits;
-                uint32_t spins = 0;
-                while (!(cur & kDone) && ++spins < kSpinLimit) {
-                    __builtin_amdgcn_s_sleep(2);
-                    cur = ld_coherent(t.bucket + slot);
-                }
-            }
-            if (!(cur & kDone)) {
-                out_code = kStall;
-                set_error(t.status, 4u /* LHS_ESTALL */);
-                finished = true;
                 kind = 0;
             }
         }
-        // ---- compare phase --------------------------------------------------
-        const bool cmp = kind == 2;
-        if (__ballot(cmp)) {
-            after_done_observed();
-            const bool eq = coop_rows_equal<Vec>(ws, smem, t.data, t.W, cmp, slot, d);
-            if (cmp && eq) {
-                out_slot = slot;
-                out_code = kSeen;
-                finished = true;
+        // ---- wait phase (only slots not yet seen done); a match then goes
+        // to the next iteration's compare -------------------------------------
+        if (kind == 2) {
+            matched = true;
+            if (!known_done) {
+                uint64_t cur = ld_coherent(t.bucket + slot);
+                if (!(cur & kDone)) {
+                    ++cnt.waits;
+                    uint32_t spins = 0;
+                    while (!(cur & kDone) && ++spins < kSpinLimit) {
+                        __builtin_amdgcn_s_sleep(2);
+                        cur = ld_coherent(t.bucket + slot);
+                    }
+                }
+                if (!(cur & kDone)) {
+                    out_code = kStall;
+                    set_error(t.status, 4u /* LHS_ESTALL */);
+                    finished = true;
+                }
             }
         }
     }

@@ -51,7 +51,7 @@ __device__ __forceinline__ const uint32_t *seg_tile(const SegFront &f, uint32_t 
 // Expand one BFS level of one model: the frontier's tiles, new states
 // appended to the segments of the next frontier.
 template <int G, uint32_t LS>
-__global__ __launch_bounds__(kExpandBlock) void k_expand(TableView t, ModelView m, SegFront f, SegOut o,
+__global__ __launch_bounds__(kExpandBlock, LS == 8 ? 4 : 1) void k_expand(TableView t, ModelView m, SegFront f, SegOut o,
                                                          LevelCounters *lc, uint32_t limit, uint32_t tcap) {
     extern __shared__ uint32_t smem[];
     expand_begin();
@@ -87,7 +87,7 @@ __global__ void k_rollback(uint64_t *bucket, SegFront f) {
 // once, so a replay may run past the last level.
 
 template <int G, uint32_t LS>
-__global__ __launch_bounds__(kExpandBlock) void k_expand_graph(const GraphCtx *ctx, uint32_t tcap) {
+__global__ __launch_bounds__(kExpandBlock, LS == 8 ? 4 : 1) void k_expand_graph(const GraphCtx *ctx, uint32_t tcap) {
     extern __shared__ uint32_t smem[];
     __shared__ uint32_t s_go, s_lim;
     __shared__ SegFront s_f;

@@ -146,7 +146,7 @@ __device__ void step_finalize(BatchSlot *slots, StepCtl *ctl, LevelCounters *lc,
 // finish does the level bookkeeping for the next step.  `arrived` counts the
 // workgroups done with the step (zero at launch; reset by the last one).
 template <int G, uint32_t LS>
-__global__ __launch_bounds__(kExpandBlock) void k_step(BatchSlot *slots, uint32_t *begin, uint32_t n,
+__global__ __launch_bounds__(kExpandBlock, LS == 8 ? 4 : 1) void k_step(BatchSlot *slots, uint32_t *begin, uint32_t n,
                                                        uint32_t tcap, StepCtl *ctl, LevelCounters *lc,
                                                        DevStatus *st, uint32_t *arrived) {
     extern __shared__ uint32_t smem[];
@@ -315,7 +315,7 @@ __device__ void admit_query(const ModelState &M, ModelProgress *mp, LevelState *
 }
 
 template <int G, uint32_t LS>
-__global__ __launch_bounds__(kExpandBlock) void k_serve(const ModelState *ms, ModelProgress *mp, LevelState *lv,
+__global__ __launch_bounds__(kExpandBlock, LS == 8 ? 4 : 1) void k_serve(const ModelState *ms, ModelProgress *mp, LevelState *lv,
                                                         QueueState *qs, QCell *ring, ServeBox *box, DoneRec *done,
                                                         const uint32_t *roots, uint32_t tcap) {
     extern __shared__ uint32_t smem[];
