@@ -388,25 +388,40 @@ __device__ __forceinline__ bool expand_tile(uint32_t *smem, const TableView &t, 
 
     __syncthreads();   // the previous tile is fully consumed
     const bool restage = tr_in_lds && (s_trans_staged != m.trans || s_trans_key != m.key);
+    // The tile's first loads go out together: the level's abort flag and
+    // count, the frontier entries, and transitions to stage.
+    uint32_t abort_now = 0, count_now = 0;
     if (tid == 0) {
-        s_tail = 0;
-        s_abort = __hip_atomic_load(&lc->abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        abort_now = __hip_atomic_load(&lc->abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         // SEG: the level's count is this workgroup's estimate (the cursors
         // are read only near the cap)
-        const uint32_t nn = SEG ? s_seg_est : __hip_atomic_load(&lc->n_next, __ATOMIC_RELAXED,
-                                                                __HIP_MEMORY_SCOPE_AGENT);
-        s_eager = limit != 0xFFFFFFFFu && (uint64_t)nn + kEagerRoom > limit;
+        count_now = SEG ? s_seg_est : __hip_atomic_load(&lc->n_next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    if (restage)
-        for (uint32_t i = tid; i < PLK; i += kBlock)
-            tr_lds[i] = ld_trans<CL>(m.trans + i);
-    succ_cnt[tid] = 0;
     bool staged = tid < rows;
     uint64_t slot = 0;
-    if (staged) {
+    if (staged)
         // rows of earlier levels were published before this level started
         slot = COHERENT ? ld_coherent(front + base + tid) : front[base + tid];
-        if constexpr (AWAIT) {
+    if (restage) {
+        constexpr uint32_t kPer = 4;
+        for (uint32_t i0 = tid; i0 < PLK; i0 += kPer * kBlock) {
+            uint2 x[kPer];
+#pragma unroll
+            for (uint32_t k = 0; k < kPer; ++k)
+                x[k] = ld_trans<CL>(m.trans + min(i0 + k * kBlock, PLK - 1));
+#pragma unroll
+            for (uint32_t k = 0; k < kPer; ++k)
+                tr_lds[min(i0 + k * kBlock, PLK - 1)] = x[k];
+        }
+    }
+    succ_cnt[tid] = 0;
+    if (tid == 0) {
+        s_tail = 0;
+        s_abort = abort_now;
+        s_eager = limit != 0xFFFFFFFFu && (uint64_t)count_now + kEagerRoom > limit;
+    }
+    if constexpr (AWAIT) {
+        if (staged) {
             for (uint32_t spins = 0; slot == 0xFFFFFFFFu; ++spins) {
                 // give up on an aborted launch (the writer may have stopped)
                 // or after the bound (then also an error)
@@ -417,7 +432,7 @@ __device__ __forceinline__ bool expand_tile(uint32_t *smem, const TableView &t, 
                         set_error(t.status, 4u /* LHS_ESTALL */);
                     __hip_atomic_store(&lc->abort, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     s_stall = 1;
-                    staged = false;
+                    slot = 0;   // not expanded (the tile ends below)
                     break;
                 }
                 __builtin_amdgcn_s_sleep(1);
@@ -425,53 +440,50 @@ __device__ __forceinline__ bool expand_tile(uint32_t *smem, const TableView &t, 
             }
         }
     }
-    // plain loads of rows of W = 4, 8, 16 or 32 words: the wavefront loads
-    // its 64 rows together, W/4 lanes per row with one 16-byte piece each,
-    // so one load instruction moves 64/(W/4) whole rows
-    const bool coop = !COHERENT && (W == 4 || W == 8 || W == 16 || W == 32);
-    if (coop) {
-        const uint32_t lane = __lane_id(), wrow = tid - lane;    // the wave's first row
-        const uint32_t cs = W == 4 ? 0u : (W == 8 ? 1u : (W == 16 ? 2u : 3u));   // log2(W/4)
-        const uint32_t c = lane & ((1u << cs) - 1u);
-        const uint32_t my_slot = (uint32_t)slot;
-        for (uint32_t r0 = 0; r0 < 64; r0 += 64u >> cs) {
-            const uint32_t r = r0 + (lane >> cs);
-            const uint32_t rs = (uint32_t)__shfl((int)my_slot, (int)r, 64);
-            if (wrow + r < rows) {
-                const uint4 x = reinterpret_cast<const uint4 *>(t.data + (uint64_t)rs * W)[c];
-                uint32_t *dst = tile + (wrow + r) * stride + 4 * c;
-                dst[0] = x.x;
-                dst[1] = x.y;
-                dst[2] = x.z;
-                dst[3] = x.w;
+    // Row staging, a wavefront for its 64 rows: the rows' pieces (16 bytes,
+    // or 8 or 4 where coherent loads or the width ask for it) are dealt to
+    // the lanes in row order, and up to eight loads per lane are in flight.
+    // One lane per row, or one load at a time, makes a row as many round
+    // trips as it has pieces.  Lanes past the last piece repeat it.  With the
+    // guards and the hash read several words at a time (below, hash_vec):
+    // exploration without levels of 32.5 M states 13.5 -> 12.0 ms, search to
+    // 2^27 states 22.2 -> 21.0 ms, 64-model batch 10.1 -> 9.6 ms.
+    const uint32_t wrow = tid - __lane_id();    // the wave's first row
+    if (wrow < rows) {
+        const uint32_t my_slot = (uint32_t)slot, words = min(rows - wrow, 64u) * W;
+        uint32_t *wtile = tile + wrow * stride;
+        auto stage = [&](auto piece, auto batch, auto load) {
+            constexpr uint32_t Z = decltype(piece)::value, B = decltype(batch)::value;   // words, loads in flight
+            const uint32_t lane = fresh_lane();
+            for (uint32_t f0 = 0; f0 < words; f0 += B * 64 * Z) {
+                uint32_t at[B];
+                decltype(load((const uint32_t *)nullptr)) x[B];
+#pragma unroll
+                for (uint32_t k = 0; k < B; ++k) {
+                    const uint32_t f = min(f0 + (k * 64 + lane) * Z, words - Z);
+                    const uint32_t r = W == 1 ? f : __umulhi(f, m.magic_W), c = f - r * W;
+                    const uint32_t rs = (uint32_t)__shfl((int)my_slot, (int)r, 64);
+                    x[k] = load(t.data + (uint64_t)rs * W + c);
+                    at[k] = r * stride + c;
+                }
+#pragma unroll
+                for (uint32_t k = 0; k < B; ++k) {
+                    const uint32_t *w = reinterpret_cast<const uint32_t *>(&x[k]);
+#pragma unroll
+                    for (uint32_t z = 0; z < Z; ++z)
+                        wtile[at[k] + z] = w[z];
+                }
             }
-        }
-    } else if (staged) {
-        const uint32_t *src = t.data + slot * W;
-        uint32_t *dst = tile + tid * stride;
-        if (COHERENT && (W & 1u) == 0) {
-            const uint64_t *s2 = reinterpret_cast<const uint64_t *>(src);
-            for (uint32_t i = 0; i < W; i += 2) {
-                const uint64_t x = ld_coherent(s2 + (i >> 1));
-                dst[i] = (uint32_t)x;
-                dst[i + 1] = (uint32_t)(x >> 32);
-            }
-        } else if (COHERENT) {
-            for (uint32_t i = 0; i < W; ++i)
-                dst[i] = ld_coherent(src + i);
-        } else if ((W & 3u) == 0) {
-            const uint4 *s4 = reinterpret_cast<const uint4 *>(src);
-            for (uint32_t i = 0; i < W; i += 4) {
-                const uint4 x = s4[i >> 2];
-                dst[i] = x.x;
-                dst[i + 1] = x.y;
-                dst[i + 2] = x.z;
-                dst[i + 3] = x.w;
-            }
-        } else {
-            for (uint32_t i = 0; i < W; ++i)
-                dst[i] = src[i];
-        }
+        };
+        if (!COHERENT && (W & 3u) == 0)
+            stage(U32C<4>{}, U32C<4>{}, [](const uint32_t *p) { return *reinterpret_cast<const uint4 *>(p); });
+        else if ((W & 1u) == 0)
+            stage(U32C<2>{}, U32C<8>{}, [](const uint32_t *p) {
+                return COHERENT ? ld_coherent(reinterpret_cast<const uint64_t *>(p))
+                                : *reinterpret_cast<const uint64_t *>(p);
+            });
+        else
+            stage(U32C<1>{}, U32C<8>{}, [](const uint32_t *p) { return COHERENT ? ld_coherent(p) : *p; });
     }
     __syncthreads();
     // the LDS copy lives behind this model's tile rows: a tile that does not
@@ -561,62 +573,83 @@ __device__ __forceinline__ bool expand_tile(uint32_t *smem, const TableView &t, 
         }
     };
 
-    bool aborted = false;
-    if (PK <= 64) {
+    // Successors are numbered by enabled masks (PK <= 64), or found by
+    // running over all candidates (wider models); either way in passes of 256.
+    const bool narrow = PK <= 64;
+    uint32_t total = 0, nextq = 0, at = 0;    // narrow: successors, this state's next one, the pass's first
+    uint32_t c_pos = 0, head = 0, tail = 0;   // wide: next candidate, queue ends
+    uint64_t rem = 0;
+    uint32_t *pick = reinterpret_cast<uint32_t *>(masks);   // narrow: the (state, enabled pair) of the pass
+    uint32_t *dedup = pick + kBlock;
+    if (narrow) {
         // ---- enabled-transition masks, one lane per state ------------------
-        uint64_t mask = 0;
         if (tid < rows) {
+            // four processes at a time: their reads of local state,
+            // transition and guarded variable are chains of their own
             const uint32_t *row = tile + tid * stride;
-            for (uint32_t p = 0; p < m.P; ++p) {
-                const uint32_t local = row[p];
-                if (local >= m.L)
-                    continue;
-                const uint64_t tb = ((uint64_t)p * m.L + local) * m.K;
+            for (uint32_t p0 = 0; p0 < m.P; p0 += 4) {
+                uint32_t tb[4];
+                bool on[4];
+#pragma unroll
+                for (uint32_t j = 0; j < 4; ++j) {
+                    const uint32_t p = min(p0 + j, m.P - 1), local = row[p];
+                    on[j] = p0 + j < m.P && local < m.L;
+                    tb[j] = on[j] ? (p * m.L + local) * m.K : 0u;   // below 32 * 65535 * 16
+                }
                 for (uint32_t k = 0; k < m.K; ++k) {
-                    const uint2 x = trans_at(tb + k);
-                    const uint32_t gvar = (x.x >> 16) & 0xFFu;
-                    const bool en = gvar == 0xFFu || row[m.P + gvar] == (x.y & 0xFFFFu);
-                    mask |= (uint64_t)en << (p * m.K + k);
+                    uint2 x[4];
+#pragma unroll
+                    for (uint32_t j = 0; j < 4; ++j)
+                        x[j] = trans_at(tb[j] + k);
+#pragma unroll
+                    for (uint32_t j = 0; j < 4; ++j) {
+                        const uint32_t gvar = (x[j].x >> 16) & 0xFFu;
+                        const uint32_t val = row[gvar == 0xFFu ? 0u : m.P + gvar];
+                        const bool en = on[j] && (gvar == 0xFFu || val == (x[j].y & 0xFFFFu));
+                        rem |= (uint64_t)en << (((p0 + j) * m.K + k) & 63u);
+                    }
                 }
             }
         }
-        const uint32_t c = (uint32_t)__popcll(mask);
+        const uint32_t c = (uint32_t)__popcll(rem);
         succ_cnt[tid] = c;
         const uint32_t incl = wave_scan_incl(c);
         if (__lane_id() == 63)
             s_wtot[tid / 64] = incl;
         __syncthreads();
-        uint32_t woff = 0, total = 0;
+        uint32_t woff = 0;
         for (uint32_t w = 0; w < kBlock / 64; ++w) {
             woff += w < tid / 64 ? s_wtot[w] : 0u;
             total += s_wtot[w];
         }
         // this state's successors are numbered [nextq, nextq + c) in the tile
-        uint32_t nextq = woff + incl - c;
-        uint64_t rem = mask;
-        // ---- passes of 256 successors -------------------------------------
-        // Every state lane writes the (state, enabled pair) of its successors
-        // that fall in the pass into `pick` (the mask area); lane q of the
-        // pass then stages successor s0 + q.
-        uint32_t *pick = reinterpret_cast<uint32_t *>(masks);
-        uint32_t *dedup = pick + kBlock;
-        auto pick_succ = [&](uint32_t e) -> SuccVec {
-            const uint32_t j = e & 0xFFu;
-            const uint32_t p = m.K == 1 ? j : __umulhi(j, m.magic_K);
-            return succ_of(e >> 8, p, j - p * m.K);
-        };
-        for (uint32_t s0 = 0; s0 < total && !aborted; s0 += kBlock) {
-            const uint32_t take = min(total - s0, kBlock);
-            while (rem && nextq < s0 + kBlock) {
-                pick[nextq - s0] = (tid << 8) | (uint32_t)__builtin_ctzll(rem);
+        nextq = woff + incl - c;
+    }
+    auto pick_succ = [&](uint32_t e) -> SuccVec {
+        const uint32_t j = e & 0xFFu;
+        const uint32_t p = m.K == 1 ? j : __umulhi(j, m.magic_K);
+        return succ_of(e >> 8, p, j - p * m.K);
+    };
+    while (true) {
+        uint32_t take = 0;
+        bool skip = false;
+        if (narrow) {
+            // ---- every state lane writes the (state, enabled pair) of its
+            // successors that fall in the pass into `pick` (the mask area);
+            // lane q of the pass then stages successor `at` + q --------------
+            take = min(total - at, kBlock);
+            if (!take)
+                break;
+            while (rem && nextq < at + kBlock) {
+                pick[nextq - at] = (tid << 8) | (uint32_t)__builtin_ctzll(rem);
                 rem &= rem - 1;
                 ++nextq;
             }
+            at += take;
             if constexpr (G == 1)
                 for (uint32_t i = tid; i < kDedupCells; i += kBlock)
                     dedup[i] = 0;
             __syncthreads();
-            bool skip = false;
             if (tid < take) {
                 const uint32_t e = pick[tid];
                 const SuccVec v = pick_succ(e);
@@ -659,14 +692,9 @@ __device__ __forceinline__ bool expand_tile(uint32_t *smem, const TableView &t, 
                     }
                 }
             }
-            __syncthreads();
-            aborted = fop_pass(take, skip);
-        }
-    } else {
-        // ---- wide models: candidates 256 at a time into the LDS ring ------
-        const uint32_t total_c = rows * PK;
-        uint32_t c_pos = 0, head = 0, tail = 0;
-        while (true) {
+        } else {
+            // ---- candidates 256 at a time into the LDS ring ----------------
+            const uint32_t total_c = rows * PK;
             while (c_pos < total_c && tail - head < kBlock) {
                 const uint32_t c = c_pos + tid;
                 bool en = false;
@@ -702,18 +730,16 @@ __device__ __forceinline__ bool expand_tile(uint32_t *smem, const TableView &t, 
             }
             if (tail == head)
                 break;
-            const uint32_t take = min(tail - head, kBlock);
+            take = min(tail - head, kBlock);
             if (tid < take) {
                 const uint32_t e = queue[(head + tid) & (kQueue - 1)];
                 stage_successor(tid, e & 0xFFu, succ_of(e & 0xFFu, (e >> 8) & 0xFFu, e >> 16));
             }
-            __syncthreads();
             head += take;
-            if (fop_pass(take, false)) {
-                aborted = true;
-                break;
-            }
         }
+        __syncthreads();
+        if (fop_pass(take, skip))
+            break;
     }
     // a workgroup that runs several tiles of one level keeps its buffer
     if constexpr (!DEFER)

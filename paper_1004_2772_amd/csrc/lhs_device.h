@@ -104,6 +104,15 @@ __device__ __forceinline__ uint32_t mbcnt(uint64_t mask) {
                                      __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
+// The lane number, recomputed where it is asked for: what is derived from it
+// then lives where it is used, instead of being hoisted out of the loops
+// around and spilled there.
+__device__ __forceinline__ uint32_t fresh_lane() {
+    uint32_t l = __lane_id();
+    asm volatile("" : "+v"(l));
+    return l;
+}
+
 // ---- coherent (agent-scope) accesses --------------------------------------
 __device__ __forceinline__ uint64_t ld_coherent(const uint64_t *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -163,6 +172,24 @@ __device__ __forceinline__ uint64_t hash_vec(const Vec &v, uint32_t W, uint64_t 
     const uint64_t c1 = 0x87c37b91114253d5ull, c2 = 0x4cf5ad432745937full;
     uint64_t h = seed;
     uint32_t i = 0;
+    // four pairs at a time: their words are read and scrambled independently,
+    // only the short mixing into h is a chain
+    for (; i + 8 <= W; i += 8) {
+        uint32_t w[8];
+        uint64_t k[4];
+#pragma unroll
+        for (uint32_t j = 0; j < 8; ++j)
+            w[j] = v.get(i + j);
+#pragma unroll
+        for (uint32_t j = 0; j < 4; ++j)
+            k[j] = rotl64(((uint64_t)w[2 * j] | ((uint64_t)w[2 * j + 1] << 32)) * c1, 31) * c2;
+#pragma unroll
+        for (uint32_t j = 0; j < 4; ++j) {
+            h ^= k[j];
+            h = rotl64(h, 27);
+            h = h * 5 + 0x52dce729ull;
+        }
+    }
     for (; i + 1 < W; i += 2) {
         uint64_t k = (uint64_t)v.get(i) | ((uint64_t)v.get(i + 1) << 32);
         k *= c1;
@@ -501,7 +528,7 @@ __device__ __forceinline__ void wave_lds_sync() {
 template <uint32_t LS, bool CL, uint32_t NQ>
 __device__ __forceinline__ void coop_line_part(WaveScratch<LS> *ws, const uint64_t *bucket, uint32_t nn) {
     constexpr uint32_t C = LS / 2, CS = line_shift<LS>() - 1, LPQ = 64 / C;
-    const uint32_t lane = __lane_id(), c = lane & (C - 1);
+    const uint32_t lane = fresh_lane(), c = lane & (C - 1);
     uint4 x[NQ];
     uint32_t r[NQ];
 #pragma unroll
@@ -566,7 +593,7 @@ __device__ __forceinline__ void coop_line_masks(WaveScratch<LS> *ws, const uint6
 template <class Vec, class WS>
 __device__ __forceinline__ void coop_write_rows(WS *ws, const uint32_t *smem, uint32_t *data,
                                                 uint32_t W, bool go, uint32_t slot, uint2 d) {
-    const uint32_t lane = __lane_id();
+    const uint32_t lane = fresh_lane();
     const uint64_t gm = __ballot(go);
     const uint32_t ng = (uint32_t)__popcll(gm);
     const uint32_t rank = mbcnt(gm);
@@ -600,7 +627,7 @@ __device__ __forceinline__ void coop_write_rows(WS *ws, const uint32_t *smem, ui
 template <uint32_t NB, class Vec, class WS>
 __device__ __forceinline__ void coop_rows_part(WS *ws, const uint32_t *smem, const uint32_t *data, uint32_t W,
                                                uint32_t i0, uint32_t ng) {
-    const uint32_t lane = __lane_id(), c = lane & 7u;
+    const uint32_t lane = fresh_lane(), c = lane & 7u;
     uint32_t r[NB], slot[NB], diff[NB];
 #pragma unroll
     for (uint32_t q = 0; q < NB; ++q) {

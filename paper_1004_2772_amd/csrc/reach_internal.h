@@ -13,7 +13,7 @@ struct ModelView {
     uint32_t P, L, S, K, W;
     uint32_t magic_PK;   // ceil(2^32 / (P*K)) for __umulhi division
     uint32_t magic_K;
-    uint32_t pad;
+    uint32_t magic_W;
     unsigned long long key;   // tells apart models whose transitions reuse one
                               // buffer (0 where every model has a buffer of its own)
 };
