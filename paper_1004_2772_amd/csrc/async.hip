@@ -160,7 +160,7 @@ __global__ __launch_bounds__(kExpandBlock, LS == 8 ? 4 : 1) void k_explore_async
             break;
     }
     // counts kept in LDS over the launch (and, after an abort, the buffer)
-    expand_end<G, true>(smem, m.W, tcap, queue, lc, limit);
+    expand_end<G, true>(smem, m.W, tcap, queue, lc, limit, t.status);
 }
 
 }  // namespace

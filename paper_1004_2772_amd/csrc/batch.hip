@@ -123,11 +123,11 @@ uint64_t batch_auto_capacity(const reach_model *m) {
     return 1ull << 21;
 }
 
-// One table to empty: its slots and its status word.
+// One table to empty: its slots, status word and striped counters.
 struct TableZero {
     uint4 *bucket;
     unsigned long long chunks;   // 16-byte chunks of the slot array
-    DevStatus *status;
+    TableStatus *status;
 };
 
 // Empty every table of the batch in one launch: blockIdx.y = table.
@@ -136,8 +136,8 @@ __global__ void k_clear_tables(const TableZero *z) {
     for (unsigned long long i = (unsigned long long)blockIdx.x * blockDim.x + threadIdx.x; i < tz.chunks;
          i += (unsigned long long)gridDim.x * blockDim.x)
         tz.bucket[i] = make_uint4(0, 0, 0, 0);
-    if (blockIdx.x == 0 && threadIdx.x == 0)
-        *tz.status = DevStatus{0, 0, 0, 0, 0};
+    if (blockIdx.x == 0)
+        zero_status(tz.status);
 }
 
 // Copy levels 1 .. n_levels-1 of every model into one compact array, model
@@ -409,7 +409,8 @@ static lhs_status reach_explore_batch_impl(const reach_model *const *models, uin
         sl.limit = b.limit;
         sl.tile_begin = 0;
         sl.pad = 0;
-        u_zero[i] = TableZero{reinterpret_cast<uint4 *>(b.t->bucket), b.t->capacity / 2, b.t->status};
+        u_zero[i] = TableZero{reinterpret_cast<uint4 *>(b.t->bucket), b.t->capacity / 2,
+                              reinterpret_cast<TableStatus *>(b.t->status)};
         max_chunks = std::max<uint64_t>(max_chunks, b.t->capacity / 2);
     }
     if (!host_loop) {

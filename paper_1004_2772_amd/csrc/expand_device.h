@@ -101,6 +101,8 @@ static __shared__ const uint2 *s_trans_staged;
 static __shared__ unsigned long long s_trans_key;
 // Edge / deadlock counts accumulated over tiles (deferred mode).
 static __shared__ unsigned long long s_acc_edges, s_acc_dead;
+// The event counts of LaneCounters, accumulated the same way.
+static __shared__ uint32_t s_cnt_waits, s_cnt_cas, s_cnt_lines, s_cnt_merged;
 // New-state buffer fill, its reserved base in next[], and the level's abort
 // / near-the-cap flags as this workgroup last saw them.
 static __shared__ uint32_t s_nnew, s_nbase, s_abort, s_eager;
@@ -124,6 +126,10 @@ __device__ __forceinline__ void expand_begin() {
         s_trans_key = 0;
         s_acc_edges = 0;
         s_acc_dead = 0;
+        s_cnt_waits = 0;
+        s_cnt_cas = 0;
+        s_cnt_lines = 0;
+        s_cnt_merged = 0;
         s_nnew = 0;
         s_abort = 0;
         s_eager = 0;
@@ -269,13 +275,47 @@ __device__ __forceinline__ void flush_new_slots_seg(const uint32_t *nbuf, const 
     }
 }
 
+// Add a wavefront's lane counters to the workgroup's (all 64 lanes call it).
+__device__ __forceinline__ void gather_counters(const TableView &t, const LaneCounters &c) {
+    const uint32_t w = wave_sum(c.waits), f = wave_sum(c.cas_failures);
+    const uint32_t l = (t.flags & kCountLines) ? wave_sum(c.lines) : 0u;
+    const uint32_t mg = (t.flags & kCountMerged) ? wave_sum(c.merged) : 0u;
+    if (__lane_id() == 0) {
+        if (w)
+            atomicAdd(&s_cnt_waits, w);
+        if (f)
+            atomicAdd(&s_cnt_cas, f);
+        if (l)
+            atomicAdd(&s_cnt_lines, l);
+        if (mg)
+            atomicAdd(&s_cnt_merged, mg);
+    }
+}
+
+// Add the workgroup's event counts to the status (one thread).
+__device__ __forceinline__ void flush_counters(DevStatus *st) {
+    if (s_cnt_waits)
+        atomicAdd(&st->wait_hits, (unsigned long long)s_cnt_waits);
+    if (s_cnt_cas)
+        atomicAdd(&st->cas_failures, (unsigned long long)s_cnt_cas);
+    if (s_cnt_lines)
+        atomicAdd(&st->lines, (unsigned long long)s_cnt_lines);
+    if (s_cnt_merged)
+        atomicAdd(&st->merged, (unsigned long long)s_cnt_merged);
+    s_cnt_waits = 0;
+    s_cnt_cas = 0;
+    s_cnt_lines = 0;
+    s_cnt_merged = 0;
+}
+
 // Deferred mode: append the workgroup's remaining new states and add its
-// accumulated edge/deadlock counts to lc.  Call by all threads after the
+// accumulated edge/deadlock counts to lc and its event counts to st.  Call by all threads after the
 // last expand_tile of the launch (also after an aborted tile: every claimed
 // slot must be listed in next[] for the rollback).
 template <int G, bool COHERENT = false, bool SEG = false>
 __device__ __forceinline__ void expand_end(uint32_t *smem, uint32_t W, uint32_t tcap, uint32_t *next,
-                                           LevelCounters *lc, uint32_t limit, const SegOut &so = SegOut{}) {
+                                           LevelCounters *lc, uint32_t limit, DevStatus *st,
+                                           const SegOut &so = SegOut{}) {
     if constexpr (SEG)
         flush_new_slots_seg<COHERENT>(expand_nbuf<G>(smem, W, tcap), so, lc, limit);
     else
@@ -285,6 +325,7 @@ __device__ __forceinline__ void expand_end(uint32_t *smem, uint32_t W, uint32_t 
             atomicAdd(&lc->edges, s_acc_edges);
         if (s_acc_dead)
             atomicAdd(&lc->deadlocks, s_acc_dead);
+        flush_counters(st);
     }
 }
 
@@ -345,7 +386,7 @@ __device__ __forceinline__ uint32_t wave_scan_incl(uint32_t x) {
 // was produced inside the same launch by other workgroups (the persistent
 // driver); across launches the kernel boundary already makes them visible.
 // DEFER: new states stay buffered across tiles (flushed when the buffer
-// nears full) and edge/deadlock counts stay in LDS until expand_end
+// nears full) and edge, deadlock and event counts stay in LDS until expand_end
 // (single-model launches, whose workgroups run many tiles of one level);
 // otherwise both go out at the end of every tile.  DEFER_COUNTS alone keeps
 // only the counts in LDS.
@@ -514,6 +555,14 @@ __device__ __forceinline__ bool expand_tile(uint32_t *smem, const TableView &t, 
     // ---- find-or-put of successors d0/d1/hq[0, take); new slots to nbuf ----
     // skip (G == 1): this lane's successor is another lane's in the same pass
     auto fop_pass = [&](uint32_t take, bool skip) {
+        // G > 1: the next round's home line is loaded while this one runs
+        const Group<G> g;
+        auto home_of = [&](uint32_t q) {
+            return load_line<G, LS, CL>(g, t.bucket + (uint64_t)home_line<LS>(t, hq[q < take ? q : 0]) * LS);
+        };
+        LinePart<G, LS> home{};
+        if constexpr (G > 1)
+            home = home_of(gi);
         for (uint32_t r = 0; r < G; ++r) {
             const uint32_t q = r * NG + gi;
             const bool active = q < take && !(G == 1 && skip);
@@ -523,8 +572,11 @@ __device__ __forceinline__ bool expand_tile(uint32_t *smem, const TableView &t, 
                                                   active, slot, code, cnt);
             } else {
                 const uint32_t o = active ? q : 0;
-                find_or_put<G, LS, SuccVec, CL>(t, SuccVec::decode(smem, make_uint2(d0[o], d1[o])), hq[o], active,
-                                                slot, code, cnt);
+                const LinePart<G, LS> line = home;
+                if (r + 1 < G)
+                    home = home_of(q + NG);
+                find_or_put<G, LS, SuccVec, CL>(t, SuccVec::decode(smem, make_uint2(d0[o], d1[o])), hq[o], line,
+                                                active, slot, code, cnt);
             }
             const bool is_new = active && leader && code == kNew;
             if (t.parent && is_new) {
@@ -756,6 +808,7 @@ __device__ __forceinline__ bool expand_tile(uint32_t *smem, const TableView &t, 
         atomicAdd(&s_acc_edges, (unsigned long long)e32);
         atomicAdd(&s_acc_dead, (unsigned long long)d32);
     }
+    gather_counters(t, cnt);
     if constexpr (!DEFER_COUNTS) {
         __syncthreads();
         if (tid == 0) {
@@ -765,9 +818,9 @@ __device__ __forceinline__ bool expand_tile(uint32_t *smem, const TableView &t, 
                 atomicAdd(&lc->deadlocks, s_acc_dead);
             s_acc_edges = 0;
             s_acc_dead = 0;
+            flush_counters(t.status);
         }
     }
-    flush_counters(t, cnt);
     return s_abort != 0;
 }
 

@@ -24,6 +24,7 @@ struct LevelCounters {
 
 struct lhs_table {
     int device = 0;
+    int ncu = 0;               // the device's CUs
     uint64_t capacity = 0;
     uint32_t W = 0;
     uint32_t lines = 0;
@@ -38,7 +39,7 @@ struct lhs_table {
     uint64_t seed = 0;
     uint64_t *bucket = nullptr;
     uint32_t *data = nullptr;
-    lhs::DevStatus *status = nullptr;
+    lhs::DevStatus *status = nullptr;   // first member of a TableStatus
     hipStream_t last_stream = nullptr;
     // BFS buffers, allocated on first use by reach_explore and kept.
     uint32_t *frontier[2] = {nullptr, nullptr};

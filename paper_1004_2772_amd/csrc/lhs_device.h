@@ -46,6 +46,24 @@ struct DevStatus {
     unsigned long long merged;  // successors merged into an equal one of their pass (counted)
 };
 
+// A batched find-or-put has up to a million wavefronts, and almost every one
+// has a wait or a lost claim to report when a call's rows repeat.  On one
+// address such additions are served one after the other, some tens of
+// millions a second: they were most of the time of a call whose rows repeat.
+// So find-or-put adds to one of kStripes lines behind the table's status, by
+// workgroup, and read_status sums them; an expansion's workgroups add up in
+// LDS first.  A call of 2^18 rows of 16 words, half of them repeats, into
+// 2^20 slots: 98 us on one address, 42 us striped; 2^20 rows of 8 words into
+// 2^22 slots 224 and 90 us.
+struct alignas(128) CounterLine {
+    unsigned long long waits, cas_failures, lines, merged;
+};
+constexpr uint32_t kStripes = 64;
+struct TableStatus {
+    DevStatus st;
+    CounterLine stripe[kStripes];
+};
+
 // TableView::flags: counters to keep, and how expansions merge equal
 // successors of a pass (expand_tile)
 enum : uint32_t { kCountLines = 1, kCountMerged = 2, kNoMerge = 4, kNarrowTags = 8 };
@@ -215,6 +233,15 @@ __device__ __forceinline__ uint64_t hash_vec(const Vec &v, uint32_t W, uint64_t 
     return h;
 }
 
+// Clear a table's status and striped counters (a workgroup of at least
+// kStripes threads).
+__device__ __forceinline__ void zero_status(TableStatus *ts) {
+    if (threadIdx.x == 0)
+        ts->st = DevStatus{};
+    if (threadIdx.x < kStripes)
+        ts->stripe[threadIdx.x] = CounterLine{};
+}
+
 __device__ __forceinline__ void set_error(DevStatus *st, uint32_t code) {
     atomicCAS(&st->error, 0u, code);
 }
@@ -264,49 +291,78 @@ struct Group {
     }
 };
 
-// Snapshot of one line of LS slots: masks of empty slots and of slots whose
-// memo equals `memo` (any status), bit i = slot i of the line.  The line is
-// LS/2 16-byte chunks (two slots each); lane `sub` of a group of G loads
-// chunks sub, sub + G, ..., so every load instruction of the group covers one
-// contiguous 16*G-byte segment of the line.  With G >= LS every lane below
-// LS loads one slot and the others only take part in the ballots.
+// A lane's part of one line of LS slots, loaded by a group of G lanes.  The
+// line is LS/2 16-byte chunks (two slots each); lane `sub` loads chunks sub,
+// sub + G, ..., so every load instruction of the group covers one contiguous
+// 16*G-byte segment of the line.  With G >= LS every lane below LS loads one
+// slot and the others only take part in the ballots.
+template <int G, uint32_t LS>
+struct LinePart {
+    static constexpr uint32_t SPL = LS / G;               // slots per lane
+    static constexpr uint32_t Q = SPL <= 1 ? 1 : SPL / 2; // chunks per lane
+    uint4 x[Q];
+};
+
 template <int G, uint32_t LS, bool CL = false>
-__device__ __forceinline__ void line_masks(const Group<G> &g, const uint64_t *line_ptr, uint64_t memo,
-                                           uint32_t &empty, uint32_t &match) {
-    constexpr uint32_t SPL = LS / G;
-    uint32_t e = 0, m = 0;
-    if constexpr (SPL <= 1) {
+__device__ __forceinline__ LinePart<G, LS> load_line(const Group<G> &g, const uint64_t *line_ptr) {
+    using P = LinePart<G, LS>;
+    P p;
+    if constexpr (P::SPL <= 1) {
+        const uint64_t *q = line_ptr + ((uint32_t)G == LS ? g.sub : min(g.sub, LS - 1));
+        const uint64_t s0 = CL ? ld_coherent(q) : *q;
+        p.x[0] = make_uint4((uint32_t)s0, (uint32_t)(s0 >> 32), 0u, 0u);
+    } else {
+#pragma unroll
+        for (uint32_t q = 0; q < P::Q; ++q)
+            p.x[q] = ld_line16<CL>(reinterpret_cast<const uint4 *>(line_ptr) + q * G + g.sub);
+    }
+    return p;
+}
+
+// Masks of a loaded line's empty slots, of slots whose memo equals `memo`
+// (any status) and of done slots, bit i = slot i of the line.
+template <int G, uint32_t LS>
+__device__ __forceinline__ void line_masks(const Group<G> &g, const LinePart<G, LS> &p, uint64_t memo,
+                                           uint32_t &empty, uint32_t &match, uint32_t &done) {
+    using P = LinePart<G, LS>;
+    uint32_t e = 0, m = 0, d = 0;
+    if constexpr (P::SPL <= 1) {
         const bool own = (uint32_t)G == LS || g.sub < LS;
-        const uint64_t s0 = own ? (CL ? ld_coherent(line_ptr + g.sub) : line_ptr[g.sub]) : ~0ull;
+        const uint64_t s0 = ((uint64_t)p.x[0].y << 32) | p.x[0].x;
         constexpr uint32_t lm = LS == 32 ? 0xFFFFFFFFu : (1u << LS) - 1u;
         e = g.bits(__ballot(own && s0 == 0)) & lm;
         m = g.bits(__ballot(own && (s0 & ~kDone) == memo)) & lm;
+        d = g.bits(__ballot(own && (s0 & kDone))) & lm;
     } else {
-        constexpr uint32_t Q = SPL / 2;          // chunks per lane
-        const uint4 *p = reinterpret_cast<const uint4 *>(line_ptr);
-        uint4 x[Q];
 #pragma unroll
-        for (uint32_t q = 0; q < Q; ++q)
-            x[q] = ld_line16<CL>(p + q * G + g.sub);
-#pragma unroll
-        for (uint32_t q = 0; q < Q; ++q) {
-            const uint64_t s0 = ((uint64_t)x[q].y << 32) | x[q].x;
-            const uint64_t s1 = ((uint64_t)x[q].w << 32) | x[q].z;
+        for (uint32_t q = 0; q < P::Q; ++q) {
+            const uint64_t s0 = ((uint64_t)p.x[q].y << 32) | p.x[q].x;
+            const uint64_t s1 = ((uint64_t)p.x[q].w << 32) | p.x[q].z;
             if constexpr (G == 1) {
                 e |= ((uint32_t)(s0 == 0) | ((uint32_t)(s1 == 0) << 1)) << (2 * q);
                 m |= ((uint32_t)((s0 & ~kDone) == memo) | ((uint32_t)((s1 & ~kDone) == memo) << 1))
                      << (2 * q);
+                d |= (((uint32_t)(s0 >> 62) & 1u) | (((uint32_t)(s1 >> 62) & 1u) << 1)) << (2 * q);
             } else {
                 // chunk q*G + sub holds slots 2(q*G + sub) and 2(q*G + sub) + 1
                 e |= spread2(g.bits(__ballot(s0 == 0))) << (2 * q * G);
                 e |= spread2(g.bits(__ballot(s1 == 0))) << (2 * q * G + 1);
                 m |= spread2(g.bits(__ballot((s0 & ~kDone) == memo))) << (2 * q * G);
                 m |= spread2(g.bits(__ballot((s1 & ~kDone) == memo))) << (2 * q * G + 1);
+                d |= spread2(g.bits(__ballot((s0 & kDone) != 0))) << (2 * q * G);
+                d |= spread2(g.bits(__ballot((s1 & kDone) != 0))) << (2 * q * G + 1);
             }
         }
     }
     empty = e;
     match = m;
+    done = d;
+}
+
+// The home line of a vector with hash h.
+template <uint32_t LS>
+__device__ __forceinline__ uint32_t home_line(const TableView &t, uint64_t h) {
+    return (uint32_t)(h >> line_shift<LS>()) & t.line_mask;
 }
 
 // Row write by the group: 64-bit coherent stores when W is even (rows are
@@ -323,39 +379,45 @@ __device__ __forceinline__ void write_row(const Group<G> &g, uint32_t *row, cons
     }
 }
 
-// Row compare by the group, up to four pieces per lane in flight at once
+// Row compare by the group, up to B pieces per lane in flight at once
 // (pieces past the row's end are read as its last one).
-template <int G, class Vec>
-__device__ __forceinline__ bool row_equals(const Group<G> &g, const uint32_t *row, const Vec &v,
-                                           uint32_t W) {
+template <int G, uint32_t B, class Vec>
+__device__ __forceinline__ bool row_equals_by(const Group<G> &g, const uint32_t *row, const Vec &v, uint32_t W) {
     uint32_t diff = 0;
     if ((W & 1u) == 0) {
         const uint64_t *r2 = reinterpret_cast<const uint64_t *>(row);
         const uint32_t last = W / 2 - 1;
-        for (uint32_t j0 = g.sub; j0 <= last; j0 += 4 * G) {
-            uint64_t x[4];
+        for (uint32_t j0 = g.sub; j0 <= last; j0 += B * G) {
+            uint64_t x[B];
 #pragma unroll
-            for (uint32_t k = 0; k < 4; ++k)
+            for (uint32_t k = 0; k < B; ++k)
                 x[k] = ld_coherent(r2 + min(j0 + k * G, last));
 #pragma unroll
-            for (uint32_t k = 0; k < 4; ++k) {
+            for (uint32_t k = 0; k < B; ++k) {
                 const uint32_t j = min(j0 + k * G, last);
                 diff |= ((uint32_t)x[k] ^ v.get(2 * j)) | ((uint32_t)(x[k] >> 32) ^ v.get(2 * j + 1));
             }
         }
     } else {
         const uint32_t last = W - 1;
-        for (uint32_t j0 = g.sub; j0 <= last; j0 += 4 * G) {
-            uint32_t x[4];
+        for (uint32_t j0 = g.sub; j0 <= last; j0 += B * G) {
+            uint32_t x[B];
 #pragma unroll
-            for (uint32_t k = 0; k < 4; ++k)
+            for (uint32_t k = 0; k < B; ++k)
                 x[k] = ld_coherent(row + min(j0 + k * G, last));
 #pragma unroll
-            for (uint32_t k = 0; k < 4; ++k)
+            for (uint32_t k = 0; k < B; ++k)
                 diff |= x[k] ^ v.get(min(j0 + k * G, last));
         }
     }
     return g.all(diff == 0);
+}
+template <int G, class Vec>
+__device__ __forceinline__ bool row_equals(const Group<G> &g, const uint32_t *row, const Vec &v, uint32_t W) {
+    if constexpr (G == 1)
+        return row_equals_by<G, 4>(g, row, v, W);
+    else
+        return ((W & 1u) ? W : W / 2) <= G ? row_equals_by<G, 1>(g, row, v, W) : row_equals_by<G, 2>(g, row, v, W);
 }
 
 // One find-or-put per group of G lanes (G = 1, 4, 8 or 16) on a table of
@@ -380,9 +442,11 @@ __device__ __forceinline__ bool row_equals(const Group<G> &g, const uint32_t *ro
 //    writes the row, waits for the stores, and the leader stores
 //    OCC|DONE|memo; result "new".  Lost: the CAS returned the slot's value;
 //    if its memo is ours it becomes a match candidate, otherwise walk on.
-//  - match candidate: load the slot until DONE (a bounded wait, the paper's
-//    write-busy "lock"), then compare the stored row; equal means "seen",
-//    otherwise walk on.
+//  - match candidate: unless the snapshot (or the failed CAS) already showed
+//    DONE, load the slot until DONE (a bounded wait, the paper's write-busy
+//    "lock"); then compare the stored row; equal means "seen", otherwise walk
+//    on.  DONE never goes away, and the row loads are issued after it was
+//    observed.
 //
 // SIMT forward progress: every loop iteration runs the claim phase (CAS,
 // row write, publish) for all lanes before the wait phase of any lane, and
@@ -390,17 +454,20 @@ __device__ __forceinline__ bool row_equals(const Group<G> &g, const uint32_t *ro
 // slot claimed by a group of its own wavefront therefore finds it already
 // published; a claim made by another wavefront is published without that
 // wavefront waiting on anything first.
+//
+// `first` is the home line, loaded by the caller: a caller with several
+// operations loads the next one's while this one runs.
 template <int G, uint32_t LS, class Vec, bool CL = false>
-__device__ __forceinline__ void find_or_put(const TableView &t, const Vec &v, uint64_t h, bool active,
-                                            uint32_t &out_slot, uint32_t &out_code,
+__device__ __forceinline__ void find_or_put(const TableView &t, const Vec &v, uint64_t h, LinePart<G, LS> first,
+                                            bool active, uint32_t &out_slot, uint32_t &out_code,
                                             LaneCounters &cnt) {
     const Group<G> g;
     const uint64_t memo = kOcc | (h & kMemoMask);
     const uint32_t start = (uint32_t)h & (LS - 1);
     const uint32_t step = probe_step(h, t.probe);
-    uint32_t line = (uint32_t)(h >> line_shift<LS>()) & t.line_mask;
+    uint32_t line = home_line<LS>(t, h);
     uint32_t rounds = 0;
-    uint32_t cand = 0, empty = 0;  // walk-ordered: bit k <-> slot start+k (mod LS)
+    uint32_t cand = 0, empty = 0, donem = 0;  // walk-ordered: bit k <-> slot start+k (mod LS)
     bool have_line = false;
     out_slot = kNoSlot;
     out_code = kFull;
@@ -415,10 +482,13 @@ __device__ __forceinline__ void find_or_put(const TableView &t, const Vec &v, ui
                     set_error(t.status, 3u /* LHS_EFULL */);
                 break;
             }
-            uint32_t e, m;
-            line_masks<G, LS, CL>(g, t.bucket + (uint64_t)line * LS, memo, e, m);
+            if (rounds)
+                first = load_line<G, LS, CL>(g, t.bucket + (uint64_t)line * LS);
+            uint32_t e, m, d;
+            line_masks<G, LS>(g, first, memo, e, m, d);
             empty = rotr_line<LS>(e, start);
             cand = rotr_line<LS>(e | m, start);
+            donem = rotr_line<LS>(d, start);
             have_line = true;
             cnt.lines += g.leader();
         }
@@ -434,6 +504,7 @@ __device__ __forceinline__ void find_or_put(const TableView &t, const Vec &v, ui
         uint64_t *bp = t.bucket + slot;
         uint32_t *row = t.data + (uint64_t)slot * t.W;
         bool match = ((empty >> k) & 1u) == 0;
+        bool known_done = (donem >> k) & 1u;
         bool finished = false;
 
         // ---- claim phase ------------------------------------------------
@@ -454,11 +525,12 @@ __device__ __forceinline__ void find_or_put(const TableView &t, const Vec &v, ui
             } else {
                 cnt.cas_failures += g.leader();
                 match = (old & ~kDone) == memo;
+                known_done = (old & kDone) != 0;
             }
         }
         // ---- wait + compare phase --------------------------------------
         if (match && !finished) {
-            uint64_t cur = ld_coherent(bp);
+            uint64_t cur = known_done ? kDone : ld_coherent(bp);
             if (!(cur & kDone)) {
                 cnt.waits += g.leader();
                 uint32_t spins = 0;
@@ -484,6 +556,14 @@ __device__ __forceinline__ void find_or_put(const TableView &t, const Vec &v, ui
         if (finished)
             break;
     }
+}
+
+template <int G, uint32_t LS, class Vec, bool CL = false>
+__device__ __forceinline__ void find_or_put(const TableView &t, const Vec &v, uint64_t h, bool active,
+                                            uint32_t &out_slot, uint32_t &out_code, LaneCounters &cnt) {
+    const Group<G> g;
+    find_or_put<G, LS, Vec, CL>(t, v, h, load_line<G, LS, CL>(g, t.bucket + (uint64_t)home_line<LS>(t, h) * LS),
+                                active, out_slot, out_code, cnt);
 }
 
 // ---------------------------------------------------------------------------
@@ -713,7 +793,7 @@ __device__ __forceinline__ void find_or_put_wave(const TableView &t, WaveScratch
     const uint64_t memo = kOcc | (h & kMemoMask);
     const uint32_t start = (uint32_t)h & (LS - 1);
     const uint32_t step = probe_step(h, t.probe);
-    uint32_t line = (uint32_t)(h >> line_shift<LS>()) & t.line_mask;
+    uint32_t line = home_line<LS>(t, h);
     uint32_t rounds = 0, cand = 0, empty = 0, donem = 0, slot = 0;
     bool have_line = false, finished = !active;
     bool matched = false;   // `slot` holds a done match whose row is still to be compared
@@ -835,23 +915,21 @@ __device__ __forceinline__ uint32_t wave_sum(uint32_t x) {
     return x;
 }
 
-// Flush lane counters into the table status: one atomic per wavefront.
-// Must be called by all 64 lanes of the wavefront.
-// Lines probed are added only when the table counts them (one more atomic
-// per wavefront, on by request: see lhs_set_counters).
-__device__ __forceinline__ void flush_counters(const TableView &t, const LaneCounters &c) {
+// Add a wavefront's lane counters to the table's striped counters; t.status
+// is a table's own (the first member of its TableStatus).  Must be called by
+// all 64 lanes of the wavefront.  Lines probed are added only when the table
+// counts them (on by request: see lhs_set_counters).
+__device__ __forceinline__ void flush_counters_striped(const TableView &t, const LaneCounters &c) {
     const uint32_t w = wave_sum(c.waits), f = wave_sum(c.cas_failures);
     const uint32_t l = (t.flags & kCountLines) ? wave_sum(c.lines) : 0u;
-    const uint32_t mg = (t.flags & kCountMerged) ? wave_sum(c.merged) : 0u;
     if (__lane_id() == 0) {
+        CounterLine &o = reinterpret_cast<TableStatus *>(t.status)->stripe[blockIdx.x & (kStripes - 1)];
         if (w)
-            atomicAdd(&t.status->wait_hits, (unsigned long long)w);
+            atomicAdd(&o.waits, (unsigned long long)w);
         if (f)
-            atomicAdd(&t.status->cas_failures, (unsigned long long)f);
+            atomicAdd(&o.cas_failures, (unsigned long long)f);
         if (l)
-            atomicAdd(&t.status->lines, (unsigned long long)l);
-        if (mg)
-            atomicAdd(&t.status->merged, (unsigned long long)mg);
+            atomicAdd(&o.lines, (unsigned long long)l);
     }
 }
 

@@ -4,7 +4,7 @@
 // table, memoised hash, empty = 0):
 //   bucket : uint64[capacity]            8 B/slot, 8/16/32 slots per line
 //   data   : uint32[capacity][W]         row of slot i at data + i*W
-//   status : DevStatus                   sticky error + counters
+//   status : TableStatus                 sticky error + counters
 #include <algorithm>
 #include <cstring>
 #include <new>
@@ -30,56 +30,74 @@ struct LdsRow {
     }
 };
 
-// Batched find-or-put.  A workgroup takes a tile of 256 consecutive input
-// rows: it stages them into LDS with coalesced loads (rows padded to an odd
-// stride so that lanes reading different rows hit different banks), hashes
-// each row with one lane, then runs find-or-put.  G == 1: one operation per
-// lane with wavefront-cooperative line and row accesses (256 operations in
-// flight per workgroup); the lane keeps its hash and result in registers and
-// writes seen/index itself (lane i <-> row i: coalesced).  G > 1: one group
-// of G lanes per operation (256/G in flight, G rounds per tile); hashes and
-// results go through LDS so that seen/index are written coalesced.
+// Batched find-or-put.  A workgroup takes a tile of `tile_rows` consecutive
+// input rows: it stages them into LDS with coalesced loads, up to four in
+// flight per lane (rows padded to an odd stride so that lanes reading
+// different rows hit different banks), hashes each row with one lane, then
+// runs find-or-put.  G == 1: tiles of 256 rows, one operation per lane with
+// wavefront-cooperative line and row accesses; the lane keeps its hash and
+// result in registers and writes seen/index itself (lane i <-> row i:
+// coalesced).  G > 1: one group of G lanes per operation, 256/G at a time,
+// the next one's home line loaded while one runs; hashes and results go
+// through LDS so that seen/index are written coalesced.
 // One lane per operation with 8-slot lines (the tuned shape of large
 // tables): at most 80 VGPRs, six waves per SIMD, as the LDS of a 16-word
-// tile allows (measured 0.8 % faster than five).
+// tile allows (measured 0.8 % faster than five); at most seven with G > 1.
 template <int G, uint32_t LS>
-__global__ __launch_bounds__(kBlock, (G == 1 && LS == 8) ? 6 : 1) void k_find_or_put(TableView t, const uint32_t *__restrict__ in,
+__global__ __launch_bounds__(kBlock, LS == 8 ? (G == 1 ? 6 : 7) : 1) void k_find_or_put(TableView t, const uint32_t *__restrict__ in,
                                                         uint64_t n, uint8_t *__restrict__ seen,
                                                         uint32_t *__restrict__ index,
-                                                        uint32_t magicW) {
+                                                        uint32_t magicW, uint32_t tile_rows) {
     extern __shared__ uint32_t smem[];
     const uint32_t W = t.W, stride = W | 1u;
-    uint32_t *tile = smem;                                          // kBlock x stride
-    uint64_t *hs = reinterpret_cast<uint64_t *>(tile + kBlock * stride);
-    uint32_t *res_slot = reinterpret_cast<uint32_t *>(hs + kBlock);
-    uint32_t *res_code = res_slot + kBlock;
+    if constexpr (G == 1)
+        tile_rows = kBlock;
+    uint32_t *tile = smem;                                          // tile_rows x stride
+    uint64_t *hs = reinterpret_cast<uint64_t *>(tile + tile_rows * stride);
+    uint32_t *res_slot = reinterpret_cast<uint32_t *>(hs + tile_rows);
+    uint32_t *res_code = res_slot + tile_rows;
     constexpr uint32_t NG = kBlock / G;
     const uint32_t tid = threadIdx.x, gi = tid / G;
     LaneCounters cnt;
-    for (uint64_t base = (uint64_t)blockIdx.x * kBlock; base < n;
-         base += (uint64_t)gridDim.x * kBlock) {
-        const uint32_t rows = (uint32_t)min<uint64_t>(kBlock, n - base);
+    for (uint64_t base = (uint64_t)blockIdx.x * tile_rows; base < n;
+         base += (uint64_t)gridDim.x * tile_rows) {
+        const uint32_t rows = (uint32_t)min<uint64_t>(tile_rows, n - base);
         const uint32_t words = rows * W;
         const uint32_t *src = in + base * W;
         __syncthreads();
         if ((W & 3u) == 0 && (reinterpret_cast<uintptr_t>(in) & 15u) == 0) {
             // rows of a multiple of four words, 16-byte aligned: 16-byte
-            // loads, each inside one row
+            // loads, each inside one row (lanes past the end repeat the last)
             typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
             const u32x4 *src4 = reinterpret_cast<const u32x4 *>(src);
-            for (uint32_t f4 = tid; f4 < words / 4; f4 += kBlock) {
-                const uint32_t f = 4 * f4, r = __umulhi(f, magicW);
-                const u32x4 x = __builtin_nontemporal_load(src4 + f4);   // read once
-                uint32_t *dst = tile + r * stride + (f - r * W);
-                dst[0] = x.x;
-                dst[1] = x.y;
-                dst[2] = x.z;
-                dst[3] = x.w;
+            const uint32_t last = words / 4 - 1;
+            for (uint32_t f0 = tid; f0 <= last; f0 += 4 * kBlock) {
+                u32x4 x[4];
+#pragma unroll
+                for (uint32_t k = 0; k < 4; ++k)
+                    x[k] = __builtin_nontemporal_load(src4 + min(f0 + k * kBlock, last));   // read once
+#pragma unroll
+                for (uint32_t k = 0; k < 4; ++k) {
+                    const uint32_t f = 4 * min(f0 + k * kBlock, last), r = __umulhi(f, magicW);
+                    uint32_t *dst = tile + r * stride + (f - r * W);
+                    dst[0] = x[k].x;
+                    dst[1] = x[k].y;
+                    dst[2] = x[k].z;
+                    dst[3] = x[k].w;
+                }
             }
         } else {
-            for (uint32_t f = tid; f < words; f += kBlock) {
-                const uint32_t r = W == 1 ? f : __umulhi(f, magicW);
-                tile[r * stride + (f - r * W)] = src[f];
+            const uint32_t last = words - 1;
+            for (uint32_t f0 = tid; f0 <= last; f0 += 4 * kBlock) {
+                uint32_t x[4];
+#pragma unroll
+                for (uint32_t k = 0; k < 4; ++k)
+                    x[k] = src[min(f0 + k * kBlock, last)];
+#pragma unroll
+                for (uint32_t k = 0; k < 4; ++k) {
+                    const uint32_t f = min(f0 + k * kBlock, last), r = W == 1 ? f : __umulhi(f, magicW);
+                    tile[r * stride + (f - r * W)] = x[k];
+                }
             }
         }
         __syncthreads();
@@ -103,12 +121,17 @@ __global__ __launch_bounds__(kBlock, (G == 1 && LS == 8) ? 6 : 1) void k_find_or
                     __builtin_nontemporal_store(slot, index + base + tid);
             }
         } else {
-            for (uint32_t r = 0; r < G; ++r) {
-                const uint32_t op = r * NG + gi;
+            const Group<G> g;
+            auto home_of = [&](uint32_t op) {
+                return load_line<G, LS>(g, t.bucket + (uint64_t)home_line<LS>(t, hs[op < rows ? op : 0]) * LS);
+            };
+            for (uint32_t r0 = 0; r0 < rows; r0 += NG) {
+                const uint32_t op = r0 + gi;
                 const bool active = op < rows;
                 const uint32_t o = active ? op : 0;
+                const LinePart<G, LS> line = home_of(op);
                 uint32_t slot, code;
-                find_or_put<G, LS>(t, LdsRow{tile + o * stride}, hs[o], active, slot, code, cnt);
+                find_or_put<G, LS>(t, LdsRow{tile + o * stride}, hs[o], line, active, slot, code, cnt);
                 if (active && (tid & (G - 1)) == 0) {
                     res_slot[op] = slot;
                     res_code[op] = code;
@@ -123,7 +146,7 @@ __global__ __launch_bounds__(kBlock, (G == 1 && LS == 8) ? 6 : 1) void k_find_or
             }
         }
     }
-    flush_counters(t, cnt);
+    flush_counters_striped(t, cnt);
 }
 
 // Zero n 64-bit words (p 16-byte aligned): 16-byte stores, so one
@@ -139,8 +162,8 @@ __global__ void k_zero_u64(uint64_t *p, uint64_t n) {
         p[n - 1] = 0;
 }
 
-__global__ void k_zero_status(DevStatus *st) {
-    *st = DevStatus{};
+__global__ void k_zero_status(TableStatus *ts) {
+    zero_status(ts);
 }
 
 // Done slots are scanned in chunks of kLineSlots slots (any line width).
@@ -216,6 +239,22 @@ uint32_t grid_for(uint64_t items, uint32_t per_block) {
     return (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(b, kMaxGrid));
 }
 
+// Rows per workgroup of a find-or-put with tps > 1 lanes per operation, a
+// multiple of the 256/tps operations that run at once.  A tile's operations
+// beyond those are a serial chain, so a call that cannot fill the GPU with
+// full tiles takes smaller ones: as many rows as spread it over eight
+// workgroups per CU.  Nor more rows than let eight workgroups share a CU's
+// LDS (160 KB).  A table of 2^20 slots built by four calls of 30 000 8-word
+// rows, eight lanes each: 100 us with 256-row tiles, 44 us so; 10^6 lookups
+// of 32-word rows, four lanes each: 131 and 94 us.
+uint32_t fop_tile_rows(uint32_t tps, uint32_t W, uint64_t n, uint32_t ncu) {
+    const uint32_t at_once = kBlock / tps;
+    const uint64_t most = 8ull * ncu * at_once;
+    const uint64_t by_n = (n + most - 1) / most;
+    const uint32_t by_lds = 20480 / (((W | 1u) + 4u) * sizeof(uint32_t)) / at_once;
+    return at_once * (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>({by_n, by_lds, tps}));
+}
+
 // Per-block done counts and their exclusive prefix (host).  Returns total.
 lhs_status done_offsets(lhs_table *t, std::vector<uint64_t> &offsets, uint32_t **d_counts_out,
                         uint64_t *total) {
@@ -254,15 +293,16 @@ lhs_status launch_find_or_put(lhs_table *t, const uint32_t *d_states, uint64_t n
                               uint32_t *d_index, hipStream_t s) {
     if (!n)
         return LHS_OK;
-    // G == 1 needs only the row tile; G > 1 also hashes and results
     const uint32_t tps = tps_find_or_put(t);
-    const size_t lds = (size_t)kBlock * ((t->W | 1u) + (tps > 1 ? 4u : 0u)) * sizeof(uint32_t);
-    const dim3 grid(grid_for(n, kBlock)), block(kBlock);
+    const uint32_t rows = tps > 1 ? fop_tile_rows(tps, t->W, n, (uint32_t)t->ncu) : kBlock;
+    // G == 1 needs only the row tile; G > 1 also hashes and results
+    const size_t lds = (size_t)rows * ((t->W | 1u) + (tps > 1 ? 4u : 0u)) * sizeof(uint32_t);
+    const dim3 grid(grid_for(n, rows)), block(kBlock);
     const TableView v = view(t);
     const uint32_t mw = div_magic(t->W);
     const lhs_status rc = with_shape(tps, t->line_slots, [&](auto G, auto L) {
         hipLaunchKernelGGL((k_find_or_put<decltype(G)::value, decltype(L)::value>), grid, block, lds, s,
-                           v, d_states, n, d_seen, d_index, mw);
+                           v, d_states, n, d_seen, d_index, mw, rows);
         return LHS_OK;
     });
     if (rc != LHS_OK)
@@ -277,7 +317,14 @@ lhs_status launch_zero_u64(uint64_t *p, uint64_t n, hipStream_t s) {
 
 lhs_status read_status(lhs_table *t, DevStatus *out) {
     LHS_HIP(hipStreamSynchronize(t->last_stream));
-    LHS_HIP(hipMemcpy(out, t->status, sizeof(DevStatus), hipMemcpyDeviceToHost));
+    TableStatus ts;
+    LHS_HIP(hipMemcpy(&ts, t->status, sizeof(ts), hipMemcpyDeviceToHost));
+    *out = ts.st;
+    for (const CounterLine &c : ts.stripe) {
+        out->wait_hits += c.waits;
+        out->cas_failures += c.cas_failures;
+        out->lines += c.lines;
+    }
     return LHS_OK;
 }
 
@@ -335,13 +382,14 @@ lhs_status lhs_create_ex(uint64_t capacity, uint32_t state_words, const lhs_conf
     // visited every line, i.e. when the table has no empty slot
     t->max_rounds = t->lines;
     t->seed = kDefaultSeed;
-    if (hipGetDevice(&t->device) != hipSuccess) {
+    if (hipGetDevice(&t->device) != hipSuccess ||
+        hipDeviceGetAttribute(&t->ncu, hipDeviceAttributeMultiprocessorCount, t->device) != hipSuccess) {
         delete t;
         return LHS_EDEVICE;
     }
     if (hipMalloc(&t->bucket, capacity * sizeof(uint64_t)) != hipSuccess ||
         hipMalloc(&t->data, capacity * (uint64_t)state_words * sizeof(uint32_t)) != hipSuccess ||
-        hipMalloc(&t->status, sizeof(DevStatus)) != hipSuccess) {
+        hipMalloc(&t->status, sizeof(TableStatus)) != hipSuccess) {
         (void)hipGetLastError();
         lhs_destroy(t);
         return LHS_ENOMEM;
@@ -386,7 +434,7 @@ lhs_status lhs_clear(lhs_table *t, void *hip_stream) {
     t->has_parents = false;
     if (launch_zero_u64(t->bucket, t->capacity, s) != LHS_OK)
         return LHS_EDEVICE;
-    hipLaunchKernelGGL(k_zero_status, dim3(1), dim3(1), 0, s, t->status);
+    hipLaunchKernelGGL(k_zero_status, dim3(1), dim3(kStripes), 0, s, reinterpret_cast<TableStatus *>(t->status));
     return hipGetLastError() == hipSuccess ? LHS_OK : LHS_EDEVICE;
 }
 

@@ -63,7 +63,7 @@ __global__ __launch_bounds__(kExpandBlock, LS == 8 ? 4 : 1) void k_expand(TableV
                                                                       limit, tcap, o))
             break;
     }
-    expand_end<G, false, true>(smem, m.W, tcap, nullptr, lc, limit, o);
+    expand_end<G, false, true>(smem, m.W, tcap, nullptr, lc, limit, t.status, o);
 }
 
 // Undo the inserts of a discarded level: zero the slots listed in its
@@ -124,7 +124,7 @@ __global__ __launch_bounds__(kExpandBlock, LS == 8 ? 4 : 1) void k_expand_graph(
                                                                       limit, tcap, o))
             break;
     }
-    expand_end<G, false, true>(smem, m.W, tcap, nullptr, lc, limit, o);
+    expand_end<G, false, true>(smem, m.W, tcap, nullptr, lc, limit, t.status, o);
 }
 
 // The host loop's per-level bookkeeping, on the device (one thread).

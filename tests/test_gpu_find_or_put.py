@@ -292,3 +292,32 @@ def test_max_capacity_2p32(lhs, W, tps):
     pos = np.searchsorted(slots, idx)
     assert np.array_equal(slots[pos], idx)
     assert np.array_equal(got[pos], stream)
+
+
+@pytest.mark.parametrize("tps", [4, 8, 16])
+@pytest.mark.parametrize("W", [1, 6, 32])
+def test_tile_row_edges(lhs, W, tps):
+    """Call sizes where a call's rows per workgroup change (with tps > 1 lanes
+    per operation: one row, one short of and one over a multiple of the
+    operations that run at once, and of what fills the GPU once and twice)."""
+    import torch
+    at_once = 256 // tps
+    fill = 8 * torch.cuda.get_device_properties(0).multi_processor_count * at_once
+    sizes = [1, at_once - 1, at_once, at_once + 1, fill - 1, fill + 1, 2 * fill, 2 * fill + 1]
+    print(f"\n[fop] tile rows W={W} tps={tps} sizes={sizes}", flush=True)
+    rows, order = gen.dup_stream(300 + W, sum(sizes) // 2 + 1, W, 2)
+    stream = gen.gather(rows, order)[: sum(sizes)]
+    o_seen, o_id, distinct = oracle.stream(stream)
+    dev = dev_u32(stream)
+    seen = torch.empty(len(stream), dtype=torch.uint8, device="cuda")
+    idx = torch.empty(len(stream), dtype=torch.int32, device="cuda")
+    with lhs.Table(1 << 20, W) as t:
+        t.set_threads_per_state(tps)
+        bounds, at = [], 0
+        for n in sizes:
+            t.find_or_put(dev[at:at + n], seen[at:at + n], idx[at:at + n])
+            bounds.append((at, at + n))
+            at += n
+        t.check()
+        check_stream_batches(o_id, distinct, seen.cpu().numpy(), idx.cpu().numpy().view(np.uint32), bounds)
+        assert t.count() == distinct
