@@ -71,7 +71,7 @@ __global__ void k_async_init(AsyncCtl *ctl, LevelCounters *lc) {
     lc->deadlocks = 0;
 }
 
-template <int G, uint32_t LS>
+template <int G, uint32_t LS, class R>
 __global__ __launch_bounds__(kExpandBlock, LS == 8 ? 4 : 1) void k_explore_async(TableView t, ModelView m, uint32_t *queue,
                                                                 LevelCounters *lc, AsyncCtl *ctl,
                                                                 uint32_t limit, uint32_t tcap) {
@@ -80,7 +80,7 @@ __global__ __launch_bounds__(kExpandBlock, LS == 8 ? 4 : 1) void k_explore_async
     enum : uint32_t { kStop = 0, kExpand = 1, kPublish = 2 };
     __shared__ uint32_t s_from, s_take, s_act;
     const uint32_t tid = threadIdx.x;
-    uint32_t *nbuf = expand_nbuf<G>(smem, m.W, tcap);
+    uint32_t *nbuf = expand_nbuf<G, R>(smem, m.W, tcap);
     // thread 0: the owned chunk is queue[base, base + kChunk), its first
     // `used` entries already taken.  s_found = new states this workgroup has
     // discovered (appended or still buffered) that ctl->work holds
@@ -149,7 +149,7 @@ __global__ __launch_bounds__(kExpandBlock, LS == 8 ? 4 : 1) void k_explore_async
         }
         // new states stay buffered across tiles while this chunk has work
         const bool aborted =
-            expand_tile<G, LS, true, true, true, true>(smem, t, m, queue, from, n, queue, lc, limit, tcap);
+            expand_tile<G, LS, R, true, true, true, true>(smem, t, m, queue, from, n, queue, lc, limit, tcap);
         if (tid == 0) {
             // discovered - expanded, after the discoveries are counted
             const uint32_t now = s_pushed + s_nnew;
@@ -160,7 +160,7 @@ __global__ __launch_bounds__(kExpandBlock, LS == 8 ? 4 : 1) void k_explore_async
             break;
     }
     // counts kept in LDS over the launch (and, after an abort, the buffer)
-    expand_end<G, true>(smem, m.W, tcap, queue, lc, limit, t.status);
+    expand_end<G, R, true>(smem, m.W, tcap, queue, lc, limit, t.status);
 }
 
 }  // namespace
@@ -191,9 +191,10 @@ lhs_status explore_async(lhs_table *t, const reach_model *m, const uint2 *d_tran
     const uint32_t limit =
         m->state_cap ? (uint32_t)std::min<uint64_t>(m->state_cap, 0xFFFFFFFFull) : 0xFFFFFFFFu;
     const uint32_t tc = trans_lds_entries(mv.P, mv.L, mv.K);
-    const size_t lds = expand_lds_bytes(mv.W, tc, tps_expand(t));
-    rc = with_shape(tps_expand(t), t->line_slots, [&](auto G, auto L) {
-        const void *fn = (const void *)k_explore_async<decltype(G)::value, decltype(L)::value>;
+    const bool bytes = rows_fit_bytes(m);
+    const size_t lds = expand_lds_bytes(mv.W, tc, tps_expand(t), bytes);
+    rc = with_tile(tps_expand(t), t->line_slots, bytes, [&](auto G, auto L, auto R) {
+        const void *fn = (const void *)k_explore_async<decltype(G)::value, decltype(L)::value, decltype(R)>;
         int ncu = 0, per_cu = 0, dev = 0;
         if (hipGetDevice(&dev) != hipSuccess ||
             hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
@@ -202,7 +203,7 @@ lhs_status explore_async(lhs_table *t, const reach_model *m, const uint2 *d_tran
             return LHS_EDEVICE;
         // the resident workgroups; waits are bounded, so the protocol needs
         // no co-residency guarantee
-        hipLaunchKernelGGL((k_explore_async<decltype(G)::value, decltype(L)::value>),
+        hipLaunchKernelGGL((k_explore_async<decltype(G)::value, decltype(L)::value, decltype(R)>),
                            dim3(exploration_grid(t, (uint64_t)ncu * per_cu)),
                            dim3(kExpandBlock), lds, s, tv, mv, queue, t->level, d_ctl, limit, tc);
         return hipGetLastError() == hipSuccess ? LHS_OK : LHS_EDEVICE;

@@ -31,7 +31,7 @@ constexpr uint32_t kMaxBatch = 1024;   // models per call (tile prefix lives in 
 
 // With 8-slot lines, at least four waves per SIMD (at most 128 VGPRs): four
 // workgroups per CU, as the LDS layout allows.  Wider lines would spill.
-template <int G, uint32_t LS>
+template <int G, uint32_t LS, class R>
 __global__ __launch_bounds__(kExpandBlock, LS == 8 ? 4 : 1) void k_batch_persistent(const ModelState *__restrict__ ms,
                                                                    ModelProgress *mp, LevelState *lv,
                                                                    QueueState *qs, QCell *ring,
@@ -86,7 +86,7 @@ __global__ __launch_bounds__(kExpandBlock, LS == 8 ? 4 : 1) void k_batch_persist
         const uint32_t rows_per = ld_coherent(&L.tile_rows);
         const uint64_t base = (uint64_t)j * rows_per;
         const uint32_t rows = (uint32_t)min<uint64_t>(rows_per, n_front - base);
-        expand_tile<G, LS, true>(smem, M.t, M.m, front, base, rows, next, M.lc, limit, tcap);
+        expand_tile<G, LS, R, true>(smem, M.t, M.m, front, base, rows, next, M.lc, limit, tcap);
         // this workgroup's stores of the tile are complete before it counts
         // the tile as done
         wait_vm_complete();
@@ -177,7 +177,7 @@ struct BatchModel {
 
 namespace lhs {
 
-lhs_status explore_prefix(lhs_table *t, const TableView &tv, const ModelView &mv, uint64_t cap, PrefixArea *d,
+lhs_status explore_prefix(lhs_table *t, const TableView &tv, const ModelView &mv, bool bytes, uint64_t cap, PrefixArea *d,
                           PrefixArea *h, hipStream_t s, PrefixOut &out) {
     // level 0 (s0 at frontier[0][0]) is tile 0 of queue position 0
     const size_t head = offsetof(PrefixArea, levels);
@@ -210,9 +210,9 @@ lhs_status explore_prefix(lhs_table *t, const TableView &tv, const ModelView &mv
     LHS_HIP(hipGetLastError());
     const uint32_t tps = tps_expand(t);
     const uint32_t tcap = trans_lds_entries(mv.P, mv.L, mv.K);
-    const size_t lds = (size_t)expand_lds_words(mv.W, tcap, tps) * sizeof(uint32_t);
-    lhs_status rc = with_shape(tps, t->line_slots, [&](auto G, auto LS) {
-        const void *fn = (const void *)k_batch_persistent<decltype(G)::value, decltype(LS)::value>;
+    const size_t lds = expand_lds_bytes(mv.W, tcap, tps, bytes);
+    lhs_status rc = with_tile(tps, t->line_slots, bytes, [&](auto G, auto LS, auto R) {
+        const void *fn = (const void *)k_batch_persistent<decltype(G)::value, decltype(LS)::value, decltype(R)>;
         int dev = 0, ncu = 0, per_cu = 0;
         if (hipGetDevice(&dev) != hipSuccess ||
             hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
@@ -285,6 +285,7 @@ static lhs_status reach_explore_batch_impl(const reach_model *const *models, uin
     std::vector<BatchModel> bm(n);
     lhs_status rc = LHS_OK;
     uint32_t max_W = 1, tcap = 0, tps = 0, ls = 0;
+    bool bytes = true;   // one launch, one element type of the LDS rows
     // shape of the internal tables: the tuned batch choice for the widest model
     uint32_t widest = 1;
     for (uint32_t i = 0; i < n; ++i)
@@ -300,6 +301,7 @@ static lhs_status reach_explore_batch_impl(const reach_model *const *models, uin
         b.m = models[i];
         b.W = b.m->n_procs + b.m->n_shared;
         max_W = std::max(max_W, b.W);
+        bytes = bytes && rows_fit_bytes(b.m);
         tcap = std::max(tcap, trans_lds_entries(b.m->n_procs, b.m->n_locals, b.m->trans_per_local));
         if (tables && tables[i]) {
             b.t = tables[i];
@@ -456,14 +458,14 @@ static lhs_status reach_explore_batch_impl(const reach_model *const *models, uin
                 LHS_OK)
             rc = LHS_EDEVICE;
     }
-    const size_t lds = (size_t)expand_lds_words(max_W, tcap, tps) * sizeof(uint32_t);
+    const size_t lds = expand_lds_bytes(max_W, tcap, tps, bytes);
 
     // ---- exploration -------------------------------------------------------
     if (rc == LHS_OK && !host_loop) {
         int ncu = 0, per_cu = 0;
         const void *fn = nullptr;
-        (void)with_shape(tps, ls, [&](auto G, auto L) {
-            fn = (const void *)k_batch_persistent<decltype(G)::value, decltype(L)::value>;
+        (void)with_tile(tps, ls, bytes, [&](auto G, auto L, auto R) {
+            fn = (const void *)k_batch_persistent<decltype(G)::value, decltype(L)::value, decltype(R)>;
             return LHS_OK;
         });
         if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||

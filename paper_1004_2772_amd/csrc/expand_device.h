@@ -40,11 +40,26 @@ struct SegFront {
     uint32_t tiles[kSegs + 1];
 };
 
+// A tile's rows in LDS hold their words as uint32_t, or as bytes where every
+// word of every reachable state fits one (rows_fit_bytes).  LDS is what
+// bounds how many tiles a CU has in flight: 256 rows of 31 words and a table
+// of 1536 transitions leave room for two workgroups with uint32_t rows and
+// four with bytes, and a row's hash and compare read four words at once.
+// Measured with uint32_t rows and with bytes: search to 2^27 states 21.0 and
+// 20.0 ms, 64-model batch 9.5 and 9.1 ms, a burst of 96 served queries 19.6
+// and 17.3 ms.  (Five workgroups per CU: 21.6 ms, the registers spill.)
+// Rows start at a word and have an odd stride in words.
+template <class R>
+__host__ __device__ constexpr uint32_t row_stride(uint32_t W) {
+    return (sizeof(R) == 1 ? (W + 3) / 4 : W) | 1u;
+}
+
 // Successor of an LDS row: row with s[p] = target and, if ew != NONE,
 // s[ew] = ev (ew already offset by P).  Descriptor: x = row word offset from
 // the LDS base | p << 16 | ew << 24 (0xFF = no effect), y = target | ev << 16.
+template <class R>
 struct SuccVec {
-    const uint32_t *row;
+    const R *row;
     uint32_t p, target, ew, ev;
     __device__ __forceinline__ uint32_t get(uint32_t i) const {
         uint32_t x = row[i];
@@ -52,16 +67,44 @@ struct SuccVec {
         x = i == ew ? ev : x;
         return x;
     }
+    // Byte rows: words i .. i + 3 (i a multiple of four), one per byte.
+    __device__ __forceinline__ uint32_t get4(uint32_t i) const {
+        static_assert(sizeof(R) == 1, "byte rows");
+        uint32_t x = reinterpret_cast<const uint32_t *>(row)[i >> 2];
+        const uint32_t ps = 8 * (p & 3u), pm = (p >> 2) == (i >> 2) ? 0xFFu << ps : 0u;
+        const uint32_t es = 8 * (ew & 3u), em = (ew >> 2) == (i >> 2) ? 0xFFu << es : 0u;
+        x = (x & ~pm) | ((target << ps) & pm);
+        return (x & ~em) | ((ev << es) & em);
+    }
     __device__ __forceinline__ static SuccVec decode(const uint32_t *smem, uint2 d) {
         const uint32_t ew = d.x >> 24;
-        return SuccVec{smem + (d.x & 0xFFFFu), (d.x >> 16) & 0xFFu, d.y & 0xFFFFu,
+        return SuccVec{reinterpret_cast<const R *>(smem + (d.x & 0xFFFFu)), (d.x >> 16) & 0xFFu, d.y & 0xFFFFu,
                        ew == 0xFFu ? 0xFFFFFFFFu : ew, d.y >> 16};
     }
 };
+template <>
+inline constexpr bool kByteWords<SuccVec<uint8_t>> = true;
+
+// Whether two successors are the same vector.
+template <class R>
+__device__ __forceinline__ bool same_vector(const SuccVec<R> &v, const SuccVec<R> &o, uint32_t W) {
+    uint32_t diff = 0, w = 0;
+    if constexpr (sizeof(R) == 1) {
+        for (; w + 4 <= W; w += 4)
+            diff |= v.get4(w) ^ o.get4(w);
+    } else {
+        for (; w + 4 <= W; w += 4)
+            diff |= (v.get(w) ^ o.get(w)) | (v.get(w + 1) ^ o.get(w + 1)) |
+                    (v.get(w + 2) ^ o.get(w + 2)) | (v.get(w + 3) ^ o.get(w + 3));
+    }
+    for (; w < W; ++w)
+        diff |= v.get(w) ^ o.get(w);
+    return diff == 0;
+}
 
 // Dynamic LDS of the expansion (32-bit words), for state width W and a
 // transition-table area of `tcap` entries:
-//   tile     [256][W|1]  frontier states of the current tile
+//   tile     [256][row_stride]  frontier states of the current tile
 //   tr       [tcap] u64  the model's packed transitions (when they fit)
 //   pick     [256]       the (state, enabled pair) of each successor of the
 //                        current pass (P*K <= 64), in the mask area
@@ -81,8 +124,9 @@ constexpr uint32_t kMaskArea = 2 * kExpandBlock + 258;
 static_assert(kQueue <= kMaskArea, "queue shares the mask area");
 constexpr uint32_t kDedupCells = 512;   // twice the successors of a pass
 static_assert(kExpandBlock + kDedupCells <= kMaskArea, "pick and the dedup cells share the mask area");
+template <class R>
 __host__ __device__ constexpr uint32_t expand_lds_words(uint32_t W, uint32_t tcap, uint32_t G) {
-    return kExpandBlock * (W | 1u) + 2 * tcap + kMaskArea + kExpandBlock +
+    return kExpandBlock * row_stride<R>(W) + 2 * tcap + kMaskArea + kExpandBlock +
            (G > 1 ? 4 * kExpandBlock : 0u) + kNewBuf;
 }
 
@@ -140,9 +184,9 @@ __device__ __forceinline__ void expand_begin() {
 }
 
 // The new-state buffer in the expansion's LDS layout.
-template <int G>
+template <int G, class R>
 __device__ __forceinline__ uint32_t *expand_nbuf(uint32_t *smem, uint32_t W, uint32_t tcap) {
-    return smem + expand_lds_words(W, tcap, G) - kNewBuf;
+    return smem + expand_lds_words<R>(W, tcap, G) - kNewBuf;
 }
 
 // Append the buffered new slots to next[] with one atomic on the level's
@@ -312,14 +356,14 @@ __device__ __forceinline__ void flush_counters(DevStatus *st) {
 // accumulated edge/deadlock counts to lc and its event counts to st.  Call by all threads after the
 // last expand_tile of the launch (also after an aborted tile: every claimed
 // slot must be listed in next[] for the rollback).
-template <int G, bool COHERENT = false, bool SEG = false>
+template <int G, class R, bool COHERENT = false, bool SEG = false>
 __device__ __forceinline__ void expand_end(uint32_t *smem, uint32_t W, uint32_t tcap, uint32_t *next,
                                            LevelCounters *lc, uint32_t limit, DevStatus *st,
                                            const SegOut &so = SegOut{}) {
     if constexpr (SEG)
-        flush_new_slots_seg<COHERENT>(expand_nbuf<G>(smem, W, tcap), so, lc, limit);
+        flush_new_slots_seg<COHERENT>(expand_nbuf<G, R>(smem, W, tcap), so, lc, limit);
     else
-        flush_new_slots<COHERENT>(expand_nbuf<G>(smem, W, tcap), next, lc, limit);
+        flush_new_slots<COHERENT>(expand_nbuf<G, R>(smem, W, tcap), next, lc, limit);
     if (threadIdx.x == 0) {
         if (s_acc_edges)
             atomicAdd(&lc->edges, s_acc_edges);
@@ -396,7 +440,8 @@ __device__ __forceinline__ uint32_t wave_scan_incl(uint32_t x) {
 // their states as open first (flush_new_slots, COUNT_OPEN).
 // CL: slot lines are read with coherent loads (tables reused within one
 // launch, the persistent server).
-template <int G, uint32_t LS, bool COHERENT = false, bool DEFER = false, bool DEFER_COUNTS = DEFER,
+// R: the element type of the tile's LDS rows (uint8_t with G = 1 only).
+template <int G, uint32_t LS, class R, bool COHERENT = false, bool DEFER = false, bool DEFER_COUNTS = DEFER,
           bool AWAIT = false, bool CL = false, bool SEG = false>
 __device__ __forceinline__ bool expand_tile(uint32_t *smem, const TableView &t, const ModelView &m,
                                             const uint32_t *__restrict__ front, uint64_t base,
@@ -404,7 +449,9 @@ __device__ __forceinline__ bool expand_tile(uint32_t *smem, const TableView &t, 
                                             LevelCounters *lc, uint32_t limit, uint32_t tcap,
                                             const SegOut &so = SegOut{}) {
     constexpr uint32_t kBlock = kExpandBlock;
-    const uint32_t W = m.W, stride = W | 1u;
+    static_assert(sizeof(R) == 4 || G == 1, "byte rows: one lane per operation");
+    using Succ = SuccVec<R>;
+    const uint32_t W = m.W, stride = row_stride<R>(W);
     uint32_t *tile = smem;
     uint2 *tr_lds = reinterpret_cast<uint2 *>(tile + kBlock * stride);
     uint64_t *masks = reinterpret_cast<uint64_t *>(tr_lds + tcap);
@@ -492,7 +539,7 @@ __device__ __forceinline__ bool expand_tile(uint32_t *smem, const TableView &t, 
     const uint32_t wrow = tid - __lane_id();    // the wave's first row
     if (wrow < rows) {
         const uint32_t my_slot = (uint32_t)slot, words = min(rows - wrow, 64u) * W;
-        uint32_t *wtile = tile + wrow * stride;
+        R *wtile = reinterpret_cast<R *>(tile + wrow * stride);
         auto stage = [&](auto piece, auto batch, auto load) {
             constexpr uint32_t Z = decltype(piece)::value, B = decltype(batch)::value;   // words, loads in flight
             const uint32_t lane = fresh_lane();
@@ -505,14 +552,20 @@ __device__ __forceinline__ bool expand_tile(uint32_t *smem, const TableView &t, 
                     const uint32_t r = W == 1 ? f : __umulhi(f, m.magic_W), c = f - r * W;
                     const uint32_t rs = (uint32_t)__shfl((int)my_slot, (int)r, 64);
                     x[k] = load(t.data + (uint64_t)rs * W + c);
-                    at[k] = r * stride + c;
+                    at[k] = r * stride * (uint32_t)(4 / sizeof(R)) + c;
                 }
 #pragma unroll
                 for (uint32_t k = 0; k < B; ++k) {
                     const uint32_t *w = reinterpret_cast<const uint32_t *>(&x[k]);
+                    if constexpr (sizeof(R) == 1 && Z == 4) {
+                        *reinterpret_cast<uint32_t *>(wtile + at[k]) = w[0] | (w[1] << 8) | (w[2] << 16) | (w[3] << 24);
+                    } else if constexpr (sizeof(R) == 1 && Z == 2) {
+                        *reinterpret_cast<uint16_t *>(wtile + at[k]) = (uint16_t)(w[0] | (w[1] << 8));
+                    } else {
 #pragma unroll
-                    for (uint32_t z = 0; z < Z; ++z)
-                        wtile[at[k] + z] = w[z];
+                        for (uint32_t z = 0; z < Z; ++z)
+                            wtile[at[k] + z] = (R)w[z];
+                    }
                 }
             }
         };
@@ -568,14 +621,14 @@ __device__ __forceinline__ bool expand_tile(uint32_t *smem, const TableView &t, 
             const bool active = q < take && !(G == 1 && skip);
             uint32_t slot, code;
             if constexpr (G == 1) {
-                find_or_put_wave<LS, SuccVec, CL>(t, &ws[tid / 64], smem, make_uint2(my_d0, my_d1), my_h,
+                find_or_put_wave<LS, Succ, CL>(t, &ws[tid / 64], smem, make_uint2(my_d0, my_d1), my_h,
                                                   active, slot, code, cnt);
             } else {
                 const uint32_t o = active ? q : 0;
                 const LinePart<G, LS> line = home;
                 if (r + 1 < G)
                     home = home_of(q + NG);
-                find_or_put<G, LS, SuccVec, CL>(t, SuccVec::decode(smem, make_uint2(d0[o], d1[o])), hq[o], line,
+                find_or_put<G, LS, Succ, CL>(t, Succ::decode(smem, make_uint2(d0[o], d1[o])), hq[o], line,
                                                 active, slot, code, cnt);
             }
             const bool is_new = active && leader && code == kNew;
@@ -601,15 +654,16 @@ __device__ __forceinline__ bool expand_tile(uint32_t *smem, const TableView &t, 
         return s_abort != 0;
     };
     // successor (p, k) of tile row st
-    auto succ_of = [&](uint32_t st, uint32_t p, uint32_t k) -> SuccVec {
-        const uint32_t *row = tile + st * stride;
+    auto row_of = [&](uint32_t st) { return reinterpret_cast<const R *>(tile + st * stride); };
+    auto succ_of = [&](uint32_t st, uint32_t p, uint32_t k) -> Succ {
+        const R *row = row_of(st);
         const uint2 x = trans_at(((uint64_t)p * m.L + row[p]) * m.K + k);
         const uint32_t evar = x.x >> 24;
-        return SuccVec{row, p, x.x & 0xFFFFu, evar == 0xFFu ? 0xFFFFFFFFu : m.P + evar, x.y >> 16};
+        return Succ{row, p, x.x & 0xFFFFu, evar == 0xFFu ? 0xFFFFFFFFu : m.P + evar, x.y >> 16};
     };
     // decode successor (st, p, k) into hq/d0/d1[i] (G > 1) or this lane's
     // registers (G == 1, i == tid)
-    auto stage_successor = [&](uint32_t i, uint32_t st, const SuccVec &v) {
+    auto stage_successor = [&](uint32_t i, uint32_t st, const Succ &v) {
         const uint32_t ew = v.ew == 0xFFFFFFFFu ? 0xFFu : v.ew;
         const uint64_t h = hash_vec(v, W, t.seed);
         const uint32_t e0 = (st * stride) | (v.p << 16) | (ew << 24);
@@ -638,7 +692,7 @@ __device__ __forceinline__ bool expand_tile(uint32_t *smem, const TableView &t, 
         if (tid < rows) {
             // four processes at a time: their reads of local state,
             // transition and guarded variable are chains of their own
-            const uint32_t *row = tile + tid * stride;
+            const R *row = row_of(tid);
             for (uint32_t p0 = 0; p0 < m.P; p0 += 4) {
                 uint32_t tb[4];
                 bool on[4];
@@ -677,7 +731,7 @@ __device__ __forceinline__ bool expand_tile(uint32_t *smem, const TableView &t, 
         // this state's successors are numbered [nextq, nextq + c) in the tile
         nextq = woff + incl - c;
     }
-    auto pick_succ = [&](uint32_t e) -> SuccVec {
+    auto pick_succ = [&](uint32_t e) -> Succ {
         const uint32_t j = e & 0xFFu;
         const uint32_t p = m.K == 1 ? j : __umulhi(j, m.magic_K);
         return succ_of(e >> 8, p, j - p * m.K);
@@ -704,7 +758,7 @@ __device__ __forceinline__ bool expand_tile(uint32_t *smem, const TableView &t, 
             __syncthreads();
             if (tid < take) {
                 const uint32_t e = pick[tid];
-                const SuccVec v = pick_succ(e);
+                const Succ v = pick_succ(e);
                 stage_successor(tid, e >> 8, v);
                 if (G == 1 && !(t.flags & kNoMerge)) {
                     // Successors of one pass that are the same state (two
@@ -732,14 +786,7 @@ __device__ __forceinline__ bool expand_tile(uint32_t *smem, const TableView &t, 
                     }
                     if (other) {
                         // one compare per lane, its words loaded independently
-                        const SuccVec o = pick_succ(pick[other - 1]);
-                        uint32_t diff = 0, w = 0;
-                        for (; w + 4 <= W; w += 4)
-                            diff |= (v.get(w) ^ o.get(w)) | (v.get(w + 1) ^ o.get(w + 1)) |
-                                    (v.get(w + 2) ^ o.get(w + 2)) | (v.get(w + 3) ^ o.get(w + 3));
-                        for (; w < W; ++w)
-                            diff |= v.get(w) ^ o.get(w);
-                        skip = diff == 0;
+                        skip = same_vector(v, pick_succ(pick[other - 1]), W);
                         cnt.merged += skip;
                     }
                 }
@@ -756,7 +803,7 @@ __device__ __forceinline__ bool expand_tile(uint32_t *smem, const TableView &t, 
                     const uint32_t j = c - st * PK;
                     const uint32_t p = m.K == 1 ? j : __umulhi(j, m.magic_K);
                     const uint32_t k = j - p * m.K;
-                    const uint32_t *row = tile + st * stride;
+                    const R *row = row_of(st);
                     const uint32_t local = row[p];
                     if (local < m.L) {
                         const uint2 x = trans_at(((uint64_t)p * m.L + local) * m.K + k);

@@ -149,6 +149,18 @@ lhs_status with_shape(uint32_t tps, uint32_t ls, F &&f) {
     return LHS_EINVAL;
 }
 
+// ... and f(G, LS, R{}) with the element type R of the expansion's LDS rows:
+// bytes where the models allow it and one lane runs an operation.
+template <class F>
+lhs_status with_tile(uint32_t tps, uint32_t ls, bool bytes, F &&f) {
+    return with_shape(tps, ls, [&](auto G, auto L) {
+        if constexpr (decltype(G)::value == 1)
+            if (bytes)
+                return f(G, L, uint8_t{});
+        return f(G, L, uint32_t{});
+    });
+}
+
 // Tuned table configuration for (kind, W, capacity) from the loaded tuning
 // table, or the defaults; never fails.
 lhs_config tuned_config(uint32_t kind, uint32_t W, uint64_t capacity);

@@ -182,6 +182,10 @@ __device__ __forceinline__ uint64_t rotl64(uint64_t x, int r) {
     return (x << r) | (x >> (64 - r));
 }
 
+// Vectors that also give four words at a time as the bytes of one (get4).
+template <class Vec>
+constexpr bool kByteWords = false;
+
 // 64-bit vector hash: MurmurHash3 x64 block mixing over 64-bit pairs of
 // words, closed by its fmix64 finaliser (A. Appleby, MurmurHash3, public
 // domain).  `Vec` provides get(i) for word i.
@@ -195,9 +199,18 @@ __device__ __forceinline__ uint64_t hash_vec(const Vec &v, uint32_t W, uint64_t 
     for (; i + 8 <= W; i += 8) {
         uint32_t w[8];
         uint64_t k[4];
+        if constexpr (kByteWords<Vec>) {
+            const uint32_t a = v.get4(i), b = v.get4(i + 4);
 #pragma unroll
-        for (uint32_t j = 0; j < 8; ++j)
-            w[j] = v.get(i + j);
+            for (uint32_t j = 0; j < 4; ++j) {
+                w[j] = (a >> (8 * j)) & 0xFFu;
+                w[4 + j] = (b >> (8 * j)) & 0xFFu;
+            }
+        } else {
+#pragma unroll
+            for (uint32_t j = 0; j < 8; ++j)
+                w[j] = v.get(i + j);
+        }
 #pragma unroll
         for (uint32_t j = 0; j < 4; ++j)
             k[j] = rotl64(((uint64_t)w[2 * j] | ((uint64_t)w[2 * j + 1] << 32)) * c1, 31) * c2;

@@ -50,7 +50,7 @@ __device__ __forceinline__ const uint32_t *seg_tile(const SegFront &f, uint32_t 
 
 // Expand one BFS level of one model: the frontier's tiles, new states
 // appended to the segments of the next frontier.
-template <int G, uint32_t LS>
+template <int G, uint32_t LS, class R>
 __global__ __launch_bounds__(kExpandBlock, LS == 8 ? 4 : 1) void k_expand(TableView t, ModelView m, SegFront f, SegOut o,
                                                          LevelCounters *lc, uint32_t limit, uint32_t tcap) {
     extern __shared__ uint32_t smem[];
@@ -59,11 +59,11 @@ __global__ __launch_bounds__(kExpandBlock, LS == 8 ? 4 : 1) void k_expand(TableV
     for (uint32_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
         uint32_t rows = 0;
         const uint32_t *front = seg_tile(f, tile, rows);
-        if (expand_tile<G, LS, false, true, true, false, false, true>(smem, t, m, front, 0, rows, nullptr, lc,
-                                                                      limit, tcap, o))
+        if (expand_tile<G, LS, R, false, true, true, false, false, true>(smem, t, m, front, 0, rows, nullptr, lc,
+                                                                         limit, tcap, o))
             break;
     }
-    expand_end<G, false, true>(smem, m.W, tcap, nullptr, lc, limit, t.status, o);
+    expand_end<G, R, false, true>(smem, m.W, tcap, nullptr, lc, limit, t.status, o);
 }
 
 // Undo the inserts of a discarded level: zero the slots listed in its
@@ -86,7 +86,7 @@ __global__ void k_rollback(uint64_t *bucket, SegFront f) {
 // the table's GraphCtx; once the exploration is done every kernel returns at
 // once, so a replay may run past the last level.
 
-template <int G, uint32_t LS>
+template <int G, uint32_t LS, class R>
 __global__ __launch_bounds__(kExpandBlock, LS == 8 ? 4 : 1) void k_expand_graph(const GraphCtx *ctx, uint32_t tcap) {
     extern __shared__ uint32_t smem[];
     __shared__ uint32_t s_go, s_lim;
@@ -120,11 +120,11 @@ __global__ __launch_bounds__(kExpandBlock, LS == 8 ? 4 : 1) void k_expand_graph(
     for (uint32_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
         uint32_t rows = 0;
         const uint32_t *front = seg_tile(f, tile, rows);
-        if (expand_tile<G, LS, false, true, true, false, false, true>(smem, t, m, front, 0, rows, nullptr, lc,
-                                                                      limit, tcap, o))
+        if (expand_tile<G, LS, R, false, true, true, false, false, true>(smem, t, m, front, 0, rows, nullptr, lc,
+                                                                         limit, tcap, o))
             break;
     }
-    expand_end<G, false, true>(smem, m.W, tcap, nullptr, lc, limit, t.status, o);
+    expand_end<G, R, false, true>(smem, m.W, tcap, nullptr, lc, limit, t.status, o);
 }
 
 // The host loop's per-level bookkeeping, on the device (one thread).
@@ -319,8 +319,23 @@ ModelView model_view(const reach_model *m, const uint2 *d_trans) {
     return v;
 }
 
-size_t expand_lds_bytes(uint32_t W, uint32_t tcap, uint32_t tps) {
-    return (size_t)expand_lds_words(W, tcap, tps) * sizeof(uint32_t);
+bool rows_fit_bytes(const reach_model *m) {
+    if (m->n_locals > 256)
+        return false;
+    for (uint32_t i = 0; i < m->n_procs + m->n_shared; ++i)
+        if (m->init[i] > 255)
+            return false;
+    const uint64_t n = (uint64_t)m->n_procs * m->n_locals * m->trans_per_local;
+    for (uint64_t i = 0; i < n; ++i)
+        if (m->trans[i].eff_var != REACH_NONE && m->trans[i].eff_val > 255)
+            return false;
+    return true;
+}
+
+size_t expand_lds_bytes(uint32_t W, uint32_t tcap, uint32_t tps, bool bytes) {
+    return (size_t)(bytes && tps == 1 ? expand_lds_words<uint8_t>(W, tcap, tps)
+                                      : expand_lds_words<uint32_t>(W, tcap, tps)) *
+           sizeof(uint32_t);
 }
 
 // The first frontier, s0 alone in segment 0 of buf; a frontier from the
@@ -346,13 +361,13 @@ SegFront seg_front(const uint32_t *buf, uint32_t size, const uint32_t *cursors, 
 
 uint32_t seg_size(const lhs_table *t) { return (uint32_t)(t->capacity / kSegs); }
 
-lhs_status launch_expand(lhs_table *t, const TableView &tv, const ModelView &mv, const SegFront &f,
+lhs_status launch_expand(lhs_table *t, const TableView &tv, const ModelView &mv, bool bytes, const SegFront &f,
                          const SegOut &o, LevelCounters *lc, uint32_t limit, hipStream_t s) {
     const uint64_t tiles = f.tiles[kSegs];
     const uint32_t tc = trans_lds_entries(mv.P, mv.L, mv.K);
-    const size_t lds = expand_lds_bytes(mv.W, tc, tps_expand(t));
-    const lhs_status rc = with_shape(tps_expand(t), t->line_slots, [&](auto G, auto L) {
-        const void *fn = (const void *)k_expand<decltype(G)::value, decltype(L)::value>;
+    const size_t lds = expand_lds_bytes(mv.W, tc, tps_expand(t), bytes);
+    const lhs_status rc = with_tile(tps_expand(t), t->line_slots, bytes, [&](auto G, auto L, auto R) {
+        const void *fn = (const void *)k_expand<decltype(G)::value, decltype(L)::value, decltype(R)>;
         // workgroups loop over tiles: as many as are resident at once, so that
         // each keeps its new-state buffer across many tiles
         int ncu = 0, per_cu = 0, dev = 0;
@@ -362,7 +377,7 @@ lhs_status launch_expand(lhs_table *t, const TableView &tv, const ModelView &mv,
             per_cu < 1)
             return LHS_EDEVICE;
         const uint32_t blocks = exploration_grid(t, std::min<uint64_t>(tiles, (uint64_t)ncu * per_cu));
-        hipLaunchKernelGGL((k_expand<decltype(G)::value, decltype(L)::value>), dim3(blocks), dim3(kExpandBlock),
+        hipLaunchKernelGGL((k_expand<decltype(G)::value, decltype(L)::value, decltype(R)>), dim3(blocks), dim3(kExpandBlock),
                            lds, s, tv, mv, f, o, lc, limit, tc);
         return LHS_OK;
     });
@@ -425,6 +440,7 @@ lhs_status explore_host_loop(lhs_table *t, const reach_model *m, const uint2 *d_
                              uint32_t max_levels, hipStream_t s, reach_result *r,
                              uint32_t *d_init, bool parents, PrefixArea *d_pre, PrefixArea *h_pre) {
     const ModelView mv = model_view(m, d_trans);
+    const bool bytes = rows_fit_bytes(m);
     const TableView tv = bfs_view(t, parents);
     std::vector<uint64_t> levels;
     // s0 is level 0: insert it with the batched find-or-put; its slot is the
@@ -445,7 +461,7 @@ lhs_status explore_host_loop(lhs_table *t, const reach_model *m, const uint2 *d_
     bool finished = false;
     if (d_pre) {
         PrefixOut pre;
-        rc = explore_prefix(t, tv, mv, m->state_cap, d_pre, h_pre, s, pre);
+        rc = explore_prefix(t, tv, mv, bytes, m->state_cap, d_pre, h_pre, s, pre);
         if (rc != LHS_OK)
             return rc;
         levels.insert(levels.end(), pre.levels.begin(), pre.levels.end());
@@ -464,7 +480,7 @@ lhs_status explore_host_loop(lhs_table *t, const reach_model *m, const uint2 *d_
         if (m->state_cap)
             limit = (uint32_t)std::min<uint64_t>(m->state_cap - total, 0xFFFFFFFFull);
         const SegOut o{t->frontier[cur ^ 1], t->segs, size, t->status};
-        rc = launch_expand(t, tv, mv, f, o, t->level, limit, s);
+        rc = launch_expand(t, tv, mv, bytes, f, o, t->level, limit, s);
         if (rc != LHS_OK)
             return rc;
         // the level's summary lands in pinned memory (and the counters are
@@ -562,18 +578,19 @@ lhs_status explore_graph(lhs_table *t, const reach_model *m, const uint2 *d_tran
     LHS_HIP(hipMemcpyAsync(d_ctx, &h, sizeof(h), hipMemcpyHostToDevice, s));
 
     // the captured graph depends on the table, its lanes per state, the LDS
-    // layout (W is the table's) and the worker cap
+    // layout (W is the table's), its rows' element and the worker cap
     const uint32_t tps = tps_expand(t);
-    const uint64_t key = ((uint64_t)t->workers << 32) | (tcap * 32u + tps);
+    const bool bytes = rows_fit_bytes(m);
+    const uint64_t key = ((uint64_t)t->workers << 32) | (tcap * 64u + (bytes ? 32u : 0u) + tps);
     if (!t->gexec || t->gexec_tcap != key) {
         if (t->gexec) {
             (void)hipGraphExecDestroy(t->gexec);
             t->gexec = nullptr;
         }
-        const size_t lds = expand_lds_bytes(W, tcap, tps);
+        const size_t lds = expand_lds_bytes(W, tcap, tps, bytes);
         hipGraph_t g = nullptr;
-        rc = with_shape(tps, t->line_slots, [&](auto G, auto L) {
-            const void *fn = (const void *)k_expand_graph<decltype(G)::value, decltype(L)::value>;
+        rc = with_tile(tps, t->line_slots, bytes, [&](auto G, auto L, auto R) {
+            const void *fn = (const void *)k_expand_graph<decltype(G)::value, decltype(L)::value, decltype(R)>;
             int ncu = 0, per_cu = 0, dev = 0;
             if (hipGetDevice(&dev) != hipSuccess ||
                 hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
@@ -583,7 +600,7 @@ lhs_status explore_graph(lhs_table *t, const reach_model *m, const uint2 *d_tran
             if (hipStreamBeginCapture(t->gstream, hipStreamCaptureModeThreadLocal) != hipSuccess)
                 return LHS_EDEVICE;
             for (uint32_t k = 0; k < kGraphLevels; ++k) {
-                hipLaunchKernelGGL((k_expand_graph<decltype(G)::value, decltype(L)::value>),
+                hipLaunchKernelGGL((k_expand_graph<decltype(G)::value, decltype(L)::value, decltype(R)>),
                                    dim3(exploration_grid(t, (uint64_t)ncu * per_cu)), dim3(kExpandBlock), lds,
                                    t->gstream,
                                    (const GraphCtx *)d_ctx, tcap);
@@ -861,6 +878,7 @@ static lhs_status reach_explore_noalloc_impl(const reach_model *m, lhs_table *t,
     if ((rc = launch_find_or_put(t, d_init, 1, seen, fr[0], s)) != LHS_OK)
         return rc;
     const ModelView mv = model_view(m, d_trans);
+    const bool bytes = rows_fit_bytes(m);
     const TableView tv = bfs_view(t, false);
     h_level_counts[0] = 1;
     uint32_t n_levels = 1, cur = 0;
@@ -876,7 +894,7 @@ static lhs_status reach_explore_noalloc_impl(const reach_model *m, lhs_table *t,
             m->state_cap ? (uint32_t)std::min<uint64_t>(m->state_cap - total, 0xFFFFFFFFull) : 0xFFFFFFFFu;
         hipLaunchKernelGGL(k_zero_level, dim3(1), dim3(64), 0, s, lc, segs);
         const SegOut o{fr[cur ^ 1], segs, size, t->status};
-        if ((rc = launch_expand(t, tv, mv, f, o, lc, limit, s)) != LHS_OK)
+        if ((rc = launch_expand(t, tv, mv, bytes, f, o, lc, limit, s)) != LHS_OK)
             return rc;
         LHS_HIP(hipMemcpyAsync(&h_lc, lc, sizeof(h_lc), hipMemcpyDeviceToHost, s));
         LHS_HIP(hipMemcpyAsync(h_segs, segs, kSegCursorBytes, hipMemcpyDeviceToHost, s));

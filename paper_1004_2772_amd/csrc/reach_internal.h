@@ -74,7 +74,10 @@ namespace lhs {
 lhs_status validate_model(const reach_model *m);
 void pack_model(const reach_model *m, std::vector<uint2> &out);
 ModelView model_view(const reach_model *m, const uint2 *d_trans);
-size_t expand_lds_bytes(uint32_t W, uint32_t tcap, uint32_t tps);
+// Whether every word of every reachable state is below 256: the initial
+// words, the local states and the values that effects write.
+bool rows_fit_bytes(const reach_model *m);
+size_t expand_lds_bytes(uint32_t W, uint32_t tcap, uint32_t tps, bool bytes);
 lhs_status ensure_bfs_buffers(lhs_table *t);
 
 // The first levels of a single-model BFS in one persistent launch (the batch
@@ -89,7 +92,7 @@ struct PrefixOut {
     bool handed = false;            // stopped after a level above the threshold
     bool capped = false;
 };
-lhs_status explore_prefix(lhs_table *t, const TableView &tv, const ModelView &mv, uint64_t cap,
+lhs_status explore_prefix(lhs_table *t, const TableView &tv, const ModelView &mv, bool bytes, uint64_t cap,
                           PrefixArea *d_area, PrefixArea *h_area, hipStream_t s, PrefixOut &out);
 uint64_t auto_capacity(const reach_model *m);
 // The view a BFS on t expands with: predecessor records when requested.

@@ -66,7 +66,7 @@ struct StepCtl {
 // prefix; run by the one workgroup that finished the step last (all other
 // workgroups' counter updates are complete by then).  `scan` is LDS for
 // kDefaultMaxActive words.
-static_assert(expand_lds_words(1, 0, 1) >= kDefaultMaxActive, "the scan reuses the expansion's LDS");
+static_assert(expand_lds_words<uint32_t>(1, 0, 1) >= kDefaultMaxActive, "the scan reuses the expansion's LDS");
 
 __device__ void step_finalize(BatchSlot *slots, StepCtl *ctl, LevelCounters *lc, DevStatus *st,
                               uint32_t *begin, uint32_t n, uint32_t *scan) {
@@ -157,7 +157,7 @@ __global__ __launch_bounds__(kExpandBlock, LS == 8 ? 4 : 1) void k_step(BatchSlo
         const BatchSlot &s = slots[find_slot_by_tile(begin, n, g)];
         const uint64_t base = (uint64_t)(g - s.tile_begin) * kExpandBlock;
         const uint32_t rows = (uint32_t)min<uint64_t>(kExpandBlock, s.n_front - base);
-        expand_tile<G, LS>(smem, s.t, s.m, s.front, base, rows, s.next, s.lc, s.limit, tcap);
+        expand_tile<G, LS, uint32_t>(smem, s.t, s.m, s.front, base, rows, s.next, s.lc, s.limit, tcap);
     }
     // this workgroup's counter updates are complete before it checks in
     wait_vm_complete();
@@ -314,7 +314,7 @@ __device__ void admit_query(const ModelState &M, ModelProgress *mp, LevelState *
     __syncthreads();
 }
 
-template <int G, uint32_t LS>
+template <int G, uint32_t LS, class R>
 __global__ __launch_bounds__(kExpandBlock, LS == 8 ? 4 : 1) void k_serve(const ModelState *ms, ModelProgress *mp, LevelState *lv,
                                                         QueueState *qs, QCell *ring, ServeBox *box, DoneRec *done,
                                                         const uint32_t *roots, uint32_t tcap) {
@@ -452,8 +452,8 @@ __global__ __launch_bounds__(kExpandBlock, LS == 8 ? 4 : 1) void k_serve(const M
         const uint32_t rows_per = ld_coherent(&L.tile_rows);
         const uint64_t base = (uint64_t)j * rows_per;
         const uint32_t rows = (uint32_t)min<uint64_t>(rows_per, n_front - base);
-        expand_tile<G, LS, true, false, false, false, true>(smem, s_M.t, s_M.m, front, base, rows, next, s_M.lc,
-                                                            limit, tcap);
+        expand_tile<G, LS, R, true, false, false, false, true>(smem, s_M.t, s_M.m, front, base, rows, next, s_M.lc,
+                                                               limit, tcap);
         wait_vm_complete();
         __syncthreads();
         if (tid == 0) {
@@ -541,6 +541,7 @@ struct Query {
     bool done = false;
     uint32_t slot = 0xFFFFFFFFu;   // persistent server: its slot while on the GPU
     uint64_t tiles_bound = 0;      // bound on its items in the work queue
+    bool bytes_rows = false;       // every word of its states fits a byte
 };
 
 // A query's items in the work queue at once: one level's tiles, full or cut
@@ -555,6 +556,7 @@ struct Persist {
     hipEvent_t ev_end = nullptr;       // recorded after each launch
     bool running = false;
     uint32_t launch_W = 0;             // widest vector the running launch's LDS holds
+    bool launch_bytes = false;         // ... in rows of bytes
     uint64_t launches = 0;
     ModelState *d_ms = nullptr;
     ModelProgress *d_mp = nullptr;
@@ -872,7 +874,7 @@ lhs_status step_queries(reach_server *s, std::vector<Query *> &finished) {
                        d_arrived);
     // workgroups for the expansion: enough for the round's first level four
     // times over (later levels loop), at most as many as are resident
-    const size_t lds = (size_t)expand_lds_words(maxW, tcap, tps) * sizeof(uint32_t);
+    const size_t lds = (size_t)expand_lds_words<uint32_t>(maxW, tcap, tps) * sizeof(uint32_t);
     rc = with_shape(tps, s->cfg.line_slots, [&](auto G, auto L) {
         const void *fn = (const void *)k_step<decltype(G)::value, decltype(L)::value>;
         int ncu = 0, per_cu = 0;
@@ -1097,15 +1099,17 @@ lhs_status persist_post(reach_server *s, const std::vector<Query *> &qs) {
 lhs_status persist_launch(reach_server *s) {
     Persist &P = s->ps;
     uint32_t maxW = 1, tcap = 0;
+    bool bytes = true;
     for (Query *q : P.slot_q)
         if (q) {
             maxW = std::max(maxW, q->W);
+            bytes = bytes && q->bytes_rows;
             tcap = std::max(tcap, trans_lds_entries(q->m.n_procs, q->m.n_locals, q->m.trans_per_local));
         }
     const uint32_t tps = s->cfg.tps_expand ? s->cfg.tps_expand : kDefaultTpsExpand;
-    const size_t lds = (size_t)expand_lds_words(maxW, tcap, tps) * sizeof(uint32_t);
-    const lhs_status rc = with_shape(tps, s->cfg.line_slots, [&](auto G, auto L) {
-        const void *fn = (const void *)k_serve<decltype(G)::value, decltype(L)::value>;
+    const size_t lds = expand_lds_bytes(maxW, tcap, tps, bytes);
+    const lhs_status rc = with_tile(tps, s->cfg.line_slots, bytes, [&](auto G, auto L, auto R) {
+        const void *fn = (const void *)k_serve<decltype(G)::value, decltype(L)::value, decltype(R)>;
         int ncu = 0, per_cu = 0;
         if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, s->device) != hipSuccess ||
             hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kExpandBlock, lds) != hipSuccess ||
@@ -1113,7 +1117,7 @@ lhs_status persist_launch(reach_server *s) {
             return LHS_EDEVICE;
         const uint32_t grid = (uint32_t)ncu * (uint32_t)std::max(1, per_cu - 1);
         hipLaunchKernelGGL(k_serve_reopen, dim3(1), dim3(1), 0, s->stream, P.d_qs, P.d_box);
-        hipLaunchKernelGGL((k_serve<decltype(G)::value, decltype(L)::value>), dim3(grid), dim3(kExpandBlock), lds,
+        hipLaunchKernelGGL((k_serve<decltype(G)::value, decltype(L)::value, decltype(R)>), dim3(grid), dim3(kExpandBlock), lds,
                            s->stream, (const ModelState *)P.d_ms, P.d_mp, P.d_lv, P.d_qs, P.d_ring, P.d_box,
                            P.h_done_dev, (const uint32_t *)P.d_roots, tcap);
         return hipGetLastError() == hipSuccess ? LHS_OK : LHS_EDEVICE;
@@ -1124,6 +1128,7 @@ lhs_status persist_launch(reach_server *s) {
     P.running = true;
     P.close_sent = false;
     P.launch_W = maxW;
+    P.launch_bytes = bytes;
     ++P.launches;
     return LHS_OK;
 }
@@ -1202,11 +1207,12 @@ void persist_worker(reach_server *s) {
                 return;
             // first come first served, while a slot, room in the work queue
             // and the budget allow; a query wider than the running launch's
-            // LDS waits for the next launch (and holds the queries behind it)
+            // LDS, or with words its rows cannot hold, waits for the next
+            // launch (and holds the queries behind it)
             bool drain = false;
             while (!s->queue.empty() && admitted.size() < P.free_slots.size()) {
                 Query *q = s->queue.front();
-                if (P.running && q->W > P.launch_W) {
+                if (P.running && (q->W > P.launch_W || (P.launch_bytes && !q->bytes_rows))) {
                     drain = true;
                     break;
                 }
@@ -1524,6 +1530,7 @@ static lhs_status reach_server_submit_impl(reach_server *s, const reach_model *m
     if (!q)
         return LHS_ENOMEM;
     q->W = m->n_procs + m->n_shared;
+    q->bytes_rows = rows_fit_bytes(m);
     const uint64_t nt = (uint64_t)m->n_procs * m->n_locals * m->trans_per_local;
     q->trans.assign(m->trans, m->trans + nt);
     q->init.assign(m->init, m->init + q->W);
