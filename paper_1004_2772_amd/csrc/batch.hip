@@ -6,8 +6,7 @@
 // small and large models, and models of different state widths, share the
 // GPU.  Two drivers:
 //   * persistent (default): one launch of resident workgroups runs every
-//     level of every model from a device work queue of (model, tile) items;
-//     each model advances at its own pace, with no grid-wide barrier;
+//     level of every model, each model at its own pace (board.h);
 //   * host loop (REACH_F_HOST_LOOP): all models advance together, one launch
 //     per level step covering the tiles of every unfinished model, the host
 //     reading the per-model counters after each.
@@ -18,9 +17,9 @@
 #include <vector>
 
 #include "batch_kernels.h"
+#include "board.h"
 #include "expand_device.h"
 #include "internal.h"
-#include "persistent.h"
 #include "reach_internal.h"
 
 using namespace lhs;
@@ -32,89 +31,11 @@ constexpr uint32_t kMaxBatch = 1024;   // models per call (tile prefix lives in 
 // With 8-slot lines, at least four waves per SIMD (at most 128 VGPRs): four
 // workgroups per CU, as the LDS layout allows.  Wider lines would spill.
 template <int G, uint32_t LS, class R>
-__global__ __launch_bounds__(kExpandBlock, LS == 8 ? 4 : 1) void k_batch_persistent(const ModelState *__restrict__ ms,
-                                                                   ModelProgress *mp, LevelState *lv,
-                                                                   QueueState *qs, QCell *ring,
-                                                                   uint32_t tcap) {
+__global__ __launch_bounds__(kExpandBlock, LS == 8 ? 4 : 1) void k_levels(const ModelState *__restrict__ ms,
+                                                                         BoardModel *bm, unsigned long long *tickets,
+                                                                         BoardCtl *ctl, uint32_t n, uint32_t tcap) {
     extern __shared__ uint32_t smem[];
-    expand_begin();
-    __shared__ uint32_t s_model, s_tile, s_exit, s_fin;
-    const uint32_t tid = threadIdx.x;
-    bool kept = false;   // tile 0 of s_model's new level is this workgroup's
-    while (true) {
-        if (tid == 0 && kept) {
-            s_tile = 0;
-            s_exit = queue_failed(qs) ? 1u : 0u;
-        } else if (tid == 0) {
-            uint32_t ex = 0;
-            const unsigned long long pos = atomicAdd(&qs->head, 1ull);
-            QCell *c = ring + (pos & qs->mask);
-            uint32_t spins = 0;
-            while (ld_coherent(&c->seq) != pos + 1ull) {
-                if (ld_coherent(&qs->remaining) == 0u || queue_failed(qs)) {
-                    ex = 1;
-                    break;
-                }
-                if (++spins > kBarrierSpinLimit) {
-                    atomicCAS(&qs->error, 0u, (uint32_t)LHS_ESTALL);
-                    ex = 1;
-                    break;
-                }
-                __builtin_amdgcn_s_sleep(4);
-            }
-            if (!ex) {
-                s_model = ld_coherent(&c->model);
-                s_tile = ld_coherent(&c->tile);
-                // the item is read before the cell is freed: the store must
-                // not be performed ahead of the loads (different addresses),
-                // or the next producer could overwrite the item first
-                wait_vm_complete();
-                st_coherent(&c->seq, pos + qs->mask + 1ull);   // free for position pos + R
-            }
-            s_exit = ex;
-        }
-        __syncthreads();
-        if (s_exit)
-            break;
-        const uint32_t i = s_model, j = s_tile;
-        const ModelState &M = ms[i];
-        LevelState &L = lv[i];
-        const uint32_t *front = reinterpret_cast<const uint32_t *>(ld_coherent(&L.front));
-        uint32_t *next = reinterpret_cast<uint32_t *>(ld_coherent(&L.next));
-        const uint32_t n_front = ld_coherent(&L.n_front);
-        const uint32_t limit = ld_coherent(&L.limit);
-        const uint32_t rows_per = ld_coherent(&L.tile_rows);
-        const uint64_t base = (uint64_t)j * rows_per;
-        const uint32_t rows = (uint32_t)min<uint64_t>(rows_per, n_front - base);
-        expand_tile<G, LS, R, true>(smem, M.t, M.m, front, base, rows, next, M.lc, limit, tcap);
-        // this workgroup's stores of the tile are complete before it counts
-        // the tile as done
-        wait_vm_complete();
-        __syncthreads();
-        if (tid == 0) {
-            // the level's tile count, read while this tile still holds the
-            // level open: once the count below reaches it, the finaliser
-            // may already be writing the next level's count
-            const uint32_t total = ld_coherent(&L.tiles_total);
-            // the load and the add go to different addresses, which the
-            // memory model does not order: the load completes first
-            wait_vm_complete();
-            const uint32_t done = atomicAdd(&L.tiles_done, 1u) + 1u;
-            s_fin = done == total;
-        }
-        __syncthreads();
-        kept = s_fin && finalize_level(M, mp, lv, i, qs, ring);
-    }
-}
-
-__global__ void k_init_ring(QCell *ring, unsigned long long cells, uint32_t n_models) {
-    for (unsigned long long p = (unsigned long long)blockIdx.x * blockDim.x + threadIdx.x; p < cells;
-         p += (unsigned long long)gridDim.x * blockDim.x) {
-        // positions 0..n_models-1 hold level 0 (tile 0) of every model
-        ring[p].seq = p < n_models ? p + 1 : p;
-        ring[p].model = p < n_models ? (uint32_t)p : 0u;
-        ring[p].tile = 0;
-    }
+    board_run<G, LS, R>(smem, ms, bm, tickets, ctl, n, tcap);
 }
 
 uint64_t batch_auto_capacity(const reach_model *m) {
@@ -141,23 +62,23 @@ __global__ void k_clear_tables(const TableZero *z) {
 }
 
 // Copy levels 1 .. n_levels-1 of every model into one compact array, model
-// after model (one workgroup; n <= kMaxBatch).
-__global__ __launch_bounds__(1024) void k_gather_levels(const ModelState *ms, const ModelProgress *mp,
+// after model (one workgroup; n <= kMaxBatch): a wavefront per model.
+__global__ __launch_bounds__(1024) void k_gather_levels(const ModelState *ms, const BoardModel *bm,
                                                         uint32_t n, unsigned long long *out) {
     __shared__ uint32_t off[kMaxBatch + 1];
     const uint32_t tid = threadIdx.x;
+    for (uint32_t i = tid; i < n; i += blockDim.x)
+        off[i + 1] = bm[i].n_levels - 1;
+    __syncthreads();
     if (tid == 0) {
-        uint32_t acc = 0;
-        for (uint32_t i = 0; i < n; ++i) {
-            off[i] = acc;
-            acc += mp[i].n_levels - 1;
-        }
-        off[n] = acc;
+        off[0] = 0;
+        for (uint32_t i = 0; i < n; ++i)
+            off[i + 1] += off[i];
     }
     __syncthreads();
-    for (uint32_t i = tid; i < n; i += blockDim.x)
-        for (uint32_t k = 1; k < mp[i].n_levels; ++k)
-            out[off[i] + k - 1] = ms[i].levels[k];
+    for (uint32_t i = tid / 64; i < n; i += blockDim.x / 64)
+        for (uint32_t k = tid % 64; k < off[i + 1] - off[i]; k += 64)
+            out[off[i] + k] = ms[i].levels[k + 1];
 }
 
 struct BatchModel {
@@ -177,81 +98,60 @@ struct BatchModel {
 
 namespace lhs {
 
-lhs_status explore_prefix(lhs_table *t, const TableView &tv, const ModelView &mv, bool bytes, uint64_t cap, PrefixArea *d,
-                          PrefixArea *h, hipStream_t s, PrefixOut &out) {
-    // level 0 (s0 at frontier[0][0]) is tile 0 of queue position 0
-    const size_t head = offsetof(PrefixArea, levels);
-    std::memset(h, 0, head);
-    h->qs.tail = 1;
-    h->qs.remaining = 1;
-    h->qs.mask = kPrefixCells - 1;
+lhs_status explore_levels(lhs_table *t, const TableView &tv, const ModelView &mv, bool bytes, uint64_t cap,
+                          LevelsArea *d, LevelsArea *h, hipStream_t s, LevelsRun &run) {
+    const size_t head = offsetof(LevelsArea, levels);
+    std::memset(static_cast<void *>(h), 0, head);
+    h->ctl.remaining = 1;
+    h->tickets[0] = make_ticket((run.n_front + kExpandBlock - 1) / kExpandBlock, run.cur, kExpandBlock, 0);
     ModelState &M = h->ms;
     M.t = tv;
     M.m = mv;
-    M.lc = t->level;
     M.fr[0] = t->frontier[0];
     M.fr[1] = t->frontier[1];
     M.levels = d->levels;
     M.cap = cap;
-    M.max_levels = kPrefixLevels;
-    M.handover = kPrefixHandover;
-    h->mp.total = 1;
-    h->mp.n_levels = 1;
-    LevelState &L = h->lv;
-    L.front = (unsigned long long)M.fr[0];
-    L.next = (unsigned long long)M.fr[1];
-    L.n_front = 1;
-    L.limit = cap ? (uint32_t)std::min<uint64_t>(cap - 1, 0xFFFFFFFFull) : 0xFFFFFFFFu;
-    L.tiles_total = 1;
-    L.tile_rows = kExpandBlock;
+    M.max_levels = kBoardLevels;
+    M.handover = kBoardHandover;
+    BoardModel &B = h->bm;
+    B.n_front = run.n_front;
+    B.limit = cap ? (uint32_t)std::min<uint64_t>(cap - run.total, 0xFFFFFFFFull) : 0xFFFFFFFFu;
+    B.cur = run.cur;
+    B.n_levels = 1;
+    B.total = run.total;
     LHS_HIP(hipMemcpyAsync(d, h, head, hipMemcpyHostToDevice, s));
-    hipLaunchKernelGGL(k_init_ring, dim3(kPrefixCells / 256), dim3(256), 0, s, d->ring,
-                       (unsigned long long)kPrefixCells, 1u);
-    LHS_HIP(hipGetLastError());
     const uint32_t tps = tps_expand(t);
     const uint32_t tcap = trans_lds_entries(mv.P, mv.L, mv.K);
     const size_t lds = expand_lds_bytes(mv.W, tcap, tps, bytes);
     lhs_status rc = with_tile(tps, t->line_slots, bytes, [&](auto G, auto LS, auto R) {
-        const void *fn = (const void *)k_batch_persistent<decltype(G)::value, decltype(LS)::value, decltype(R)>;
-        int dev = 0, ncu = 0, per_cu = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kExpandBlock, lds) != hipSuccess ||
-            per_cu < 1)
+        const void *fn = (const void *)k_levels<decltype(G)::value, decltype(LS)::value, decltype(R)>;
+        int per_cu = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kExpandBlock, lds) != hipSuccess || per_cu < 1)
             return LHS_EDEVICE;
-        // the workgroups that fit at once, at most kPrefixGrid: every one
-        // holds a queue position while the levels are small
-        const uint32_t grid =
-            exploration_grid(t, std::min<uint64_t>((uint64_t)ncu * per_cu, kPrefixGrid));
-        const ModelState *ms = &d->ms;
-        ModelProgress *mp = &d->mp;
-        LevelState *lv = &d->lv;
-        QueueState *qs = &d->qs;
-        QCell *ring = d->ring;
-        uint32_t tc = tcap;
-        void *args[] = {&ms, &mp, &lv, &qs, &ring, &tc};
-        return hipLaunchKernel(fn, dim3(grid), dim3(kExpandBlock), args, lds, s) == hipSuccess ? LHS_OK
-                                                                                                : LHS_EDEVICE;
+        const uint32_t grid = exploration_grid(t, std::min<uint64_t>((uint64_t)t->ncu * per_cu, kBoardGrid));
+        hipLaunchKernelGGL((k_levels<decltype(G)::value, decltype(LS)::value, decltype(R)>), dim3(grid),
+                           dim3(kExpandBlock), lds, s, (const ModelState *)&d->ms, &d->bm, d->tickets, &d->ctl, 1u,
+                           tcap);
+        return hipGetLastError() == hipSuccess ? LHS_OK : LHS_EDEVICE;
     });
     if (rc != LHS_OK)
         return rc;
-    LHS_HIP(hipMemcpyAsync(h, d, offsetof(PrefixArea, ring), hipMemcpyDeviceToHost, s));
-    LHS_HIP(hipMemcpyAsync(t->status_host, t->status, sizeof(DevStatus), hipMemcpyDeviceToHost, s));
+    LHS_HIP(hipMemcpyAsync(h, d, sizeof(LevelsArea), hipMemcpyDeviceToHost, s));
     LHS_HIP(hipStreamSynchronize(s));
-    if (h->qs.error)
-        return (lhs_status)h->qs.error;
-    if (t->status_host->error)
-        return (lhs_status)t->status_host->error;
-    const ModelProgress &P = h->mp;
-    if (!P.done || P.overflow || P.n_levels > kPrefixLevels)
+    if (h->ctl.error)
+        return (lhs_status)h->ctl.error;
+    if (B.status_error)
+        return (lhs_status)B.status_error;
+    if (!B.done || B.overflow || B.n_levels > kBoardLevels)
         return LHS_EDEVICE;
-    out.levels.assign(h->levels + 1, h->levels + P.n_levels);
-    out.total = P.total;
-    out.edges = P.edges;
-    out.deadlocks = P.deadlocks;
-    out.cur = P.cur;
-    out.handed = P.handed != 0;
-    out.capped = P.capped != 0;
+    run.levels.assign(h->levels + 1, h->levels + B.n_levels);
+    run.total = B.total;
+    run.edges = B.edges;
+    run.deadlocks = B.deadlocks;
+    run.wait_hits = B.wait_hits;
+    run.cur = B.cur;
+    run.handed = B.handed != 0;
+    run.capped = B.capped != 0;
     return LHS_OK;
 }
 
@@ -295,7 +195,6 @@ static lhs_status reach_explore_batch_impl(const reach_model *const *models, uin
     // ---- tables and host-side packing (no device work yet) -----------------
     std::vector<uint2> trans_all;
     std::vector<uint32_t> roots, root_off(n);
-    uint64_t pending = n;    // ring cells: at most one level's tiles per model
     for (uint32_t i = 0; i < n && rc == LHS_OK; ++i) {
         BatchModel &b = bm[i];
         b.m = models[i];
@@ -335,23 +234,17 @@ static lhs_status reach_explore_batch_impl(const reach_model *const *models, uin
         b.limit = b.m->state_cap ? (uint32_t)std::min<uint64_t>(b.m->state_cap - 1, 0xFFFFFFFFull)
                                  : 0xFFFFFFFFu;
         b.levels.push_back(1);
-        // tiles of one level: full tiles, or small ones for small levels
-        pending += std::max<uint64_t>(b.t->capacity / kExpandBlock, kSmallLevel / kMinTileRows) + 1;
     }
-    uint64_t cells = 1024;
-    while (cells < 2 * pending)
-        cells <<= 1;
 
     // ---- one device region: [uploaded part | device-only part] -------------
     Carve c;
-    const size_t o_status = c.take<DevStatus>(1), o_qs = c.take<QueueState>(1),
-                 o_mp = c.take<ModelProgress>(n), o_lc = c.take<LevelCounters>(n),
+    const size_t o_status = c.take<DevStatus>(1), o_ctl = c.take<BoardCtl>(1),
+                 o_bm = c.take<BoardModel>(n), o_lc = c.take<LevelCounters>(n),
                  o_slots = c.take<BatchSlot>(n), o_begin = c.take<uint32_t>(n + 1),
                  o_roots = c.take<uint32_t>(roots.size()), o_root_off = c.take<uint32_t>(n),
                  o_trans = c.take<uint2>(trans_all.size()), o_ms = c.take<ModelState>(n),
-                 o_lv = c.take<LevelState>(n), o_zero = c.take<TableZero>(n);
+                 o_tickets = c.take<unsigned long long>(n), o_zero = c.take<TableZero>(n);
     const size_t up_bytes = c.off;
-    const size_t o_ring = host_loop ? 0 : c.take<QCell>(cells);
     const size_t o_levels = host_loop ? 0 : c.take<unsigned long long>((uint64_t)n * max_levels);
     const size_t o_clevels = host_loop ? 0 : c.take<unsigned long long>((uint64_t)n * max_levels);
     const size_t dev_bytes = c.off;
@@ -375,15 +268,14 @@ static lhs_status reach_explore_batch_impl(const reach_model *const *models, uin
     }
     void *D = ws.dev, *H = ws.host;
     DevStatus *d_status = at<DevStatus>(D, o_status);
-    QueueState *d_qs = at<QueueState>(D, o_qs);
-    ModelProgress *d_mp = at<ModelProgress>(D, o_mp);
+    BoardCtl *d_ctl = at<BoardCtl>(D, o_ctl);
+    BoardModel *d_bm = at<BoardModel>(D, o_bm);
     LevelCounters *d_lc = at<LevelCounters>(D, o_lc);
     BatchSlot *d_slots = at<BatchSlot>(D, o_slots);
     uint32_t *d_begin = at<uint32_t>(D, o_begin);
     uint2 *d_trans = at<uint2>(D, o_trans);
     ModelState *d_ms = at<ModelState>(D, o_ms);
-    LevelState *d_lv = at<LevelState>(D, o_lv);
-    QCell *d_ring = at<QCell>(D, o_ring);
+    unsigned long long *d_tickets = at<unsigned long long>(D, o_tickets);
     unsigned long long *d_levels = at<unsigned long long>(D, o_levels);
     LevelCounters *h_lc = at<LevelCounters>(H, h_lc_off);
     BatchSlot *h_slots = at<BatchSlot>(H, h_slots_off);
@@ -416,34 +308,22 @@ static lhs_status reach_explore_batch_impl(const reach_model *const *models, uin
         max_chunks = std::max<uint64_t>(max_chunks, b.t->capacity / 2);
     }
     if (!host_loop) {
-        QueueState &q = *at<QueueState>(H, o_qs);
-        q.head = 0;
-        q.tail = n;
-        q.remaining = n;
-        q.error = 0;
-        q.mask = cells - 1;
+        at<BoardCtl>(H, o_ctl)->remaining = n;
         for (uint32_t i = 0; i < n; ++i) {
             ModelState &M = at<ModelState>(H, o_ms)[i];
             M.t = u_slots[i].t;
             M.m = u_slots[i].m;
-            M.lc = u_slots[i].lc;
             M.fr[0] = bm[i].t->frontier[0];
             M.fr[1] = bm[i].t->frontier[1];
             M.levels = d_levels + (uint64_t)i * max_levels;
             M.cap = bm[i].m->state_cap;
             M.max_levels = max_levels;
-            ModelProgress &P = at<ModelProgress>(H, o_mp)[i];
-            P.total = 1;
-            P.n_levels = 1;
-            LevelState &L = at<LevelState>(H, o_lv)[i];
-            L.front = (unsigned long long)M.fr[0];
-            L.next = (unsigned long long)M.fr[1];
-            L.n_front = 1;
-            L.limit = bm[i].limit;
-            L.tiles_total = 1;
-            L.tiles_done = 0;
-            L.tile_rows = kExpandBlock;
-            L.pad = 0;
+            BoardModel &B = at<BoardModel>(H, o_bm)[i];
+            B.total = 1;
+            B.n_levels = 1;
+            B.n_front = 1;
+            B.limit = bm[i].limit;
+            at<unsigned long long>(H, o_tickets)[i] = make_ticket(1, 0, kExpandBlock, 0);
         }
     }
 
@@ -465,7 +345,7 @@ static lhs_status reach_explore_batch_impl(const reach_model *const *models, uin
         int ncu = 0, per_cu = 0;
         const void *fn = nullptr;
         (void)with_tile(tps, ls, bytes, [&](auto G, auto L, auto R) {
-            fn = (const void *)k_batch_persistent<decltype(G)::value, decltype(L)::value, decltype(R)>;
+            fn = (const void *)k_levels<decltype(G)::value, decltype(L)::value, decltype(R)>;
             return LHS_OK;
         });
         if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
@@ -474,19 +354,17 @@ static lhs_status reach_explore_batch_impl(const reach_model *const *models, uin
             rc = LHS_EDEVICE;
         float ms = 0;
         if (rc == LHS_OK) {
-            hipLaunchKernelGGL(k_init_ring, dim3((uint32_t)std::min<uint64_t>((cells + 255) / 256, 4096)),
-                               dim3(256), 0, s, d_ring, (unsigned long long)cells, n);
             const uint32_t grid = (uint32_t)(ncu * per_cu);
-            void *args[] = {&d_ms, &d_mp, &d_lv, &d_qs, &d_ring, &tcap};
+            void *args[] = {&d_ms, &d_bm, &d_tickets, &d_ctl, &n, &tcap};
             (void)hipEventRecord(ws.ev[0], s);
             if (hipGetLastError() != hipSuccess ||
                 hipLaunchKernel(fn, dim3(grid), dim3(kExpandBlock), args, lds, s) != hipSuccess)
                 rc = LHS_EDEVICE;
             (void)hipEventRecord(ws.ev[1], s);
             if (rc == LHS_OK) {
-                hipLaunchKernelGGL(k_gather_levels, dim3(1), dim3(1024), 0, s, d_ms, d_mp, n,
+                hipLaunchKernelGGL(k_gather_levels, dim3(1), dim3(1024), 0, s, d_ms, d_bm, n,
                                    at<unsigned long long>(D, o_clevels));
-                // status, queue state and progress are the region's first bytes
+                // status, control words and progress are the region's first bytes
                 if (hipGetLastError() != hipSuccess ||
                     hipMemcpyAsync(H, D, o_lc, hipMemcpyDeviceToHost, s) != hipSuccess ||
                     hipStreamSynchronize(s) != hipSuccess)
@@ -496,8 +374,8 @@ static lhs_status reach_explore_batch_impl(const reach_model *const *models, uin
                 (void)hipEventElapsedTime(&ms, ws.ev[0], ws.ev[1]);
         }
         const DevStatus &st = *at<DevStatus>(H, o_status);
-        const QueueState &hq = *at<QueueState>(H, o_qs);
-        const ModelProgress *hmp = at<ModelProgress>(H, o_mp);
+        const BoardCtl &hq = *at<BoardCtl>(H, o_ctl);
+        const BoardModel *hmp = at<BoardModel>(H, o_bm);
         if (rc == LHS_OK && (hq.error || st.error))
             rc = (lhs_status)(hq.error ? hq.error : st.error);
         uint64_t n_lvl = 0;
@@ -513,7 +391,7 @@ static lhs_status reach_explore_batch_impl(const reach_model *const *models, uin
             rc = LHS_EDEVICE;
         uint64_t at_lvl = 0;
         for (uint32_t i = 0; i < n && rc == LHS_OK; ++i) {
-            const ModelProgress &M = hmp[i];
+            const BoardModel &M = hmp[i];
             reach_result &r = results[i];
             r.total_states = M.total;
             r.edges = M.edges;

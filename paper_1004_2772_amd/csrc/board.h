@@ -1,0 +1,412 @@
+// The persistent level driver of the batch (csrc/batch.hip) and of the
+// levels of a single-model BFS that are too small to fill the GPU: one launch
+// of resident workgroups runs every level of every model, each model at its
+// own pace, without grid-wide barriers.
+//
+// Work is handed out by tickets, one 64-bit word per model: the current
+// level's shape (tiles, rows per tile, frontier buffer) in the upper half,
+// the next tile in the lower.  A workgroup takes a tile with one atomic add
+// and knows from the returned word what to expand; a word whose next tile is
+// not below its tiles has no work.  The workgroup that completes a level's
+// last tile finalises the level (cap rollback, level count, frontier swap)
+// and writes the next level's ticket.  Everything one workgroup hands to
+// another goes through agent-scope (coherent) accesses, completed (vmcnt(0))
+// before the ticket or counter that announces it.
+//
+// A workgroup takes its next tile from a model picked at random among those
+// that have tiles, not in the order the levels were finished: a batch's
+// makespan is its deepest models' chains of narrow levels, and in a common
+// FIFO each of those levels waited behind all tiles of the wide models (80 to
+// 420 us a level, 5.8 of 10.2 ms).
+//
+// What bounds a narrow level is its chain of memory round trips (0.7 us
+// each).  So the finaliser keeps tile 0 of the next level for itself, and a
+// level of at most kSoloStates states never leaves its workgroup: its
+// frontier and counts stay in LDS (solo levels), which leaves the trips of
+// the expansion itself (row, slot line, claim, row write).  A one-state level
+// takes 7.8 us so and took 15 us through the queue; a level of some hundred
+// states handed out in tiles takes 19 us.  Against the queue: 64-model batch
+// 8.8 -> 8.2 ms, 5.7k-state search 535 -> 465 us, 10^6-state search (whose
+// last narrow levels no longer go through the host) 2.44 -> 2.06 ms.
+//
+// The workgroups need not all be resident at once: a workgroup waits only
+// for tickets, which finalisers write without waiting for anyone, so one
+// that starts late takes a tile or finds the launch finished.  Every wait is
+// bounded; on timeout the error flag is set and all workgroups leave.
+#pragma once
+
+#include "expand_device.h"
+#include "internal.h"
+#include "persistent.h"
+#include "reach_internal.h"
+
+namespace lhs {
+
+// Shared by all workgroups of a launch; idle ones poll this line.
+struct alignas(128) BoardCtl {
+    uint32_t remaining;   // unfinished models
+    uint32_t error;
+    uint32_t idle;        // workgroups without a tile
+};
+
+// One model's level and progress: written by whichever workgroup finalises a
+// level; and the counters its tiles update, on a line of their own.
+struct BoardModel {
+    alignas(128) uint32_t n_front;   // states of the current level
+    uint32_t limit;                  // new states it may add (the cap)
+    uint32_t cur;                    // its frontier buffer
+    uint32_t n_levels;
+    unsigned long long total, edges, deadlocks;
+    uint32_t done, capped, overflow, handed;   // handed: stopped after a level above handover
+    uint32_t status_error;           // the table's sticky error and waits at the end
+    uint32_t pad;
+    unsigned long long wait_hits;
+    alignas(128) LevelCounters lc;
+    uint32_t tiles_done;
+};
+
+// Tickets.
+constexpr uint32_t kTicketTiles = (1u << 26) - 1;
+__host__ __device__ inline unsigned long long make_ticket(uint32_t tiles, uint32_t cur, uint32_t rows, uint32_t next) {
+    const uint32_t shape = tiles | cur << 26 | (rows == 32 ? 0u : rows == 64 ? 1u : rows == 128 ? 2u : 3u) << 27;
+    return (unsigned long long)shape << 32 | next;
+}
+__device__ __forceinline__ uint32_t ticket_tiles(unsigned long long t) { return (uint32_t)(t >> 32) & kTicketTiles; }
+__device__ __forceinline__ uint32_t ticket_cur(unsigned long long t) { return (uint32_t)(t >> 58) & 1u; }
+__device__ __forceinline__ uint32_t ticket_rows(unsigned long long t) { return 32u << ((uint32_t)(t >> 59) & 3u); }
+__device__ __forceinline__ uint32_t ticket_next(unsigned long long t) { return (uint32_t)t; }
+static_assert(kExpandBlock == 256 && kMinTileRows == 32, "rows of a ticket: 32, 64, 128 or 256");
+
+// A level of at most this many states stays with the workgroup that finished
+// the level before it.  Larger ones (in tiles of 32 states on an otherwise
+// idle GPU) pass through the tickets: a level's fixed cost is about 12 round
+// trips there and four here, but each further 256 successors take three more.
+constexpr uint32_t kSoloStates = 96;
+// ... as long as its successors cannot come near the cap.
+constexpr uint32_t kSoloRoom = 1u << 17;
+
+// Rows per tile of a level (see level_tile_rows): small tiles once the GPU
+// is mostly idle.
+__device__ __forceinline__ uint32_t board_tile_rows(uint32_t remaining, uint32_t idle, uint32_t n_states) {
+    if (n_states > kSmallLevel || remaining > kFewModels || idle < gridDim.x / 2)
+        return kExpandBlock;
+    uint32_t rows = kMinTileRows;
+    while (rows < kExpandBlock && (uint64_t)rows * (idle + 1) < n_states)
+        rows <<= 1;
+    return rows;
+}
+
+// A tile of work: model i, tile `tile` of the level of ticket `ticket`.
+struct BoardItem {
+    uint32_t model, tile, rows, limit, exit;
+    unsigned long long ticket;
+};
+
+// Take a tile (one wavefront, all lanes; `h` a lane-uniform random state).
+// Each poll reads 64 tickets at once.  An idle GPU has more workgroups than
+// new tiles, and their failed adds to one ticket would be served one after
+// the other, so an idle workgroup tries with the probability that about two
+// try for each tile.
+__device__ inline void board_take(const ModelState *ms, BoardModel *bm, unsigned long long *tickets, BoardCtl *ctl,
+                                  uint32_t n, uint32_t &h, BoardItem *out) {
+    const uint32_t lane = __lane_id();
+    uint32_t w0 = 0, polls = 0;
+    bool idle = false;
+    BoardItem it{};
+    it.exit = 1;
+    while (true) {
+        const uint32_t i = w0 + lane;
+        const unsigned long long tk = i < n ? ld_coherent(tickets + i) : 0ull;
+        const uint32_t remaining = ld_coherent(&ctl->remaining), error = ld_coherent(&ctl->error);
+        const uint32_t idlers = ld_coherent(&ctl->idle);
+        if (remaining == 0u || error != 0u)
+            break;
+        const uint32_t tiles = ticket_tiles(tk), avail = tiles - min(ticket_next(tk), tiles);
+        const uint64_t mask = __ballot(avail != 0u);
+        h = h * 1664525u + 1013904223u;
+        if (mask) {
+            const uint32_t r = h >> 8;
+            bool go = true;
+            if (idle) {
+                const uint32_t all = wave_sum(min(avail, 1u << 16));
+                go = r % max(idlers, 1u) < 2u * all;
+            }
+            if (go) {
+                const uint32_t k = r % (uint32_t)__popcll(mask);
+                const uint32_t src = (uint32_t)__builtin_ctzll(__ballot(avail != 0u && mbcnt(mask) == k));
+                unsigned long long got = 0;
+                if (lane == src)
+                    got = atomicAdd(tickets + i, 1ull);
+                got = (unsigned long long)__shfl((uint32_t)got, (int)src, 64) |
+                      (unsigned long long)__shfl((uint32_t)(got >> 32), (int)src, 64) << 32;
+                if (ticket_next(got) < ticket_tiles(got)) {
+                    it.exit = 0;
+                    it.model = w0 + src;
+                    it.tile = ticket_next(got);
+                    it.ticket = got;
+                    break;
+                }
+                continue;
+            }
+        } else if (!idle) {
+            idle = true;
+            if (lane == 0)
+                atomicAdd(&ctl->idle, 1u);
+        }
+        if (++polls > kBarrierSpinLimit) {
+            if (lane == 0)
+                atomicCAS(&ctl->error, 0u, (uint32_t)LHS_ESTALL);
+            break;
+        }
+        w0 = w0 + 64 < n ? w0 + 64 : 0u;
+        __builtin_amdgcn_s_sleep(4);
+    }
+    if (idle && lane == 0)
+        atomicSub(&ctl->idle, 1u);
+    if (!it.exit) {
+        // the level record was complete before its ticket; it is read only
+        // for the level's last tile and where there is a cap
+        const uint32_t tiles = ticket_tiles(it.ticket);
+        const bool capped = ms[it.model].cap != 0;
+        it.rows = ticket_rows(it.ticket);
+        it.limit = 0xFFFFFFFFu;
+        if (it.tile + 1 == tiles || capped) {
+            const uint32_t nf = ld_coherent(&bm[it.model].n_front), lim = ld_coherent(&bm[it.model].limit);
+            it.rows = min(it.rows, nf - it.tile * it.rows);
+            it.limit = lim;
+        }
+    }
+    if (lane == 0)
+        *out = it;
+}
+
+// The progress of the model whose level this workgroup has finalised or runs
+// alone, and what it does next.
+struct BoardOwn {
+    unsigned long long total, edges, deadlocks;
+    uint32_t cur, n_levels;         // frontier buffer of the level just found; levels so far
+    uint32_t n_next, limit;         // its states, and the new states it may add
+    uint32_t tiles, rows;           // its tiles, of `rows` states (0: the model is finished)
+    uint32_t solo;                  // it stays with this workgroup
+};
+
+// Whether a level of n_next states found after own.n_levels levels stays
+// with its workgroup.
+__device__ __forceinline__ bool solo_next(const ModelState &M, const BoardOwn &own, uint32_t n_next) {
+    return n_next != 0 && n_next <= kSoloStates && own.n_levels + 1 < M.max_levels &&
+           (!M.cap || M.cap - own.total > (uint64_t)n_next + kSoloRoom);
+}
+
+// A level of n_next states of model M has been found (own: the progress
+// before it).  End the model, keep the level whole (`solo`), or hand its
+// tiles out and keep tile 0.  Thread 0.  Unless solo, the level's frontier is
+// complete in fr[own.cur ^ 1].
+__device__ inline void board_next(const ModelState &M, BoardModel &B, unsigned long long *ticket, BoardCtl *ctl,
+                                  BoardOwn &own, uint32_t n_next, bool over, bool solo, uint32_t remaining,
+                                  uint32_t idle) {
+    bool done = false;
+    own.n_next = n_next;
+    own.tiles = 0;
+    own.solo = 0;
+    if (over) {
+        st_coherent(&B.capped, 1u);
+        done = true;
+    } else if (n_next == 0) {
+        done = true;
+    } else if (own.n_levels == M.max_levels) {
+        st_coherent(&B.overflow, 1u);
+        done = true;
+    } else {
+        st_coherent(M.levels + own.n_levels, (unsigned long long)n_next);
+        ++own.n_levels;
+        own.total += n_next;
+        own.cur ^= 1u;
+        if (M.handover && (n_next > M.handover || own.n_levels == M.max_levels)) {
+            // a level too wide (or one level array full): the caller
+            // expands it and the rest
+            st_coherent(&B.handed, 1u);
+            done = true;
+        }
+    }
+    const uint64_t room = M.cap ? M.cap - own.total : 0xFFFFFFFFull;
+    own.limit = (uint32_t)min<uint64_t>(room, 0xFFFFFFFFull);
+    if (solo) {
+        own.tiles = 1;
+        own.rows = kExpandBlock;
+        own.solo = 1;
+        return;
+    }
+    if (!done) {
+        own.rows = board_tile_rows(remaining, idle, n_next);
+        own.tiles = (n_next + own.rows - 1) / own.rows;
+        st_coherent(&B.n_front, n_next);
+        st_coherent(&B.limit, own.limit);
+    } else {
+        const uint32_t err = ld_coherent(&M.t.status->error);
+        const unsigned long long waits = ld_coherent(&M.t.status->wait_hits);
+        st_coherent(&B.status_error, err);
+        st_coherent(&B.wait_hits, waits);
+        st_coherent(&B.done, 1u);
+    }
+    st_coherent(&B.total, own.total);
+    st_coherent(&B.edges, own.edges);
+    st_coherent(&B.deadlocks, own.deadlocks);
+    st_coherent(&B.cur, own.cur);
+    st_coherent(&B.n_levels, own.n_levels);
+    wait_vm_complete();
+    if (done)
+        atomicSub(&ctl->remaining, 1u);
+    else if (own.tiles > 1)
+        st_coherent(ticket, make_ticket(own.tiles, own.cur, own.rows, 1u));
+}
+
+// One launch: all levels of the n models.
+template <int G, uint32_t LS, class R>
+__device__ __forceinline__ void board_run(uint32_t *smem, const ModelState *__restrict__ ms, BoardModel *bm,
+                                          unsigned long long *tickets, BoardCtl *ctl, uint32_t n, uint32_t tcap) {
+    __shared__ BoardItem s_it;
+    __shared__ BoardOwn s_own;
+    __shared__ uint32_t s_fin, s_over;
+    enum : uint32_t { kTake, kKept, kSolo };
+    const uint32_t tid = threadIdx.x;
+    uint32_t h = (blockIdx.x + 1u) * 2654435761u, mode = kTake, solo_levels = 0;
+    expand_begin();
+    while (true) {
+        if (mode == kTake) {
+            if (tid < 64)
+                board_take(ms, bm, tickets, ctl, n, h, &s_it);
+            __syncthreads();
+            if (s_it.exit)
+                break;
+        }
+        const bool solo = mode == kSolo;
+        const uint32_t i = s_it.model;
+        const ModelState &M = ms[i];
+        BoardModel &B = bm[i];
+        const uint32_t cur = mode == kTake ? ticket_cur(s_it.ticket) : s_own.cur;
+        const uint32_t rows = s_it.rows, tiles = mode == kTake ? ticket_tiles(s_it.ticket) : s_own.tiles;
+        const uint64_t base = mode == kTake ? (uint64_t)s_it.tile * ticket_rows(s_it.ticket) : 0u;
+        const uint32_t limit = solo ? 0xFFFFFFFFu : s_it.limit;
+        uint32_t *nbuf = expand_nbuf<G, R>(smem, M.m.W, tcap), *lds_front = nbuf + kHoldFront;
+        // a solo level's frontier is in LDS from the second one on
+        const uint32_t *held = solo && solo_levels ? lds_front : nullptr;
+        if (tid == 0)
+            s_pushed = 0;
+        expand_tile<G, LS, R, true>(smem, M.t, M.m, M.fr[cur], base, rows, M.fr[cur ^ 1u], &B.lc, limit, tcap,
+                                    SegOut{}, solo, held);
+        if (!solo) {
+            // this workgroup's stores of the tile are complete before it
+            // counts the tile as done
+            wait_vm_complete();
+            __syncthreads();
+            if (tid == 0)
+                s_fin = atomicAdd(&B.tiles_done, 1u) + 1u == tiles;
+            __syncthreads();
+            if (!s_fin) {
+                mode = kTake;
+                continue;
+            }
+            // the level is complete: its counts, and the progress so far
+            uint32_t n_next = 0, remaining = 0, idle = 0, error = 0;
+            if (tid == 0) {
+                n_next = ld_coherent(&B.lc.n_next);
+                const unsigned long long e = ld_coherent(&B.lc.edges), d = ld_coherent(&B.lc.deadlocks);
+                const unsigned long long pt = ld_coherent(&B.total), pe = ld_coherent(&B.edges),
+                                         pd = ld_coherent(&B.deadlocks);
+                const uint32_t nl = ld_coherent(&B.n_levels);
+                remaining = ld_coherent(&ctl->remaining);
+                idle = ld_coherent(&ctl->idle);
+                error = ld_coherent(&ctl->error);
+                const bool over = M.cap && n_next > limit;
+                s_own.total = pt;
+                s_own.edges = pe + (over ? 0 : e);
+                s_own.deadlocks = pd + (over ? 0 : d);
+                s_own.cur = cur;
+                s_own.n_levels = nl;
+                s_own.n_next = n_next;
+                s_over = over;
+            }
+            __syncthreads();
+            if (s_over) {
+                // discard the partial level: zero every slot it claimed
+                const uint32_t *next = M.fr[cur ^ 1u];
+                for (uint32_t j = tid; j < s_own.n_next; j += kExpandBlock)
+                    st_coherent(M.t.bucket + ld_coherent(next + j), 0ull);
+                wait_vm_complete();
+                __syncthreads();
+            }
+            if (tid == 0) {
+                st_coherent(&B.lc.n_next, 0u);
+                st_coherent(&B.lc.abort, 0u);
+                st_coherent(&B.lc.edges, 0ull);
+                st_coherent(&B.lc.deadlocks, 0ull);
+                st_coherent(&B.tiles_done, 0u);
+                board_next(M, B, tickets + i, ctl, s_own, n_next, s_over != 0, solo_next(M, s_own, n_next) && !s_over,
+                           remaining, idle);
+                s_it.exit = error;
+            }
+        } else {
+            __syncthreads();
+            // found: in the buffer, or (it filled up) in the next frontier
+            const bool spilled = s_pushed != 0;
+            if (spilled)
+                flush_new_slots<true>(nbuf, M.fr[cur ^ 1u], &B.lc, 0xFFFFFFFFu);
+            const uint32_t found = spilled ? s_pushed : s_nnew;
+            const bool stay = !spilled && solo_next(M, s_own, found);
+            if (!spilled)
+                for (uint32_t j = tid; j < found; j += kExpandBlock) {
+                    if (stay)
+                        lds_front[j] = nbuf[j];
+                    else
+                        st_coherent(M.fr[cur ^ 1u] + j, nbuf[j]);
+                }
+            if (!stay)
+                wait_vm_complete();
+            __syncthreads();
+            if (tid == 0) {
+                s_own.edges += s_acc_edges;
+                s_own.deadlocks += s_acc_dead;
+                s_acc_edges = 0;
+                s_acc_dead = 0;
+                s_nnew = 0;
+                flush_counters(M.t.status);
+                uint32_t remaining = 0, idle = 0, error = 0;
+                if (!stay || (solo_levels & 31u) == 31u) {
+                    remaining = ld_coherent(&ctl->remaining);
+                    idle = ld_coherent(&ctl->idle);
+                    error = ld_coherent(&ctl->error);
+                }
+                if (spilled)
+                    st_coherent(&B.lc.n_next, 0u);
+                board_next(M, B, tickets + i, ctl, s_own, found, false, stay, remaining, idle);
+                s_it.exit = error;
+            }
+        }
+        if (tid == 0 && s_own.tiles) {
+            s_it.tile = 0;
+            s_it.rows = min(s_own.rows, s_own.n_next);
+            s_it.limit = s_own.limit;
+        }
+        __syncthreads();
+        if (s_own.tiles && s_it.exit)
+            break;
+        solo_levels = s_own.solo && solo ? solo_levels + 1 : 0;
+        mode = s_own.solo ? kSolo : (s_own.tiles ? kKept : kTake);
+    }
+}
+
+// The levels of a single-model BFS that a board launch runs (explore_levels):
+// its control words, ticket, level state, model constants and level counts,
+// in one region (device, and its pinned mirror).
+constexpr uint32_t kBoardLevels = 4096;           // level counts per launch
+constexpr uint32_t kBoardHandover = 1u << 16;     // states of a level the launch still expands
+constexpr uint32_t kBoardGrid = 256;              // workgroups
+struct LevelsArea {
+    BoardCtl ctl;
+    unsigned long long tickets[64];
+    BoardModel bm;
+    ModelState ms;
+    unsigned long long levels[kBoardLevels];
+};
+
+}  // namespace lhs

@@ -119,6 +119,7 @@ __device__ __forceinline__ bool same_vector(const SuccVec<R> &v, const SuccVec<R
 // runs its find-or-put, so hash and descriptor stay in its registers; the
 // layout then fits four workgroups of a 16-word model per CU.
 constexpr uint32_t kNewBuf = 1536;
+constexpr uint32_t kHoldFront = kNewBuf - kExpandBlock;   // a held level's frontier, behind its new states
 constexpr uint32_t kEagerRoom = 1u << 22;
 constexpr uint32_t kMaskArea = 2 * kExpandBlock + 258;
 static_assert(kQueue <= kMaskArea, "queue shares the mask area");
@@ -440,6 +441,10 @@ __device__ __forceinline__ uint32_t wave_scan_incl(uint32_t x) {
 // their states as open first (flush_new_slots, COUNT_OPEN).
 // CL: slot lines are read with coherent loads (tables reused within one
 // launch, the persistent server).
+// hold (a level that stays with its workgroup): the tile's new states stay in
+// nbuf (unless it fills up, see s_pushed) and its counts in LDS, nothing is
+// appended and no abort is looked for; held: the frontier's slots in LDS,
+// instead of front[].
 // R: the element type of the tile's LDS rows (uint8_t with G = 1 only).
 template <int G, uint32_t LS, class R, bool COHERENT = false, bool DEFER = false, bool DEFER_COUNTS = DEFER,
           bool AWAIT = false, bool CL = false, bool SEG = false>
@@ -447,7 +452,8 @@ __device__ __forceinline__ bool expand_tile(uint32_t *smem, const TableView &t, 
                                             const uint32_t *__restrict__ front, uint64_t base,
                                             uint32_t rows, uint32_t *__restrict__ next,
                                             LevelCounters *lc, uint32_t limit, uint32_t tcap,
-                                            const SegOut &so = SegOut{}) {
+                                            const SegOut &so = SegOut{}, bool hold = false,
+                                            const uint32_t *held = nullptr) {
     constexpr uint32_t kBlock = kExpandBlock;
     static_assert(sizeof(R) == 4 || G == 1, "byte rows: one lane per operation");
     using Succ = SuccVec<R>;
@@ -479,7 +485,7 @@ __device__ __forceinline__ bool expand_tile(uint32_t *smem, const TableView &t, 
     // The tile's first loads go out together: the level's abort flag and
     // count, the frontier entries, and transitions to stage.
     uint32_t abort_now = 0, count_now = 0;
-    if (tid == 0) {
+    if (tid == 0 && !hold) {
         abort_now = __hip_atomic_load(&lc->abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         // SEG: the level's count is this workgroup's estimate (the cursors
         // are read only near the cap)
@@ -489,7 +495,7 @@ __device__ __forceinline__ bool expand_tile(uint32_t *smem, const TableView &t, 
     uint64_t slot = 0;
     if (staged)
         // rows of earlier levels were published before this level started
-        slot = COHERENT ? ld_coherent(front + base + tid) : front[base + tid];
+        slot = held ? held[tid] : COHERENT ? ld_coherent(front + base + tid) : front[base + tid];
     if (restage) {
         constexpr uint32_t kPer = 4;
         for (uint32_t i0 = tid; i0 < PLK; i0 += kPer * kBlock) {
@@ -635,8 +641,9 @@ __device__ __forceinline__ bool expand_tile(uint32_t *smem, const TableView &t, 
             if (t.parent && is_new) {
                 // predecessor record: the frontier slot of the expanded row
                 const uint32_t row_off = (G == 1 ? my_d0 : d0[q]) & 0xFFFFu;
-                const uint32_t *src = front + base + row_off / stride;
-                t.parent[slot] = COHERENT ? ld_coherent(src) : *src;
+                const uint32_t row = row_off / stride;
+                const uint32_t *src = front + base + row;
+                t.parent[slot] = held ? held[row] : COHERENT ? ld_coherent(src) : *src;
             }
             const uint64_t nm = __ballot(is_new);
             if (nm) {
@@ -649,7 +656,7 @@ __device__ __forceinline__ bool expand_tile(uint32_t *smem, const TableView &t, 
             }
         }
         __syncthreads();
-        if (s_eager || s_nnew > kNewBuf - kBlock)
+        if (s_eager || s_nnew > (hold ? kHoldFront : kNewBuf) - kBlock)
             flush_new();
         return s_abort != 0;
     };
@@ -842,14 +849,15 @@ __device__ __forceinline__ bool expand_tile(uint32_t *smem, const TableView &t, 
     }
     // a workgroup that runs several tiles of one level keeps its buffer
     if constexpr (!DEFER)
-        flush_new();
+        if (!hold)
+            flush_new();
     // ---- edge and deadlock counts of the tile -------------------------------
     const uint32_t mine = tid < rows ? succ_cnt[tid] : 0u;
     const uint32_t e32 = wave_sum(mine), d32 = wave_sum(tid < rows && mine == 0);
     if (t.dead_rec && tid < rows && mine == 0) {
         const uint32_t k = atomicAdd(t.dead_rec, 1u);
         if (k < kDeadRecord)
-            t.dead_rec[1 + k] = COHERENT ? ld_coherent(front + base + tid) : front[base + tid];
+            t.dead_rec[1 + k] = held ? held[tid] : COHERENT ? ld_coherent(front + base + tid) : front[base + tid];
     }
     if (__lane_id() == 0) {
         atomicAdd(&s_acc_edges, (unsigned long long)e32);
@@ -858,7 +866,7 @@ __device__ __forceinline__ bool expand_tile(uint32_t *smem, const TableView &t, 
     gather_counters(t, cnt);
     if constexpr (!DEFER_COUNTS) {
         __syncthreads();
-        if (tid == 0) {
+        if (tid == 0 && !hold) {
             if (s_acc_edges)
                 atomicAdd(&lc->edges, s_acc_edges);
             if (s_acc_dead)

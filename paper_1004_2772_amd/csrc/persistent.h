@@ -1,7 +1,8 @@
-// The persistent work queue shared by the batch driver (csrc/batch.hip) and
-// the persistent server (csrc/serve.hip): a bounded ring of (model, tile)
-// items and the per-model level state that the workgroup finishing a level's
-// last tile advances (finalize_level).
+// The persistent server's work queue (csrc/serve.hip): a bounded ring of
+// (model, tile) items, and the per-model level state that the workgroup
+// finishing a level's last tile advances (finalize_level).  Constants that
+// the batch's level driver (board.h) shares: a model's description, and how
+// levels are cut into tiles.
 #pragma once
 
 #include "expand_device.h"
@@ -137,24 +138,6 @@ __device__ __forceinline__ uint32_t level_tile_rows(QueueState *qs, uint32_t n_s
         rows <<= 1;
     return rows;
 }
-
-// A single-model exploration's first levels, run in one persistent launch
-// until a level exceeds a threshold (explore_prefix): its work queue, model
-// constants, progress, level state and level counts, in one region (device,
-// and its pinned mirror).
-constexpr uint32_t kPrefixHandover = 1u << 16;   // states of a level the prefix still expands
-constexpr uint32_t kPrefixLevels = 4096;
-constexpr uint32_t kPrefixGrid = 256;
-constexpr uint32_t kPrefixCells = 8192;   // > tiles of a level of kPrefixHandover states + kPrefixGrid
-static_assert(kPrefixCells >= 2 * (kPrefixHandover / kMinTileRows + 1 + kPrefixGrid), "prefix ring");
-struct PrefixArea {
-    QueueState qs;
-    ModelState ms;
-    ModelProgress mp;
-    LevelState lv;
-    unsigned long long levels[kPrefixLevels];
-    QCell ring[kPrefixCells];
-};
 
 // Finalise model i's level (M = its constants); block-wide.  Called by the workgroup that
 // completed its last tile.  Returns (uniformly) true when the model has a

@@ -12,7 +12,7 @@
 #include "internal.h"
 #include "reach_internal.h"
 #include "expand_device.h"
-#include "persistent.h"
+#include "board.h"
 
 using namespace lhs;
 
@@ -176,6 +176,18 @@ __global__ void k_finalize_graph(GraphCtx *ctx) {
 __global__ void k_rollback_graph(const GraphCtx *ctx) {
     if (ctx->ctl.rollback_n)
         rollback_segments(ctx->t.bucket, ctx->fr[ctx->ctl.cur ^ 1u], ctx->seg_size, ctx->rb_n);
+}
+
+// The entries of a segmented frontier, dense in out[].
+__global__ void k_dense_front(SegFront f, uint32_t *out) {
+    uint32_t j = blockIdx.x * blockDim.x + threadIdx.x;
+    for (uint32_t k = 0, at = j; k < kSegs; ++k) {
+        if (at < f.n[k]) {
+            out[j] = f.buf[(uint64_t)k * f.size + at];
+            return;
+        }
+        at -= f.n[k];
+    }
 }
 
 constexpr uint32_t kGraphLevels = 8;
@@ -434,11 +446,14 @@ SegFront seg_dense(const uint32_t *buf, uint32_t size, uint64_t n) {
     return f;
 }
 
+// A level of at most this many states goes back to a persistent launch.
+constexpr uint64_t kBoardReturn = 1u << 15;
+
 // Host-driven level loop on table t (already sized, W matching); with a
-// prefix area, the first (small) levels run in one persistent launch.
+// levels area, small levels run in persistent launches.
 lhs_status explore_host_loop(lhs_table *t, const reach_model *m, const uint2 *d_trans,
                              uint32_t max_levels, hipStream_t s, reach_result *r,
-                             uint32_t *d_init, bool parents, PrefixArea *d_pre, PrefixArea *h_pre) {
+                             uint32_t *d_init, bool parents, LevelsArea *d_pre, LevelsArea *h_pre) {
     const ModelView mv = model_view(m, d_trans);
     const bool bytes = rows_fit_bytes(m);
     const TableView tv = bfs_view(t, parents);
@@ -459,22 +474,31 @@ lhs_status explore_host_loop(lhs_table *t, const reach_model *m, const uint2 *d_
     int capped = 0;
     hipLaunchKernelGGL(k_zero_level, dim3(1), dim3(64), 0, s, t->level, t->segs);
     bool finished = false;
-    if (d_pre) {
-        PrefixOut pre;
-        rc = explore_prefix(t, tv, mv, bytes, m->state_cap, d_pre, h_pre, s, pre);
+    // levels that cannot fill the GPU run in one persistent launch each time
+    // they come up in a row: from level `levels.size() - 1`, dense in
+    // frontier[cur]
+    auto small_levels = [&]() -> lhs_status {
+        LevelsRun run;
+        run.n_front = (uint32_t)levels.back();
+        run.cur = cur;
+        run.total = total;
+        const lhs_status rc = explore_levels(t, tv, mv, bytes, m->state_cap, d_pre, h_pre, s, run);
         if (rc != LHS_OK)
             return rc;
-        levels.insert(levels.end(), pre.levels.begin(), pre.levels.end());
+        levels.insert(levels.end(), run.levels.begin(), run.levels.end());
         if (levels.size() > max_levels)
             return LHS_EINVAL;
-        total = pre.total;
-        edges = pre.edges;
-        dead = pre.deadlocks;
-        capped = pre.capped;
-        cur = pre.cur;
-        finished = !pre.handed;
+        total = run.total;
+        edges += run.edges;
+        dead += run.deadlocks;
+        capped = run.capped;
+        cur = run.cur;
+        finished = !run.handed;
         f = seg_dense(t->frontier[cur], size, levels.back());
-    }
+        return LHS_OK;
+    };
+    if (d_pre && (rc = small_levels()) != LHS_OK)
+        return rc;
     while (!finished) {
         uint32_t limit = 0xFFFFFFFFu;
         if (m->state_cap)
@@ -510,6 +534,14 @@ lhs_status explore_host_loop(lhs_table *t, const reach_model *m, const uint2 *d_
         total += n_next;
         f = next;
         cur ^= 1;
+        if (d_pre && n_next <= kBoardReturn) {
+            hipLaunchKernelGGL(k_dense_front, dim3((uint32_t)(n_next + 255) / 256), dim3(256), 0, s, f,
+                               t->frontier[cur ^ 1]);
+            LHS_HIP(hipGetLastError());
+            cur ^= 1;
+            if ((rc = small_levels()) != LHS_OK)
+                return rc;
+        }
     }
     LHS_HIP(hipStreamSynchronize(s));
     r->total_states = total;
@@ -709,7 +741,7 @@ static lhs_status reach_explore_impl(const reach_model *m, const reach_opts *o, 
     Carve c;
     const size_t o_trans = c.take<uint2>(packed.size()), o_init = c.take<uint32_t>(W);
     const size_t upload = c.off, o_ctx = c.take<GraphCtx>(1), o_actl = c.take<AsyncCtl>(1),
-                 o_pre = c.take<PrefixArea>(1);
+                 o_pre = c.take<LevelsArea>(1);
     Workspace &ws = workspace(dev);
     std::unique_lock<std::mutex> lock(ws.mu);
     rc = ensure_bfs_buffers(t);
@@ -743,8 +775,8 @@ static lhs_status reach_explore_impl(const reach_model *m, const reach_opts *o, 
         else if (opts.flags & REACH_F_GRAPH)
             rc = explore_graph(t, m, d_trans, max_levels, s, r, d_init, at<GraphCtx>(ws.host, o_ctx), parents);
         else
-            rc = explore_host_loop(t, m, d_trans, max_levels, s, r, d_init, parents, at<PrefixArea>(ws.dev, o_pre),
-                                   at<PrefixArea>(ws.host, o_pre));
+            rc = explore_host_loop(t, m, d_trans, max_levels, s, r, d_init, parents, at<LevelsArea>(ws.dev, o_pre),
+                                   at<LevelsArea>(ws.host, o_pre));
         (void)hipEventRecord(ws.ev[1], s);
         if (hipEventSynchronize(ws.ev[1]) == hipSuccess) {
             float ms = 0;

@@ -80,20 +80,23 @@ bool rows_fit_bytes(const reach_model *m);
 size_t expand_lds_bytes(uint32_t W, uint32_t tcap, uint32_t tps, bool bytes);
 lhs_status ensure_bfs_buffers(lhs_table *t);
 
-// The first levels of a single-model BFS in one persistent launch (the batch
-// kernel on one model), until a level exceeds kPrefixHandover states: small
-// levels then cost a tile's latency each instead of a launch and a host
-// round trip.  s0 must be frontier[0][0] and the level counters zero.
-struct PrefixArea;
-struct PrefixOut {
-    std::vector<uint64_t> levels;   // counts of levels 1, 2, ...
-    uint64_t total = 1, edges = 0, deadlocks = 0;
-    uint32_t cur = 0;               // frontier buffer of the last level
+// Levels of a single-model BFS that are too small to fill the GPU, in one
+// persistent launch (board.h) from the level described in `run`, until one
+// exceeds kBoardHandover states: small levels then cost their chain of memory
+// round trips each, not a launch and a host round trip.  The level's frontier
+// must be dense in frontier[run.cur].
+struct LevelsArea;
+struct LevelsRun {
+    uint32_t n_front = 1;           // in: the level's states
+    uint32_t cur = 0;               // its frontier buffer; out: the last level's
+    uint64_t total = 1;             // states so far
+    std::vector<uint64_t> levels;   // out: counts of the levels found
+    uint64_t edges = 0, deadlocks = 0, wait_hits = 0;
     bool handed = false;            // stopped after a level above the threshold
     bool capped = false;
 };
-lhs_status explore_prefix(lhs_table *t, const TableView &tv, const ModelView &mv, bool bytes, uint64_t cap,
-                          PrefixArea *d_area, PrefixArea *h_area, hipStream_t s, PrefixOut &out);
+lhs_status explore_levels(lhs_table *t, const TableView &tv, const ModelView &mv, bool bytes, uint64_t cap,
+                          LevelsArea *d_area, LevelsArea *h_area, hipStream_t s, LevelsRun &run);
 uint64_t auto_capacity(const reach_model *m);
 // The view a BFS on t expands with: predecessor records when requested.
 TableView bfs_view(lhs_table *t, bool parents);
