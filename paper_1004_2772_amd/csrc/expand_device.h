@@ -322,6 +322,8 @@ __device__ __forceinline__ void flush_new_slots_seg(const uint32_t *nbuf, const 
 
 // Add a wavefront's lane counters to the workgroup's (all 64 lanes call it).
 __device__ __forceinline__ void gather_counters(const TableView &t, const LaneCounters &c) {
+    if (!__ballot((c.waits | c.cas_failures) != 0) && !(t.flags & (kCountLines | kCountMerged)))
+        return;
     const uint32_t w = wave_sum(c.waits), f = wave_sum(c.cas_failures);
     const uint32_t l = (t.flags & kCountLines) ? wave_sum(c.lines) : 0u;
     const uint32_t mg = (t.flags & kCountMerged) ? wave_sum(c.merged) : 0u;
@@ -385,17 +387,6 @@ __device__ __forceinline__ uint2 ld_trans(const uint2 *p) {
     } else {
         return *p;
     }
-}
-
-__device__ __forceinline__ uint32_t wave_scan_incl(uint32_t x) {
-    const uint32_t lane = __lane_id();
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const uint32_t y = __shfl_up(x, d, 64);
-        if (lane >= (uint32_t)d)
-            x += y;
-    }
-    return x;
 }
 
 // Expand states front[base, base + rows) of one model (rows <= 256).  All
@@ -709,16 +700,22 @@ __device__ __forceinline__ bool expand_tile(uint32_t *smem, const TableView &t, 
                     on[j] = p0 + j < m.P && local < m.L;
                     tb[j] = on[j] ? (p * m.L + local) * m.K : 0u;   // below 32 * 65535 * 16
                 }
-                for (uint32_t k = 0; k < m.K; ++k) {
-                    uint2 x[4];
+                uint2 x[4];
 #pragma unroll
-                    for (uint32_t j = 0; j < 4; ++j)
-                        x[j] = trans_at(tb[j] + k);
+                for (uint32_t j = 0; j < 4; ++j)
+                    x[j] = trans_at(tb[j]);
+                for (uint32_t k = 0; k < m.K; ++k) {
+                    uint32_t gvar[4], val[4], want[4];
 #pragma unroll
                     for (uint32_t j = 0; j < 4; ++j) {
-                        const uint32_t gvar = (x[j].x >> 16) & 0xFFu;
-                        const uint32_t val = row[gvar == 0xFFu ? 0u : m.P + gvar];
-                        const bool en = on[j] && (gvar == 0xFFu || val == (x[j].y & 0xFFFFu));
+                        gvar[j] = (x[j].x >> 16) & 0xFFu;
+                        want[j] = x[j].y & 0xFFFFu;
+                        val[j] = row[gvar[j] == 0xFFu ? 0u : m.P + gvar[j]];
+                        x[j] = trans_at(tb[j] + min(k + 1, m.K - 1));   // the next one, while this is compared
+                    }
+#pragma unroll
+                    for (uint32_t j = 0; j < 4; ++j) {
+                        const bool en = on[j] && (gvar[j] == 0xFFu || val[j] == want[j]);
                         rem |= (uint64_t)en << (((p0 + j) * m.K + k) & 63u);
                     }
                 }
@@ -853,7 +850,8 @@ __device__ __forceinline__ bool expand_tile(uint32_t *smem, const TableView &t, 
             flush_new();
     // ---- edge and deadlock counts of the tile -------------------------------
     const uint32_t mine = tid < rows ? succ_cnt[tid] : 0u;
-    const uint32_t e32 = wave_sum(mine), d32 = wave_sum(tid < rows && mine == 0);
+    const uint64_t dead = __ballot(tid < rows && mine == 0);
+    const uint32_t e32 = wave_sum(mine);
     if (t.dead_rec && tid < rows && mine == 0) {
         const uint32_t k = atomicAdd(t.dead_rec, 1u);
         if (k < kDeadRecord)
@@ -861,7 +859,8 @@ __device__ __forceinline__ bool expand_tile(uint32_t *smem, const TableView &t, 
     }
     if (__lane_id() == 0) {
         atomicAdd(&s_acc_edges, (unsigned long long)e32);
-        atomicAdd(&s_acc_dead, (unsigned long long)d32);
+        if (dead)
+            atomicAdd(&s_acc_dead, (unsigned long long)__popcll(dead));
     }
     gather_counters(t, cnt);
     if constexpr (!DEFER_COUNTS) {

@@ -131,6 +131,29 @@ __device__ __forceinline__ uint32_t fresh_lane() {
     return l;
 }
 
+// Inclusive prefix sum over the wavefront (all 64 lanes active): the lanes of
+// a row of 16 by shifts, then the row sums carried on.  Moves between lanes
+// inside the vector unit take a few cycles; through LDS (shuffles) each step
+// costs about 130, and a tile has some twenty of them.
+template <int Ctrl, int Rows>
+__device__ __forceinline__ uint32_t lane_move(uint32_t x) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, Ctrl, Rows, 0xF, false);
+}
+__device__ __forceinline__ uint32_t wave_scan_incl(uint32_t x) {
+    x += lane_move<0x111, 0xF>(x);   // from 1, 2, 4 and 8 lanes below in the row
+    x += lane_move<0x112, 0xF>(x);
+    x += lane_move<0x114, 0xF>(x);
+    x += lane_move<0x118, 0xF>(x);
+    x += lane_move<0x142, 0xA>(x);   // lane 15 of the row below, into rows 1 and 3
+    x += lane_move<0x143, 0xC>(x);   // lane 31, into rows 2 and 3
+    return x;
+}
+
+// Sum over the wavefront (all 64 lanes active); lane-uniform result.
+__device__ __forceinline__ uint32_t wave_sum(uint32_t x) {
+    return (uint32_t)__builtin_amdgcn_readlane((int)wave_scan_incl(x), 63);
+}
+
 // ---- coherent (agent-scope) accesses --------------------------------------
 __device__ __forceinline__ uint64_t ld_coherent(const uint64_t *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -697,18 +720,37 @@ __device__ __forceinline__ void coop_write_rows(WS *ws, const uint32_t *smem, ui
     }
     wave_lds_sync();
     const uint32_t c = lane & 7u;
-    for (uint32_t i0 = 0; i0 < ng; i0 += 8) {
-        const uint32_t i = i0 + (lane >> 3);
-        if (i < ng) {
-            const Vec v = Vec::decode(smem, make_uint2(ws->desc[i], ws->aux[i]));
-            uint32_t *row = data + (uint64_t)ws->idx[i] * W;
-            if ((W & 1u) == 0) {
-                uint64_t *r2 = reinterpret_cast<uint64_t *>(row);
-                for (uint32_t j = c; j < W / 2; j += 8)
-                    st_coherent(r2 + j, (uint64_t)v.get(2 * j) | ((uint64_t)v.get(2 * j + 1) << 32));
-            } else {
-                for (uint32_t j = c; j < W; j += 8)
-                    st_coherent(row + j, v.get(j));
+    // two rows per lane at a time: their reads from LDS overlap
+    for (uint32_t i0 = 0; i0 < ng; i0 += 16) {
+        uint32_t r[2], at[2];
+        Vec v[2];
+#pragma unroll
+        for (uint32_t q = 0; q < 2; ++q) {
+            r[q] = min(i0 + 8 * q + (lane >> 3), ng - 1);
+            at[q] = ws->idx[r[q]];
+            v[q] = Vec::decode(smem, make_uint2(ws->desc[r[q]], ws->aux[r[q]]));
+        }
+        if ((W & 1u) == 0) {
+            for (uint32_t j = c; j < W / 2; j += 8) {
+                uint64_t x[2];
+#pragma unroll
+                for (uint32_t q = 0; q < 2; ++q)
+                    x[q] = (uint64_t)v[q].get(2 * j) | ((uint64_t)v[q].get(2 * j + 1) << 32);
+#pragma unroll
+                for (uint32_t q = 0; q < 2; ++q)
+                    if (i0 + 8 * q + (lane >> 3) < ng)
+                        st_coherent(reinterpret_cast<uint64_t *>(data + (uint64_t)at[q] * W) + j, x[q]);
+            }
+        } else {
+            for (uint32_t j = c; j < W; j += 8) {
+                uint32_t x[2];
+#pragma unroll
+                for (uint32_t q = 0; q < 2; ++q)
+                    x[q] = v[q].get(j);
+#pragma unroll
+                for (uint32_t q = 0; q < 2; ++q)
+                    if (i0 + 8 * q + (lane >> 3) < ng)
+                        st_coherent(data + (uint64_t)at[q] * W + j, x[q]);
             }
         }
     }
@@ -920,19 +962,13 @@ __device__ __forceinline__ void find_or_put_wave(const TableView &t, WaveScratch
     }
 }
 
-// Sum one value over the active lanes of the wavefront; lane-uniform result.
-__device__ __forceinline__ uint32_t wave_sum(uint32_t x) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1)
-        x += __shfl_xor(x, off, 64);
-    return x;
-}
-
 // Add a wavefront's lane counters to the table's striped counters; t.status
 // is a table's own (the first member of its TableStatus).  Must be called by
 // all 64 lanes of the wavefront.  Lines probed are added only when the table
 // counts them (on by request: see lhs_set_counters).
 __device__ __forceinline__ void flush_counters_striped(const TableView &t, const LaneCounters &c) {
+    if (!__ballot((c.waits | c.cas_failures) != 0) && !(t.flags & kCountLines))
+        return;
     const uint32_t w = wave_sum(c.waits), f = wave_sum(c.cas_failures);
     const uint32_t l = (t.flags & kCountLines) ? wave_sum(c.lines) : 0u;
     if (__lane_id() == 0) {
