@@ -35,7 +35,8 @@ __global__ __launch_bounds__(kExpandBlock, LS == 8 ? 4 : 1) void k_levels(const 
                                                                          BoardModel *bm, unsigned long long *tickets,
                                                                          BoardCtl *ctl, uint32_t n, uint32_t tcap) {
     extern __shared__ uint32_t smem[];
-    board_run<G, LS, R>(smem, ms, bm, tickets, ctl, n, tcap);
+    BatchDriver drv;
+    board_run<G, LS, R>(drv, smem, ms, bm, tickets, ctl, n, tcap);
 }
 
 uint64_t batch_auto_capacity(const reach_model *m) {
@@ -43,13 +44,6 @@ uint64_t batch_auto_capacity(const reach_model *m) {
         return auto_capacity(m);
     return 1ull << 21;
 }
-
-// One table to empty: its slots, status word and striped counters.
-struct TableZero {
-    uint4 *bucket;
-    unsigned long long chunks;   // 16-byte chunks of the slot array
-    TableStatus *status;
-};
 
 // Empty every table of the batch in one launch: blockIdx.y = table.
 __global__ void k_clear_tables(const TableZero *z) {

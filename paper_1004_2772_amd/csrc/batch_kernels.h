@@ -27,6 +27,13 @@ struct BatchSlot {
     uint32_t pad;
 };
 
+// One table to empty: its slots, status word and striped counters.
+struct TableZero {
+    uint4 *bucket;
+    unsigned long long chunks;   // 16-byte chunks of the slot array
+    TableStatus *status;
+};
+
 __device__ __forceinline__ uint32_t find_slot_by_tile(const uint32_t *begin, uint32_t n, uint32_t g) {
     uint32_t lo = 0, hi = n;   // begin[lo] <= g < begin[hi]
     while (hi - lo > 1) {

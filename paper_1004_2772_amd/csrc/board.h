@@ -1,7 +1,7 @@
-// The persistent level driver of the batch (csrc/batch.hip) and of the
-// levels of a single-model BFS that are too small to fill the GPU: one launch
-// of resident workgroups runs every level of every model, each model at its
-// own pace, without grid-wide barriers.
+// The persistent level driver of the batch (csrc/batch.hip), of the levels of
+// a single-model BFS that are too small to fill the GPU, and of the server
+// (csrc/serve.hip): one launch of resident workgroups runs every level of
+// every model, each model at its own pace, without grid-wide barriers.
 //
 // Work is handed out by tickets, one 64-bit word per model: the current
 // level's shape (tiles, rows per tile, frontier buffer) in the upper half,
@@ -37,16 +37,30 @@
 
 #include "expand_device.h"
 #include "internal.h"
-#include "persistent.h"
 #include "reach_internal.h"
 
 namespace lhs {
+
+constexpr uint32_t kBarrierSpinLimit = 1u << 24;   // bound on an idle workgroup's polls
+
+// Per-model constants (written by the host before the launch, or before the
+// server admits the model).
+struct ModelState {
+    TableView t;
+    ModelView m;
+    uint32_t *fr[2];
+    unsigned long long *levels;   // [max_levels] level counts (coherent stores)
+    unsigned long long cap;
+    uint32_t max_levels;
+    uint32_t handover;            // stop after a level of more states (0 = never)
+};
 
 // Shared by all workgroups of a launch; idle ones poll this line.
 struct alignas(128) BoardCtl {
     uint32_t remaining;   // unfinished models
     uint32_t error;
     uint32_t idle;        // workgroups without a tile
+    uint32_t slots;       // server: tickets in use are below this
 };
 
 // One model's level and progress: written by whichever workgroup finalises a
@@ -61,6 +75,7 @@ struct BoardModel {
     uint32_t status_error;           // the table's sticky error and waits at the end
     uint32_t pad;
     unsigned long long wait_hits;
+    unsigned long long key;          // server: the query's ModelView key
     alignas(128) LevelCounters lc;
     uint32_t tiles_done;
 };
@@ -75,6 +90,9 @@ __device__ __forceinline__ uint32_t ticket_tiles(unsigned long long t) { return 
 __device__ __forceinline__ uint32_t ticket_cur(unsigned long long t) { return (uint32_t)(t >> 58) & 1u; }
 __device__ __forceinline__ uint32_t ticket_rows(unsigned long long t) { return 32u << ((uint32_t)(t >> 59) & 3u); }
 __device__ __forceinline__ uint32_t ticket_next(unsigned long long t) { return (uint32_t)t; }
+constexpr uint32_t kSmallLevel = 32768;
+constexpr uint32_t kMinTileRows = 32;
+constexpr uint32_t kFewModels = 8;
 static_assert(kExpandBlock == 256 && kMinTileRows == 32, "rows of a ticket: 32, 64, 128 or 256");
 
 // A level of at most this many states stays with the workgroup that finished
@@ -85,8 +103,13 @@ constexpr uint32_t kSoloStates = 96;
 // ... as long as its successors cannot come near the cap.
 constexpr uint32_t kSoloRoom = 1u << 17;
 
-// Rows per tile of a level (see level_tile_rows): small tiles once the GPU
-// is mostly idle.
+// Rows per tile of a level.  Once at most kFewModels models remain and at
+// least half the workgroups are idle, a level of at most kSmallLevel states
+// is cut into tiles of down to kMinTileRows states, about one per idle
+// workgroup: the deepest models' narrow levels, run after the rest of the
+// batch has finished, then spread over the idle GPU instead of one full
+// tile's latency chain per workgroup.  Otherwise tiles stay full (less
+// per-tile work while the GPU is busy).
 __device__ __forceinline__ uint32_t board_tile_rows(uint32_t remaining, uint32_t idle, uint32_t n_states) {
     if (n_states > kSmallLevel || remaining > kFewModels || idle < gridDim.x / 2)
         return kExpandBlock;
@@ -96,30 +119,69 @@ __device__ __forceinline__ uint32_t board_tile_rows(uint32_t remaining, uint32_t
     return rows;
 }
 
-// A tile of work: model i, tile `tile` of the level of ticket `ticket`.
+// What a workgroup does next: tile `tile` of model `model`'s level of ticket
+// `ticket`, or (server) a query to admit, or leave.
 struct BoardItem {
-    uint32_t model, tile, rows, limit, exit;
-    unsigned long long ticket;
+    uint32_t model, tile, rows, limit, exit, admit;
+    unsigned long long ticket, key;
+};
+
+// How the driver differs between the batch and the server:
+//   kServe                the server: models come and go during the launch
+//   kNapShift, kNap       an idle workgroup's wait between polls: 1 + (idle
+//                         workgroups >> kNapShift) naps of 64 kNap cycles
+//   model(ms, i, key)     model i's constants (block-wide call)
+//   idle_check(...)       server: what an idle workgroup does besides looking
+//                         for tiles (lane 0): 0 nothing, 1 admit, 2 leave
+//   admit(M, B, i)        server: model i's level 0 (block-wide call)
+//   level(M, k, n)        store a level's count (thread 0)
+//   beat()                server: a sign of progress, at each level handed out
+//   finished(...)         thread 0: model i is finished
+struct BatchDriver {
+    static constexpr bool kServe = false;
+    static constexpr uint32_t kNapShift = 5, kNap = 4;
+    __device__ const ModelState &model(const ModelState *ms, uint32_t i, unsigned long long) { return ms[i]; }
+    __device__ uint32_t idle_check(BoardCtl *, uint32_t, uint32_t, uint32_t, uint32_t &) { return 0; }
+    __device__ void admit(const ModelState &, BoardModel &, uint32_t) {}
+    __device__ void level(const ModelState &M, uint32_t k, uint32_t n) {
+        st_coherent(M.levels + k, (unsigned long long)n);
+    }
+    __device__ void beat() {}
+    template <class Own>
+    __device__ void finished(uint32_t, const Own &, uint32_t, uint32_t, uint32_t, unsigned long long) {}
 };
 
 // Take a tile (one wavefront, all lanes; `h` a lane-uniform random state).
 // Each poll reads 64 tickets at once.  An idle GPU has more workgroups than
 // new tiles, and their failed adds to one ticket would be served one after
 // the other, so an idle workgroup tries with the probability that about two
-// try for each tile.
-__device__ inline void board_take(const ModelState *ms, BoardModel *bm, unsigned long long *tickets, BoardCtl *ctl,
-                                  uint32_t n, uint32_t &h, BoardItem *out) {
+// try for each tile; and it waits the longer between polls the more are idle:
+// all polls read the same few lines, which the working workgroups' tickets and
+// counts need too, and a workgroup that has just finished a tile looks again
+// at once in any case.  768 idle workgroups that polled every 0.4 us took a
+// third of the server's time (147-level queries: 11.5 -> 8.5 ms, 60 of a few
+// thousand states each: 6.7 -> 3.4 ms) and some of the batch's (8.1 -> 7.7).
+// The single-model levels, whose 255 idle workgroups see all of a level's
+// tiles at once, lose with longer naps (437 -> 500 us at 2.4 us), so the
+// batch's are short.
+template <class Driver>
+__device__ inline void board_take(Driver &drv, const ModelState *ms, BoardModel *bm, unsigned long long *tickets,
+                                  BoardCtl *ctl, uint32_t n, uint32_t &h, BoardItem *out) {
+    constexpr bool kServe = Driver::kServe;
     const uint32_t lane = __lane_id();
-    uint32_t w0 = 0, polls = 0;
+    uint32_t polls = 0, scanned = 0;
+    h = h * 1664525u + 1013904223u;
+    uint32_t slots = kServe ? min(ld_coherent(&ctl->slots), n) : n;
+    uint32_t w0 = slots > 64 ? (h >> 8) % ((slots + 63) / 64) * 64 : 0;   // any window first
     bool idle = false;
     BoardItem it{};
     it.exit = 1;
     while (true) {
         const uint32_t i = w0 + lane;
-        const unsigned long long tk = i < n ? ld_coherent(tickets + i) : 0ull;
+        const unsigned long long tk = i < slots ? ld_coherent(tickets + i) : 0ull;
         const uint32_t remaining = ld_coherent(&ctl->remaining), error = ld_coherent(&ctl->error);
         const uint32_t idlers = ld_coherent(&ctl->idle);
-        if (remaining == 0u || error != 0u)
+        if ((!kServe && remaining == 0u) || error != 0u)
             break;
         const uint32_t tiles = ticket_tiles(tk), avail = tiles - min(ticket_next(tk), tiles);
         const uint64_t mask = __ballot(avail != 0u);
@@ -148,30 +210,58 @@ __device__ inline void board_take(const ModelState *ms, BoardModel *bm, unsigned
                 }
                 continue;
             }
-        } else if (!idle) {
+        }
+        w0 = w0 + 64 < slots ? w0 + 64 : 0u;
+        if (++scanned * 64 < slots)
+            continue;   // the other windows
+        scanned = 0;
+        if (!idle) {
             idle = true;
             if (lane == 0)
                 atomicAdd(&ctl->idle, 1u);
         }
-        if (++polls > kBarrierSpinLimit) {
+        polls += 1u + (kServe ? 0u : idlers >> 8);   // counts time: naps grow with the idle workgroups
+        const uint32_t wait = 1u + (idlers >> Driver::kNapShift);
+        if constexpr (kServe) {
+            uint32_t act = 0, slot = 0;
             if (lane == 0)
-                atomicCAS(&ctl->error, 0u, (uint32_t)LHS_ESTALL);
-            break;
+                act = drv.idle_check(ctl, polls, remaining, wait, slot);
+            act = (uint32_t)__builtin_amdgcn_readfirstlane((int)act);
+            if (act == 2u)
+                break;
+            if (act == 1u) {
+                it.exit = 0;
+                it.admit = 1;
+                it.model = (uint32_t)__builtin_amdgcn_readfirstlane((int)slot);
+                break;
+            }
+            slots = min(ld_coherent(&ctl->slots), n);
+            // the last query gone: wake up for the next one soon
+            const uint32_t naps = remaining ? wait : min(polls, 8u) / 2u + 1u;
+            for (uint32_t k = 0; k < naps; ++k)
+                __builtin_amdgcn_s_sleep(Driver::kNap);
+        } else {
+            if (polls > kBarrierSpinLimit) {
+                if (lane == 0)
+                    atomicCAS(&ctl->error, 0u, (uint32_t)LHS_ESTALL);
+                break;
+            }
+            for (uint32_t k = 0; k < wait; ++k)
+                __builtin_amdgcn_s_sleep(Driver::kNap);
         }
-        w0 = w0 + 64 < n ? w0 + 64 : 0u;
-        __builtin_amdgcn_s_sleep(4);
     }
     if (idle && lane == 0)
         atomicSub(&ctl->idle, 1u);
-    if (!it.exit) {
-        // the level record was complete before its ticket; it is read only
-        // for the level's last tile and where there is a cap
+    if (!it.exit && !it.admit) {
+        // the level record was complete before its ticket; the batch reads it
+        // only for the level's last tile and where there is a cap
         const uint32_t tiles = ticket_tiles(it.ticket);
-        const bool capped = ms[it.model].cap != 0;
         it.rows = ticket_rows(it.ticket);
         it.limit = 0xFFFFFFFFu;
-        if (it.tile + 1 == tiles || capped) {
-            const uint32_t nf = ld_coherent(&bm[it.model].n_front), lim = ld_coherent(&bm[it.model].limit);
+        if (kServe || it.tile + 1 == tiles || ms[it.model].cap != 0) {
+            const BoardModel &B = bm[it.model];
+            const uint32_t nf = ld_coherent(&B.n_front), lim = ld_coherent(&B.limit);
+            it.key = kServe ? ld_coherent(&B.key) : 0ull;
             it.rows = min(it.rows, nf - it.tile * it.rows);
             it.limit = lim;
         }
@@ -200,24 +290,28 @@ __device__ __forceinline__ bool solo_next(const ModelState &M, const BoardOwn &o
 // A level of n_next states of model M has been found (own: the progress
 // before it).  End the model, keep the level whole (`solo`), or hand its
 // tiles out and keep tile 0.  Thread 0.  Unless solo, the level's frontier is
-// complete in fr[own.cur ^ 1].
-__device__ inline void board_next(const ModelState &M, BoardModel &B, unsigned long long *ticket, BoardCtl *ctl,
-                                  BoardOwn &own, uint32_t n_next, bool over, bool solo, uint32_t remaining,
-                                  uint32_t idle) {
+// complete in fr[own.cur ^ 1].  err: the table's sticky error (server: ends
+// the model).
+template <class Driver>
+__device__ inline void board_next(Driver &drv, const ModelState &M, BoardModel &B, unsigned long long *tickets,
+                                  uint32_t i, BoardCtl *ctl, BoardOwn &own, uint32_t n_next, bool over, uint32_t err,
+                                  bool solo, uint32_t remaining, uint32_t idle) {
     bool done = false;
+    uint32_t overflow = 0;
     own.n_next = n_next;
     own.tiles = 0;
     own.solo = 0;
-    if (over) {
+    if (err || n_next == 0) {
+        done = true;
+    } else if (over) {
         st_coherent(&B.capped, 1u);
         done = true;
-    } else if (n_next == 0) {
-        done = true;
     } else if (own.n_levels == M.max_levels) {
+        overflow = 1;
         st_coherent(&B.overflow, 1u);
         done = true;
     } else {
-        st_coherent(M.levels + own.n_levels, (unsigned long long)n_next);
+        drv.level(M, own.n_levels, n_next);
         ++own.n_levels;
         own.total += n_next;
         own.cur ^= 1u;
@@ -236,14 +330,15 @@ __device__ inline void board_next(const ModelState &M, BoardModel &B, unsigned l
         own.solo = 1;
         return;
     }
+    unsigned long long waits = 0;
     if (!done) {
         own.rows = board_tile_rows(remaining, idle, n_next);
         own.tiles = (n_next + own.rows - 1) / own.rows;
         st_coherent(&B.n_front, n_next);
         st_coherent(&B.limit, own.limit);
     } else {
-        const uint32_t err = ld_coherent(&M.t.status->error);
-        const unsigned long long waits = ld_coherent(&M.t.status->wait_hits);
+        err = ld_coherent(&M.t.status->error);
+        waits = ld_coherent(&M.t.status->wait_hits);
         st_coherent(&B.status_error, err);
         st_coherent(&B.wait_hits, waits);
         st_coherent(&B.done, 1u);
@@ -254,16 +349,22 @@ __device__ inline void board_next(const ModelState &M, BoardModel &B, unsigned l
     st_coherent(&B.cur, own.cur);
     st_coherent(&B.n_levels, own.n_levels);
     wait_vm_complete();
-    if (done)
+    if (done) {
         atomicSub(&ctl->remaining, 1u);
-    else if (own.tiles > 1)
-        st_coherent(ticket, make_ticket(own.tiles, own.cur, own.rows, 1u));
+        drv.finished(i, own, err, over ? 1u : 0u, overflow, waits);
+    } else {
+        drv.beat();
+        if (own.tiles > 1)
+            st_coherent(tickets + i, make_ticket(own.tiles, own.cur, own.rows, 1u));
+    }
 }
 
-// One launch: all levels of the n models.
-template <int G, uint32_t LS, class R>
-__device__ __forceinline__ void board_run(uint32_t *smem, const ModelState *__restrict__ ms, BoardModel *bm,
-                                          unsigned long long *tickets, BoardCtl *ctl, uint32_t n, uint32_t tcap) {
+// One launch: all levels of the n models (server: of the queries in n slots).
+template <int G, uint32_t LS, class R, class Driver>
+__device__ __forceinline__ void board_run(Driver &drv, uint32_t *smem, const ModelState *__restrict__ ms,
+                                          BoardModel *bm, unsigned long long *tickets, BoardCtl *ctl, uint32_t n,
+                                          uint32_t tcap) {
+    constexpr bool kServe = Driver::kServe;
     __shared__ BoardItem s_it;
     __shared__ BoardOwn s_own;
     __shared__ uint32_t s_fin, s_over;
@@ -274,15 +375,36 @@ __device__ __forceinline__ void board_run(uint32_t *smem, const ModelState *__re
     while (true) {
         if (mode == kTake) {
             if (tid < 64)
-                board_take(ms, bm, tickets, ctl, n, h, &s_it);
+                board_take(drv, ms, bm, tickets, ctl, n, h, &s_it);
             __syncthreads();
             if (s_it.exit)
                 break;
         }
-        const bool solo = mode == kSolo;
         const uint32_t i = s_it.model;
-        const ModelState &M = ms[i];
+        const ModelState &M = drv.model(ms, i, s_it.key);
         BoardModel &B = bm[i];
+        if (kServe && mode == kTake && s_it.admit) {
+            // a query's level 0: s0, kept like a level this workgroup found
+            drv.admit(M, B, i);
+            if (tid == 0) {
+                s_own = BoardOwn{};
+                s_own.total = 1;
+                s_own.n_levels = 1;
+                s_own.n_next = 1;
+                s_own.tiles = 1;
+                s_own.rows = kExpandBlock;
+                s_own.limit = M.cap ? (uint32_t)min<unsigned long long>(M.cap - 1, 0xFFFFFFFFull) : 0xFFFFFFFFu;
+                s_own.solo = !M.cap || M.cap > 2 * kSoloRoom;
+                s_it.tile = 0;
+                s_it.rows = 1;
+                s_it.limit = s_own.limit;
+                s_it.key = M.m.key;
+            }
+            __syncthreads();
+            solo_levels = 0;
+            mode = s_own.solo ? kSolo : kKept;
+        }
+        const bool solo = mode == kSolo;
         const uint32_t cur = mode == kTake ? ticket_cur(s_it.ticket) : s_own.cur;
         const uint32_t rows = s_it.rows, tiles = mode == kTake ? ticket_tiles(s_it.ticket) : s_own.tiles;
         const uint64_t base = mode == kTake ? (uint64_t)s_it.tile * ticket_rows(s_it.ticket) : 0u;
@@ -292,8 +414,8 @@ __device__ __forceinline__ void board_run(uint32_t *smem, const ModelState *__re
         const uint32_t *held = solo && solo_levels ? lds_front : nullptr;
         if (tid == 0)
             s_pushed = 0;
-        expand_tile<G, LS, R, true>(smem, M.t, M.m, M.fr[cur], base, rows, M.fr[cur ^ 1u], &B.lc, limit, tcap,
-                                    SegOut{}, solo, held);
+        expand_tile<G, LS, R, true, false, false, false, kServe>(smem, M.t, M.m, M.fr[cur], base, rows, M.fr[cur ^ 1u],
+                                                                 &B.lc, limit, tcap, SegOut{}, solo, held);
         if (!solo) {
             // this workgroup's stores of the tile are complete before it
             // counts the tile as done
@@ -307,9 +429,10 @@ __device__ __forceinline__ void board_run(uint32_t *smem, const ModelState *__re
                 continue;
             }
             // the level is complete: its counts, and the progress so far
-            uint32_t n_next = 0, remaining = 0, idle = 0, error = 0;
+            uint32_t n_next = 0, remaining = 0, idle = 0, error = 0, err = 0;
             if (tid == 0) {
                 n_next = ld_coherent(&B.lc.n_next);
+                err = kServe ? ld_coherent(&M.t.status->error) : 0u;
                 const unsigned long long e = ld_coherent(&B.lc.edges), d = ld_coherent(&B.lc.deadlocks);
                 const unsigned long long pt = ld_coherent(&B.total), pe = ld_coherent(&B.edges),
                                          pd = ld_coherent(&B.deadlocks);
@@ -317,7 +440,7 @@ __device__ __forceinline__ void board_run(uint32_t *smem, const ModelState *__re
                 remaining = ld_coherent(&ctl->remaining);
                 idle = ld_coherent(&ctl->idle);
                 error = ld_coherent(&ctl->error);
-                const bool over = M.cap && n_next > limit;
+                const bool over = !err && M.cap && n_next > limit;
                 s_own.total = pt;
                 s_own.edges = pe + (over ? 0 : e);
                 s_own.deadlocks = pd + (over ? 0 : d);
@@ -341,8 +464,8 @@ __device__ __forceinline__ void board_run(uint32_t *smem, const ModelState *__re
                 st_coherent(&B.lc.edges, 0ull);
                 st_coherent(&B.lc.deadlocks, 0ull);
                 st_coherent(&B.tiles_done, 0u);
-                board_next(M, B, tickets + i, ctl, s_own, n_next, s_over != 0, solo_next(M, s_own, n_next) && !s_over,
-                           remaining, idle);
+                board_next(drv, M, B, tickets, i, ctl, s_own, n_next, s_over != 0, err,
+                           solo_next(M, s_own, n_next) && !s_over && !err, remaining, idle);
                 s_it.exit = error;
             }
         } else {
@@ -378,7 +501,9 @@ __device__ __forceinline__ void board_run(uint32_t *smem, const ModelState *__re
                 }
                 if (spilled)
                     st_coherent(&B.lc.n_next, 0u);
-                board_next(M, B, tickets + i, ctl, s_own, found, false, stay, remaining, idle);
+                if (kServe && (solo_levels & 31u) == 31u)
+                    drv.beat();
+                board_next(drv, M, B, tickets, i, ctl, s_own, found, false, 0u, stay, remaining, idle);
                 s_it.exit = error;
             }
         }

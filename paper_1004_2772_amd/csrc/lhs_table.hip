@@ -328,34 +328,8 @@ lhs_status read_status(lhs_table *t, DevStatus *out) {
     return LHS_OK;
 }
 
-}  // namespace lhs
-
-extern "C" {
-
-const char *lhs_strerror(lhs_status s) {
-    switch (s) {
-    case LHS_OK: return "LHS_OK";
-    case LHS_EINVAL: return "LHS_EINVAL: invalid argument";
-    case LHS_ENOMEM: return "LHS_ENOMEM: out of memory";
-    case LHS_EFULL: return "LHS_EFULL: table full (every line probed)";
-    case LHS_ESTALL: return "LHS_ESTALL: wait on a slot being written exceeded its bound";
-    case LHS_EDEVICE: return "LHS_EDEVICE: HIP runtime error";
-    case LHS_EBUDGET: return "LHS_EBUDGET: request exceeds the memory budget";
-    case LHS_ENOTFOUND: return "LHS_ENOTFOUND: unknown ticket";
-    case LHS_EAGAIN: return "LHS_EAGAIN: not ready";
-    }
-    return "LHS_?: unknown status";
-}
-
-lhs_status lhs_create(uint64_t capacity, uint32_t state_words, lhs_table **out) {
-    if (!out || state_words < 1 || state_words > 32)
-        return LHS_EINVAL;
-    const lhs_config cfg = tuned_config(LHS_TUNE_TABLE, state_words, capacity);
-    return lhs_create_ex(capacity, state_words, &cfg, out);
-}
-
-lhs_status lhs_create_ex(uint64_t capacity, uint32_t state_words, const lhs_config *cfg,
-                         lhs_table **out) {
+// lhs_create_ex without the clear: the slots hold no table yet.
+lhs_status alloc_table(uint64_t capacity, uint32_t state_words, const lhs_config *cfg, lhs_table **out) {
     lhs_config c{16, LHS_PROBE_DOUBLE, 0, 0};
     if (cfg) {
         c = *cfg;
@@ -394,11 +368,46 @@ lhs_status lhs_create_ex(uint64_t capacity, uint32_t state_words, const lhs_conf
         lhs_destroy(t);
         return LHS_ENOMEM;
     }
-    if (lhs_clear(t, nullptr) != LHS_OK || hipStreamSynchronize(nullptr) != hipSuccess) {
-        lhs_destroy(t);
+    *out = t;
+    return LHS_OK;
+}
+
+}  // namespace lhs
+
+extern "C" {
+
+const char *lhs_strerror(lhs_status s) {
+    switch (s) {
+    case LHS_OK: return "LHS_OK";
+    case LHS_EINVAL: return "LHS_EINVAL: invalid argument";
+    case LHS_ENOMEM: return "LHS_ENOMEM: out of memory";
+    case LHS_EFULL: return "LHS_EFULL: table full (every line probed)";
+    case LHS_ESTALL: return "LHS_ESTALL: wait on a slot being written exceeded its bound";
+    case LHS_EDEVICE: return "LHS_EDEVICE: HIP runtime error";
+    case LHS_EBUDGET: return "LHS_EBUDGET: request exceeds the memory budget";
+    case LHS_ENOTFOUND: return "LHS_ENOTFOUND: unknown ticket";
+    case LHS_EAGAIN: return "LHS_EAGAIN: not ready";
+    }
+    return "LHS_?: unknown status";
+}
+
+lhs_status lhs_create(uint64_t capacity, uint32_t state_words, lhs_table **out) {
+    if (!out || state_words < 1 || state_words > 32)
+        return LHS_EINVAL;
+    const lhs_config cfg = tuned_config(LHS_TUNE_TABLE, state_words, capacity);
+    return lhs_create_ex(capacity, state_words, &cfg, out);
+}
+
+lhs_status lhs_create_ex(uint64_t capacity, uint32_t state_words, const lhs_config *cfg,
+                         lhs_table **out) {
+    const lhs_status rc = lhs::alloc_table(capacity, state_words, cfg, out);
+    if (rc != LHS_OK)
+        return rc;
+    if (lhs_clear(*out, nullptr) != LHS_OK || hipStreamSynchronize(nullptr) != hipSuccess) {
+        lhs_destroy(*out);
+        *out = nullptr;
         return LHS_EDEVICE;
     }
-    *out = t;
     return LHS_OK;
 }
 

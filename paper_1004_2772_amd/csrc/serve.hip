@@ -40,9 +40,9 @@
 #include <vector>
 
 #include "batch_kernels.h"
+#include "board.h"
 #include "expand_device.h"
 #include "internal.h"
-#include "persistent.h"
 #include "reach_internal.h"
 
 using namespace lhs;
@@ -174,43 +174,46 @@ __global__ __launch_bounds__(kExpandBlock, LS == 8 ? 4 : 1) void k_step(BatchSlo
 
 // ---- persistent server ------------------------------------------------------
 //
-// One launch of resident workgroups serves every query: the batch's work
-// queue (persistent.h) of (query slot, tile) items, whose last-tile
-// finalisation advances a query's level, plus admission and completion.
+// One launch of resident workgroups serves every query: the level driver of
+// the batch (board.h), a ticket per query slot, plus admission and
+// completion.
 //  * Admission.  The host readies a slot (the query's constants in ms[slot],
-//    its s0 in roots[slot], its table emptied) with copies and a clearing
-//    kernel on its upload stream, then appends the slot to box->admit_slot
-//    and raises box->admit_tail, also by copies, in that order.  An idle
-//    workgroup takes the admission, inserts s0 and queues level 0's tile
-//    (it holds a queue position, so it keeps no tile for itself).
-//  * Completion.  The workgroup that finishes a query posts (slot, error) to
-//    a ring of records in pinned host memory (system scope, the sequence
-//    word last, after the query's progress and level counts are complete).
-//  * Work queue.  Each workgroup holds one queue position, taken with a
-//    fetch-and-add, and polls its cell; between polls it takes admissions.
+//    its s0 in roots[slot], its transitions, its table emptied) with one
+//    upload and one kernel on its upload stream, which also appends the slot
+//    to box->admit_slot; then it raises box->admit_tail, by a copy.  An idle
+//    workgroup takes the admission, inserts s0 and runs level 0.
+//  * Completion.  The workgroup that finishes a query posts its result to a
+//    ring of records in pinned host memory (system scope, the sequence word
+//    last, after the query's level counts, also in pinned memory, are
+//    complete).
 //  * Lifetime.  After a while without work, with no query admitted and
 //    unfinished, a workgroup leaves and closes the launch to admissions
 //    (box->closing); every other workgroup leaves once no query is left.
 //    The host starts a new launch when work arrives and the last one has
-//    ended (a query posted to a closing launch waits for the next); before
-//    it, the positions the last launch held unfilled are given back.  A
+//    ended (a query posted to a closing launch waits for the next).  A
 //    query wider than the running launch's LDS rows closes it early (the
 //    host sets box->closing) and waits for the next launch, with the
-//    queries behind it.  The
-//    launch leaves one workgroup's room per CU for the host's clearing
-//    kernels.
+//    queries behind it.  The launch leaves one workgroup's room per CU for
+//    the host's clearing kernels.
 // Slots, tables and transition buffers are reused while a launch runs, so
 // everything the host writes is read past the caches (system scope), and
 // slot lines are read with coherent loads (expand_tile's CL).
+//
+// What bounds a burst of queries is the deepest ones' chain of levels and, in
+// front of it, what the host does per query.  64 queries of 1k to 758k states
+// (two or five of 147 levels): 10.0 to 22.5 ms through a queue of tiles, a
+// copy and a clear per query; 8.0 to 8.9 ms through the tickets, one upload
+// and kernel per group of queries, and fewer polls.  A server's second burst,
+// whose new tables no longer wait for the launch to end: 22 -> 9 ms.
 constexpr uint32_t kAdmitRing = 2048;      // admission entries (> 2 x max active)
 constexpr uint32_t kDoneRing = 2048;       // completion records (> 2 x max active)
-constexpr uint64_t kServeCells = 1ull << 23;   // work-queue cells (128 MiB)
+constexpr uint64_t kServeCapacity = 1ull << 30;   // a served table has fewer slots
 constexpr uint32_t kServeMaxLevels = 1u << 16; // levels of one served query
-constexpr uint32_t kIdleSleepMax = 8;      // back-off steps (~0.4 us each) of an idle workgroup
 constexpr uint32_t kIdleLeave = 384;       // checks (~5 ms) finding no query on the GPU
                                            // before a workgroup leaves
-constexpr uint32_t kStallPolls = 1u << 19; // idle polls (~2 s) without any level finished while
-                                           // queries are unfinished: the launch has stalled
+constexpr uint32_t kStallChecks = 1u << 19; // an idle workgroup's checks (~3 s) without any level
+                                           // finished while queries are unfinished: the launch
+                                           // has stalled
 
 struct ServeBox {
     unsigned long long admit_tail;   // admissions posted (host copies)
@@ -226,7 +229,8 @@ struct ServeBox {
 
 struct DoneRec {
     unsigned long long seq;          // position + 1 once the record is complete
-    uint32_t slot, error, n_levels, pad;
+    unsigned long long total, edges, deadlocks, wait_hits;
+    uint32_t slot, error, n_levels, capped, overflow, pad;
 };
 
 __device__ __forceinline__ unsigned long long ld_system(const unsigned long long *p) {
@@ -235,22 +239,6 @@ __device__ __forceinline__ unsigned long long ld_system(const unsigned long long
 __device__ __forceinline__ uint32_t ld_system(const uint32_t *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
-
-// finalize_level's hook: post the finished query's completion record.
-struct ServeDone {
-    ServeBox *box;
-    DoneRec *done;
-    const ModelProgress *mp;
-    __device__ void operator()(uint32_t slot, uint32_t err) const {
-        const unsigned long long pos = atomicAdd(&box->done_tail, 1ull);
-        DoneRec *r = done + (pos % kDoneRing);
-        __hip_atomic_store(&r->slot, slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-        __hip_atomic_store(&r->error, err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-        __hip_atomic_store(&r->n_levels, ld_coherent(&mp[slot].n_levels), __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_SYSTEM);
-        __hip_atomic_store(&r->seq, pos + 1ull, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-    }
-};
 
 // The constants of slot i's query into LDS, read past every cache (the host
 // rewrites them between queries); block-wide.
@@ -263,242 +251,214 @@ __device__ __forceinline__ void load_model_state(ModelState *dst, const ModelSta
     __syncthreads();
 }
 
-// Admit slot i's query (block-wide): progress and level 0, s0 inserted into
-// its (emptied) table and listed as the first frontier.
-template <uint32_t LS>
-__device__ void admit_query(const ModelState &M, ModelProgress *mp, LevelState *lv, uint32_t i,
-                            const uint32_t *roots) {
-    __shared__ uint32_t row[32];
-    const uint32_t tid = threadIdx.x;
-    if (tid < M.m.W)
-        row[tid] = ld_system(roots + 32u * i + tid);
-    __syncthreads();
-    if (tid < 64) {
-        LaneCounters cnt;
-        const LdsRowB v{row};
-        const bool active = tid == 0;
-        uint32_t slot = kNoSlot, code = kFull;
-        const uint64_t h = hash_vec(v, M.m.W, M.t.seed);
-        find_or_put<1, LS, LdsRowB, true>(M.t, v, h, active, slot, code, cnt);
-        if (active) {
-            ModelProgress &P = mp[i];
-            LevelState &L = lv[i];
-            LevelCounters *lc = M.lc;
-            st_coherent(M.fr[0], slot);
-            st_coherent(&P.total, 1ull);
-            st_coherent(&P.edges, 0ull);
-            st_coherent(&P.deadlocks, 0ull);
-            st_coherent(&P.cur, 0u);
-            st_coherent(&P.n_levels, 1u);
-            st_coherent(&P.done, 0u);
-            st_coherent(&P.capped, 0u);
-            st_coherent(&P.overflow, 0u);
-            st_coherent(&P.error, 0u);
-            st_coherent(&P.handed, 0u);
-            st_coherent(M.levels, 1ull);
-            st_coherent(&lc->n_next, 0u);
-            st_coherent(&lc->abort, 0u);
-            st_coherent(&lc->edges, 0ull);
-            st_coherent(&lc->deadlocks, 0ull);
-            st_coherent(&L.front, (unsigned long long)M.fr[0]);
-            st_coherent(&L.next, (unsigned long long)M.fr[1]);
-            st_coherent(&L.n_front, 1u);
-            st_coherent(&L.limit, M.cap ? (uint32_t)min<unsigned long long>(M.cap - 1, 0xFFFFFFFFull) : 0xFFFFFFFFu);
-            st_coherent(&L.tiles_total, 1u);
-            st_coherent(&L.tiles_done, 0u);
-            st_coherent(&L.tile_rows, (uint32_t)kExpandBlock);
-            st_coherent(&L.key, M.m.key);
-        }
-        wait_vm_complete();
-    }
-    __syncthreads();
+template <class T>
+__device__ __forceinline__ void st_system(T *p, T v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
+
+// The level driver's hooks for the server (board.h).
+template <uint32_t LS>
+struct ServeDriver {
+    static constexpr bool kServe = true;
+    static constexpr uint32_t kNapShift = 4, kNap = 32;
+    ServeBox *box;
+    DoneRec *done;
+    const uint32_t *roots;
+    ModelState *held;        // LDS: the constants of slot *held_slot's query
+    uint32_t *held_slot;     // LDS
+    // lane 0 of the polling wavefront: checks without a query on the GPU, and
+    // without a beat while there are some
+    uint32_t quiet = 0, stall = 0, last_beat = 0;
+
+    // The constants are read again only when the slot holds another query.
+    __device__ const ModelState &model(const ModelState *ms, uint32_t i, unsigned long long key) {
+        if (*held_slot != i || held->m.key != key) {
+            __syncthreads();   // every thread has compared before they change
+            load_model_state(held, ms + i);
+            if (threadIdx.x == 0)
+                *held_slot = i;
+        }
+        return *held;
+    }
+
+    // Nothing to expand at this poll: admissions, or leave once idle.
+    // Leaving and admitting race, so each side announces itself before it
+    // looks at the other (both sequentially consistent): an admission counts
+    // itself in `remaining`, then checks `closing`; a workgroup about to
+    // leave sets `closing`, then checks `remaining`.  At least one sees the
+    // other, so no query is admitted to a launch whose workgroups have begun
+    // to leave.
+    __device__ uint32_t idle_check(BoardCtl *ctl, uint32_t polls, uint32_t remaining, uint32_t naps, uint32_t &slot) {
+        if (polls == 1u)
+            quiet = stall = 0;
+        if (polls >= 16u && (polls & 3u))
+            return 0;
+        const bool closing = ld_coherent(&box->closing) != 0u;
+        const unsigned long long ah = ld_coherent(&box->admit_head);
+        // acquire: the host's writes of the slot's constants, s0 and
+        // admission entry precede the tail it raised
+        if (!closing && ah < __hip_atomic_load(&box->admit_tail, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_SYSTEM)) {
+            __hip_atomic_fetch_add(&ctl->remaining, 1u, __ATOMIC_SEQ_CST, __HIP_MEMORY_SCOPE_AGENT);
+            if (__hip_atomic_load(&box->closing, __ATOMIC_SEQ_CST, __HIP_MEMORY_SCOPE_AGENT) == 0u &&
+                atomicCAS(&box->admit_head, ah, ah + 1ull) == ah) {
+                slot = ld_system(&box->admit_slot[ah % kAdmitRing]);
+                return 1;
+            }
+            atomicSub(&ctl->remaining, 1u);
+        } else if (remaining != 0u) {
+            quiet = 0;
+            // bounded: with queries unfinished, some level finishes every
+            // few milliseconds at most
+            const uint32_t b = ld_coherent(&box->beat);
+            stall = b == last_beat ? stall + (1u + naps) / 2u : 0u;   // counts time
+            last_beat = b;
+            if (stall > kStallChecks)
+                atomicCAS(&ctl->error, 0u, (uint32_t)LHS_ESTALL);
+        } else if (++quiet >= kIdleLeave || closing || ld_system(&box->stop) != 0u) {
+            // a read-modify-write even when closing is already seen set (the
+            // host may have set it): it takes part in the order the
+            // admissions see
+            __hip_atomic_exchange(&box->closing, 1u, __ATOMIC_SEQ_CST, __HIP_MEMORY_SCOPE_AGENT);
+            if (__hip_atomic_load(&ctl->remaining, __ATOMIC_SEQ_CST, __HIP_MEMORY_SCOPE_AGENT) == 0u)
+                return 2;
+        }
+        return 0;
+    }
+
+    // Slot i's query: progress and level 0, s0 inserted into its (emptied)
+    // table and listed as the first frontier (block-wide).
+    __device__ void admit(const ModelState &M, BoardModel &B, uint32_t i) {
+        __shared__ uint32_t row[32];
+        const uint32_t tid = threadIdx.x;
+        if (tid < M.m.W)
+            row[tid] = ld_system(roots + 32u * i + tid);
+        __syncthreads();
+        if (tid < 64) {
+            LaneCounters cnt;
+            const LdsRowB v{row};
+            const bool active = tid == 0;
+            uint32_t slot = kNoSlot, code = kFull;
+            const uint64_t h = hash_vec(v, M.m.W, M.t.seed);
+            find_or_put<1, LS, LdsRowB, true>(M.t, v, h, active, slot, code, cnt);
+            if (active) {
+                st_coherent(M.fr[0], slot);
+                st_coherent(&B.total, 1ull);
+                st_coherent(&B.edges, 0ull);
+                st_coherent(&B.deadlocks, 0ull);
+                st_coherent(&B.cur, 0u);
+                st_coherent(&B.n_levels, 1u);
+                st_coherent(&B.lc.n_next, 0u);
+                st_coherent(&B.lc.abort, 0u);
+                st_coherent(&B.lc.edges, 0ull);
+                st_coherent(&B.lc.deadlocks, 0ull);
+                st_coherent(&B.tiles_done, 0u);
+                st_coherent(&B.key, M.m.key);
+                st_system(M.levels, 1ull);
+            }
+            wait_vm_complete();
+        }
+        __syncthreads();
+    }
+
+    __device__ void level(const ModelState &M, uint32_t k, uint32_t n) {
+        st_system(M.levels + k, (unsigned long long)n);
+    }
+    __device__ void beat() { atomicAdd(&box->beat, 1u); }
+
+    // Post the finished query's completion record (one thread).
+    template <class Own>
+    __device__ void finished(uint32_t slot, const Own &own, uint32_t err, uint32_t capped, uint32_t overflow,
+                             unsigned long long waits) {
+        const unsigned long long pos = atomicAdd(&box->done_tail, 1ull);
+        DoneRec *r = done + (pos % kDoneRing);
+        st_system(&r->slot, slot);
+        st_system(&r->error, err);
+        st_system(&r->n_levels, own.n_levels);
+        st_system(&r->capped, capped);
+        st_system(&r->overflow, overflow);
+        st_system(&r->total, own.total);
+        st_system(&r->edges, own.edges);
+        st_system(&r->deadlocks, own.deadlocks);
+        st_system(&r->wait_hits, waits);
+        __hip_atomic_store(&r->seq, pos + 1ull, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+        beat();
+    }
+};
 
 template <int G, uint32_t LS, class R>
-__global__ __launch_bounds__(kExpandBlock, LS == 8 ? 4 : 1) void k_serve(const ModelState *ms, ModelProgress *mp, LevelState *lv,
-                                                        QueueState *qs, QCell *ring, ServeBox *box, DoneRec *done,
-                                                        const uint32_t *roots, uint32_t tcap) {
+__global__ __launch_bounds__(kExpandBlock, LS == 8 ? 4 : 1) void k_serve(const ModelState *ms, BoardModel *bm,
+                                                                        unsigned long long *tickets, BoardCtl *ctl,
+                                                                        ServeBox *box, DoneRec *done,
+                                                                        const uint32_t *roots, uint32_t n_slots,
+                                                                        uint32_t tcap) {
     extern __shared__ uint32_t smem[];
-    __shared__ ModelState s_M;               // constants of slot s_M_slot's query
-    __shared__ uint32_t s_act, s_slot, s_tile, s_fin, s_M_slot;
-    enum : uint32_t { kNone = 0, kTile = 1, kAdmit = 2, kLeave = 3 };
-    const uint32_t tid = threadIdx.x;
-    expand_begin();
-    if (tid == 0)
+    __shared__ ModelState s_M;
+    __shared__ uint32_t s_M_slot;
+    if (threadIdx.x == 0)
         s_M_slot = 0xFFFFFFFFu;
-    bool kept = false;       // tile 0 of kept_slot's new level is this workgroup's
-    uint32_t kept_slot = 0;
-    // thread 0: the queue position this workgroup holds (taken with one
-    // fetch-and-add, so workgroups never contend for an item), polls without
-    // work, and idle polls without a beat
-    bool holding = false;
-    unsigned long long pos = 0;
-    uint32_t idle = 0, quiet = 0, stall = 0, last_beat = 0;
-    while (true) {
-        __syncthreads();     // the last decision has been read by every thread
+    __syncthreads();
+    ServeDriver<LS> drv{box, done, roots, &s_M, &s_M_slot};
+    board_run<G, LS, R>(drv, smem, ms, bm, tickets, ctl, n_slots, tcap);
+}
+
+// Before a launch: admissions reopen.
+__global__ void k_serve_reopen(ServeBox *box) { box->closing = 0; }
+
+// A query to ready: its slot, its transitions (at trans_at of the staged
+// ones), its emptied table.
+struct PostEntry {
+    ModelState ms;
+    TableZero zero;
+    uint2 *trans;
+    uint32_t trans_at, n_trans, slot, pad;
+    uint32_t root[32];
+};
+
+// Ready n queries from one upload: blockIdx.y = query.  Their constants, s0
+// and transitions go to their places, their tables are emptied, and their
+// slots appended to the admission ring from position `posted` on (the tail is
+// raised by the host once this launch has completed).
+__global__ __launch_bounds__(256) void k_serve_post(const PostEntry *entries, const uint2 *trans, ModelState *ms,
+                                                    uint32_t *roots, ServeBox *box, BoardCtl *ctl,
+                                                    unsigned long long posted) {
+    const PostEntry &e = entries[blockIdx.y];
+    const uint32_t tid = threadIdx.x;
+    if (blockIdx.x == 0) {
+        static_assert(sizeof(ModelState) % 4 == 0, "copied by words");
+        const uint32_t *src = reinterpret_cast<const uint32_t *>(&e.ms);
+        uint32_t *dst = reinterpret_cast<uint32_t *>(ms + e.slot);
+        for (uint32_t k = tid; k < sizeof(ModelState) / 4; k += blockDim.x)
+            dst[k] = src[k];
+        if (tid < 32)
+            roots[32u * e.slot + tid] = e.root[tid];
+        for (uint32_t k = tid; k < e.n_trans; k += blockDim.x)
+            e.trans[k] = trans[e.trans_at + k];
         if (tid == 0) {
-            uint32_t act = kNone, slot = 0, tile = 0;
-            if (queue_failed(qs)) {
-                act = kLeave;
-            } else if (kept) {
-                act = kTile;
-                slot = kept_slot;
-            } else {
-                if (!holding) {
-                    pos = atomicAdd(&qs->head, 1ull);
-                    holding = true;
-                }
-                QCell *c = ring + (pos & qs->mask);
-                if (ld_coherent(&c->seq) == pos + 1ull) {
-                    slot = ld_coherent(&c->model);
-                    tile = ld_coherent(&c->tile);
-                    wait_vm_complete();   // read before the cell is freed
-                    st_coherent(&c->seq, pos + qs->mask + 1ull);
-                    holding = false;
-                    act = kTile;
-                } else if (idle < 16 || (idle & 3u) == 0) {
-                    // nothing at the held position yet: admissions, or leave
-                    // once idle.  Leaving and admitting race, so each side
-                    // announces itself before it looks at the other (both
-                    // sequentially consistent): an admission counts itself in
-                    // `remaining`, then checks `closing`; a workgroup about to
-                    // leave sets `closing`, then checks `remaining`.  At
-                    // least one sees the other, so no query is admitted to a
-                    // launch whose workgroups have begun to leave.
-                    const bool closing = ld_coherent(&box->closing) != 0u;
-                    const unsigned long long ah = ld_coherent(&box->admit_head);
-                    // acquire: the host's copies of the slot's constants,
-                    // s0 and admission entry precede the tail it raised
-                    if (!closing && ah < __hip_atomic_load(&box->admit_tail, __ATOMIC_ACQUIRE,
-                                                           __HIP_MEMORY_SCOPE_SYSTEM)) {
-                        __hip_atomic_fetch_add(&qs->remaining, 1u, __ATOMIC_SEQ_CST, __HIP_MEMORY_SCOPE_AGENT);
-                        if (__hip_atomic_load(&box->closing, __ATOMIC_SEQ_CST, __HIP_MEMORY_SCOPE_AGENT) == 0u &&
-                            atomicCAS(&box->admit_head, ah, ah + 1ull) == ah) {
-                            slot = ld_system(&box->admit_slot[ah % kAdmitRing]);
-                            act = kAdmit;
-                        } else {
-                            atomicSub(&qs->remaining, 1u);
-                        }
-                    } else if (ld_coherent(&qs->remaining) != 0u) {
-                        quiet = 0;
-                    } else if (++quiet >= kIdleLeave || closing || ld_system(&box->stop) != 0u) {
-                        // a read-modify-write even when closing is already
-                        // seen set (the host may have set it): it takes part
-                        // in the order the admissions see
-                        __hip_atomic_exchange(&box->closing, 1u, __ATOMIC_SEQ_CST, __HIP_MEMORY_SCOPE_AGENT);
-                        // the held position is never filled: no query is
-                        // left, and none can be admitted any more
-                        if (__hip_atomic_load(&qs->remaining, __ATOMIC_SEQ_CST, __HIP_MEMORY_SCOPE_AGENT) == 0u)
-                            act = kLeave;
-                    }
-                }
-                if (act == kNone) {
-                    // bounded: with queries unfinished, some level
-                    // finishes every few milliseconds at most
-                    const uint32_t b = ld_coherent(&box->beat);
-                    stall = b == last_beat ? stall + 1u : 0u;
-                    last_beat = b;
-                    if (stall > kStallPolls) {
-                        atomicCAS(&qs->error, 0u, (uint32_t)LHS_ESTALL);
-                        act = kLeave;
-                    }
-                    ++idle;
-                    for (uint32_t k = 0; k < min(idle, kIdleSleepMax); ++k)
-                        __builtin_amdgcn_s_sleep(16);
-                }
-            }
-            if (act == kTile || act == kAdmit) {
-                idle = 0;
-                stall = 0;
-            }
-            s_act = act;
-            s_slot = slot;
-            s_tile = tile;
+            box->admit_slot[(posted + blockIdx.y) % kAdmitRing] = e.slot;
+            atomicMax(&ctl->slots, e.slot + 1u);
         }
-        __syncthreads();
-        const uint32_t act = s_act, i = s_slot, j = s_tile;
-        if (act == kLeave)
-            break;
-        if (act == kNone)
-            continue;
-        if (act == kAdmit) {
-            load_model_state(&s_M, ms + i);
-            if (tid == 0)
-                s_M_slot = i;
-            admit_query<LS>(s_M, mp, lv, i, roots);
-            // Tile 0 of the new query goes to the work queue like any other
-            // tile.  This workgroup still holds the queue position it
-            // reserved before admitting: were it to keep tiles for itself
-            // now, the item that lands in that position would wait for its
-            // whole chain of levels, and once the ring wrapped onto that
-            // cell every producer would wait for it too (LHS_ESTALL).
-            if (tid == 0)
-                enqueue_item(qs, ring, i, 0u);
-            continue;
-        }
-        kept = false;
-        LevelState &L = lv[i];
-        // the constants are read again only when the slot holds another query
-        if (s_M_slot != i || s_M.m.key != ld_coherent(&L.key)) {
-            __syncthreads();   // every thread has compared before s_M changes
-            load_model_state(&s_M, ms + i);
-            if (tid == 0)
-                s_M_slot = i;
-        }
-        const uint32_t *front = reinterpret_cast<const uint32_t *>(ld_coherent(&L.front));
-        uint32_t *next = reinterpret_cast<uint32_t *>(ld_coherent(&L.next));
-        const uint32_t n_front = ld_coherent(&L.n_front);
-        const uint32_t limit = ld_coherent(&L.limit);
-        const uint32_t rows_per = ld_coherent(&L.tile_rows);
-        const uint64_t base = (uint64_t)j * rows_per;
-        const uint32_t rows = (uint32_t)min<uint64_t>(rows_per, n_front - base);
-        expand_tile<G, LS, R, true, false, false, false, true>(smem, s_M.t, s_M.m, front, base, rows, next, s_M.lc,
-                                                               limit, tcap);
-        wait_vm_complete();
-        __syncthreads();
-        if (tid == 0) {
-            const uint32_t total = ld_coherent(&L.tiles_total);
-            wait_vm_complete();
-            s_fin = atomicAdd(&L.tiles_done, 1u) + 1u == total;
-            // progress for the idle workgroups' stall bound: one per level
-            // (a level, even a query's deepest chain of one-tile levels,
-            // ends well within the bound), not one per tile on a shared
-            // address
-            if (s_fin)
-                atomicAdd(&box->beat, 1u);
-        }
-        __syncthreads();
-        if (s_fin && finalize_level<true>(s_M, mp, lv, i, qs, ring, ServeDone{box, done, mp})) {
-            kept = true;
-            kept_slot = i;
-        }
+        zero_status(e.zero.status);
     }
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    u32x4 *q = reinterpret_cast<u32x4 *>(e.zero.bucket);
+    const u32x4 z = {0u, 0u, 0u, 0u};
+    for (unsigned long long k = (unsigned long long)blockIdx.x * blockDim.x + tid; k < e.zero.chunks;
+         k += (unsigned long long)gridDim.x * blockDim.x)
+        __builtin_nontemporal_store(z, q + k);
 }
 
-// Before a launch: positions taken by the workgroups of the last launch and
-// never filled are given back (every filled one was consumed: no query was
-// left), and admissions reopen.
-__global__ void k_serve_reopen(QueueState *qs, ServeBox *box) {
-    qs->head = qs->tail;
-    box->closing = 0;
-}
-
-// Work queue empty, every cell free, admission and completion counters at
-// the host's positions.
-__global__ void k_serve_init(QCell *ring, unsigned long long cells, QueueState *qs, ServeBox *box,
+// No work, admission and completion counters at the host's positions.
+__global__ void k_serve_init(unsigned long long *tickets, BoardModel *bm, uint32_t n, BoardCtl *ctl, ServeBox *box,
                              unsigned long long posted, unsigned long long done_head) {
-    for (unsigned long long p = (unsigned long long)blockIdx.x * blockDim.x + threadIdx.x; p < cells;
-         p += (unsigned long long)gridDim.x * blockDim.x) {
-        ring[p].seq = p;
-        ring[p].model = 0;
-        ring[p].tile = 0;
+    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
+        tickets[i] = 0;
+        bm[i] = BoardModel{};
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
-        qs->head = 0;
-        qs->tail = 0;
-        qs->remaining = 0;
-        qs->error = 0;
-        qs->mask = cells - 1;
+        ctl->remaining = 0;
+        ctl->error = 0;
+        ctl->idle = 0;
+        ctl->slots = 0;
         box->admit_tail = posted;
         box->admit_head = posted;
         box->done_tail = done_head;
@@ -540,15 +500,8 @@ struct Query {
     lhs_status status = LHS_OK;
     bool done = false;
     uint32_t slot = 0xFFFFFFFFu;   // persistent server: its slot while on the GPU
-    uint64_t tiles_bound = 0;      // bound on its items in the work queue
     bool bytes_rows = false;       // every word of its states fits a byte
 };
-
-// A query's items in the work queue at once: one level's tiles, full or cut
-// small (persistent.h's level_tile_rows), plus one.
-uint64_t queue_bound(const Query *q) {
-    return std::max<uint64_t>(q->capacity / kExpandBlock, kSmallLevel / kMinTileRows) + 1;
-}
 
 // Worker-owned state of the persistent server.
 struct Persist {
@@ -559,27 +512,26 @@ struct Persist {
     bool launch_bytes = false;         // ... in rows of bytes
     uint64_t launches = 0;
     ModelState *d_ms = nullptr;
-    ModelProgress *d_mp = nullptr;
-    LevelState *d_lv = nullptr;
-    LevelCounters *d_lc = nullptr;
-    QueueState *d_qs = nullptr;
-    QCell *d_ring = nullptr;
+    BoardModel *d_bm = nullptr;
+    unsigned long long *d_tickets = nullptr;
+    BoardCtl *d_ctl = nullptr;
     ServeBox *d_box = nullptr;
     uint32_t *d_roots = nullptr;                  // [slot][32]
-    std::vector<unsigned long long *> d_levels;   // [slot] -> level counts, on first use
+    // [slot] -> level counts in pinned memory (written by the device), on
+    // first use, and their device addresses
+    std::vector<unsigned long long *> h_levels, h_levels_dev;
+    void *d_stage = nullptr;                      // device copy of the admissions' staging
+    size_t cap_d_stage = 0;
     DoneRec *h_done = nullptr;                    // pinned; written by the device
     DoneRec *h_done_dev = nullptr;                // ... its device address
-    ModelProgress *h_prog = nullptr;              // pinned read-backs
-    unsigned long long *h_lv = nullptr;
-    DevStatus *h_tst = nullptr;
-    QueueState *h_qs = nullptr;
+    BoardCtl *h_ctl = nullptr;                    // pinned read-back
     uint32_t *h_word = nullptr;                   // pinned {0, 1}: box flag values
     bool stop_sent = false;
     bool close_sent = false;                      // the running launch was asked to drain
     std::vector<Query *> slot_q;                  // query in each slot
     std::vector<uint32_t> free_slots;
     uint32_t live = 0;                            // posted and not yet completed
-    uint64_t posted = 0, done_head = 0, outstanding = 0;
+    uint64_t posted = 0, done_head = 0;
 };
 
 uint64_t table_bytes(uint64_t capacity, uint32_t W) {
@@ -703,7 +655,10 @@ bool acquire_table(reach_server *s, Query *q) {
     if (s->bytes_alloc + q->bytes > s->opts.budget_bytes)
         return false;
     lhs_table *t = nullptr;
-    if (lhs_create_ex(q->capacity, q->W, &s->cfg, &t) != LHS_OK || ensure_bfs_buffers(t) != LHS_OK) {
+    // not lhs_create_ex: its clear waits on the null stream for the running
+    // launch to end (18 ms a time), and every query's table is emptied before
+    // its use
+    if (alloc_table(q->capacity, q->W, &s->cfg, &t) != LHS_OK || ensure_bfs_buffers(t) != LHS_OK) {
         lhs_destroy(t);
         return false;
     }
@@ -933,8 +888,8 @@ lhs_status step_queries(reach_server *s, std::vector<Query *> &finished) {
 // ---- persistent server: host side (worker thread) -------------------------
 lhs_status persist_reset(reach_server *s) {
     Persist &P = s->ps;
-    hipLaunchKernelGGL(k_serve_init, dim3(4096), dim3(256), 0, P.up, P.d_ring, (unsigned long long)kServeCells,
-                       P.d_qs, P.d_box, (unsigned long long)P.posted, (unsigned long long)P.done_head);
+    hipLaunchKernelGGL(k_serve_init, dim3(16), dim3(256), 0, P.up, P.d_tickets, P.d_bm, s->opts.max_active, P.d_ctl,
+                       P.d_box, (unsigned long long)P.posted, (unsigned long long)P.done_head);
     if (hipGetLastError() != hipSuccess || hipStreamSynchronize(P.up) != hipSuccess)
         return LHS_EDEVICE;
     return LHS_OK;
@@ -947,18 +902,13 @@ lhs_status persist_init(reach_server *s) {
         hipEventCreateWithFlags(&P.ev_end, hipEventDisableTiming) != hipSuccess)
         return LHS_EDEVICE;
     if (hipMalloc(&P.d_ms, n * sizeof(ModelState)) != hipSuccess ||
-        hipMalloc(&P.d_mp, n * sizeof(ModelProgress)) != hipSuccess ||
-        hipMalloc(&P.d_lv, n * sizeof(LevelState)) != hipSuccess ||
-        hipMalloc(&P.d_lc, n * sizeof(LevelCounters)) != hipSuccess ||
-        hipMalloc(&P.d_qs, sizeof(QueueState)) != hipSuccess ||
-        hipMalloc(&P.d_ring, kServeCells * sizeof(QCell)) != hipSuccess ||
+        hipMalloc(&P.d_bm, n * sizeof(BoardModel)) != hipSuccess ||
+        hipMalloc(&P.d_tickets, n * sizeof(unsigned long long)) != hipSuccess ||
+        hipMalloc(&P.d_ctl, sizeof(BoardCtl)) != hipSuccess ||
         hipMalloc(&P.d_box, sizeof(ServeBox)) != hipSuccess ||
         hipMalloc(&P.d_roots, (size_t)n * 32 * sizeof(uint32_t)) != hipSuccess ||
         hipHostMalloc(&P.h_done, kDoneRing * sizeof(DoneRec), hipHostMallocCoherent) != hipSuccess ||
-        hipHostMalloc(&P.h_prog, sizeof(ModelProgress), hipHostMallocDefault) != hipSuccess ||
-        hipHostMalloc(&P.h_lv, kServeMaxLevels * sizeof(unsigned long long), hipHostMallocDefault) != hipSuccess ||
-        hipHostMalloc(&P.h_tst, sizeof(DevStatus), hipHostMallocDefault) != hipSuccess ||
-        hipHostMalloc(&P.h_qs, sizeof(QueueState), hipHostMallocDefault) != hipSuccess ||
+        hipHostMalloc(&P.h_ctl, sizeof(BoardCtl), hipHostMallocDefault) != hipSuccess ||
         hipHostMalloc(&P.h_word, 2 * sizeof(uint32_t), hipHostMallocDefault) != hipSuccess) {
         (void)hipGetLastError();
         return LHS_ENOMEM;
@@ -971,7 +921,8 @@ lhs_status persist_init(reach_server *s) {
         return LHS_EDEVICE;
     P.h_done_dev = static_cast<DoneRec *>(dev);
     P.slot_q.assign(n, nullptr);
-    P.d_levels.assign(n, nullptr);
+    P.h_levels.assign(n, nullptr);
+    P.h_levels_dev.assign(n, nullptr);
     for (uint32_t i = n; i-- > 0;)
         P.free_slots.push_back(i);
     return persist_reset(s);
@@ -980,16 +931,16 @@ lhs_status persist_init(reach_server *s) {
 void persist_free(reach_server *s) {
     Persist &P = s->ps;
     (void)hipFree(P.d_ms);
-    (void)hipFree(P.d_mp);
-    (void)hipFree(P.d_lv);
-    (void)hipFree(P.d_lc);
-    (void)hipFree(P.d_qs);
-    (void)hipFree(P.d_ring);
+    (void)hipFree(P.d_bm);
+    (void)hipFree(P.d_tickets);
+    (void)hipFree(P.d_ctl);
+    (void)hipFree(P.d_stage);
     (void)hipFree(P.d_box);
     (void)hipFree(P.d_roots);
-    for (auto p : P.d_levels)
-        (void)hipFree(p);
-    for (void *h : {(void *)P.h_done, (void *)P.h_prog, (void *)P.h_lv, (void *)P.h_tst, (void *)P.h_qs, (void *)P.h_word})
+    for (auto p : P.h_levels)
+        if (p)
+            (void)hipHostFree(p);
+    for (void *h : {(void *)P.h_done, (void *)P.h_ctl, (void *)P.h_word})
         if (h)
             (void)hipHostFree(h);
     if (P.ev_end)
@@ -999,26 +950,28 @@ void persist_free(reach_server *s) {
 }
 
 // Ready the slots of newly admitted queries and post them to the running
-// (or next) launch: transitions uploaded, tables emptied, each slot's
-// constants and s0 written, then the admission entries, then the tail.
+// (or next) launch: one upload of everything they need and one kernel that
+// puts it in place and empties their tables, then the tail.
 lhs_status persist_post(reach_server *s, const std::vector<Query *> &qs) {
     Persist &P = s->ps;
     if (qs.empty())
         return LHS_OK;
     const uint32_t n = (uint32_t)qs.size();
-    Carve c;
-    const size_t o_ms = c.take<ModelState>(n), o_roots = c.take<uint32_t>((size_t)n * 32),
-                 o_adm = c.take<uint32_t>(n), o_tail = c.take<unsigned long long>(1);
     size_t n_trans = 0;
     for (Query *q : qs)
         n_trans += (size_t)q->m.n_procs * q->m.n_locals * q->m.trans_per_local;
-    const size_t o_trans = c.take<uint2>(n_trans);
-    if (c.off > s->cap_stage) {
+    Carve c;
+    const size_t o_post = c.take<PostEntry>(n), o_trans = c.take<uint2>(n_trans), upload = c.off,
+                 o_tail = c.take<unsigned long long>(1);
+    if (c.off > s->cap_stage || c.off > P.cap_d_stage) {
         if (s->h_stage)
             (void)hipHostFree(s->h_stage);
+        (void)hipFree(P.d_stage);
         s->h_stage = nullptr;
         s->cap_stage = 0;
-        size_t cap = 1 << 20;
+        P.d_stage = nullptr;
+        P.cap_d_stage = 0;
+        size_t cap = 1 << 22;
         while (cap < c.off)
             cap <<= 1;
         if (hipHostMalloc(&s->h_stage, cap, hipHostMallocDefault) != hipSuccess) {
@@ -1027,12 +980,17 @@ lhs_status persist_post(reach_server *s, const std::vector<Query *> &qs) {
             return LHS_ENOMEM;
         }
         s->cap_stage = cap;
+        if (hipMalloc(&P.d_stage, cap) != hipSuccess) {
+            (void)hipGetLastError();
+            P.d_stage = nullptr;
+            return LHS_ENOMEM;
+        }
+        P.cap_d_stage = cap;
     }
-    ModelState *ms = at<ModelState>(s->h_stage, o_ms);
-    uint32_t *roots = at<uint32_t>(s->h_stage, o_roots), *adm = at<uint32_t>(s->h_stage, o_adm);
+    PostEntry *post = at<PostEntry>(s->h_stage, o_post);
     uint2 *trans = at<uint2>(s->h_stage, o_trans);
-    std::memset(roots, 0, (size_t)n * 32 * sizeof(uint32_t));
     size_t t_at = 0;
+    uint64_t max_chunks = 1;
     std::vector<uint2> packed;
     for (uint32_t k = 0; k < n; ++k) {
         Query *q = qs[k];
@@ -1041,12 +999,18 @@ lhs_status persist_post(reach_server *s, const std::vector<Query *> &qs) {
         P.slot_q[slot] = q;
         q->slot = slot;
         ++P.live;
-        P.outstanding += q->tiles_bound;
-        if (!P.d_levels[slot] &&
-            hipMalloc(&P.d_levels[slot], kServeMaxLevels * sizeof(unsigned long long)) != hipSuccess) {
-            (void)hipGetLastError();
-            P.d_levels[slot] = nullptr;
-            return LHS_ENOMEM;
+        if (!P.h_levels[slot]) {
+            void *dev = nullptr;
+            if (hipHostMalloc(&P.h_levels[slot], kServeMaxLevels * sizeof(unsigned long long),
+                              hipHostMallocCoherent) != hipSuccess ||
+                hipHostGetDevicePointer(&dev, P.h_levels[slot], 0) != hipSuccess) {
+                (void)hipGetLastError();
+                if (P.h_levels[slot])
+                    (void)hipHostFree(P.h_levels[slot]);
+                P.h_levels[slot] = nullptr;
+                return LHS_ENOMEM;
+            }
+            P.h_levels_dev[slot] = static_cast<unsigned long long *>(dev);
         }
         pack_model(&q->m, packed);
         const size_t bytes = packed.size() * sizeof(uint2);
@@ -1060,30 +1024,34 @@ lhs_status persist_post(reach_server *s, const std::vector<Query *> &qs) {
             return LHS_ENOMEM;
         }
         std::memcpy(trans + t_at, packed.data(), bytes);
-        LHS_HIP(hipMemcpyAsync(q->d_trans, trans + t_at, bytes, hipMemcpyHostToDevice, P.up));
-        t_at += packed.size();
         q->t->last_stream = P.up;
-        if (lhs_clear(q->t, P.up) != LHS_OK)
-            return LHS_EDEVICE;
-        ModelState &M = ms[k];
-        std::memset(&M, 0, sizeof(M));
-        M.t = view(q->t);
-        M.m = model_view(&q->m, q->d_trans);
-        M.m.key = q->ticket;   // unique and nonzero: a later query may reuse this transition buffer
-        M.lc = P.d_lc + slot;
-        M.fr[0] = q->t->frontier[0];
-        M.fr[1] = q->t->frontier[1];
-        M.levels = P.d_levels[slot];
-        M.cap = q->m.state_cap;
-        M.max_levels = kServeMaxLevels;
-        std::memcpy(roots + 32 * k, q->init.data(), q->W * sizeof(uint32_t));
-        adm[k] = slot;
-        LHS_HIP(hipMemcpyAsync(P.d_ms + slot, &M, sizeof(M), hipMemcpyHostToDevice, P.up));
-        LHS_HIP(hipMemcpyAsync(P.d_roots + 32 * slot, roots + 32 * k, 32 * sizeof(uint32_t), hipMemcpyHostToDevice,
-                               P.up));
-        LHS_HIP(hipMemcpyAsync(&P.d_box->admit_slot[(P.posted + k) % kAdmitRing], adm + k, sizeof(uint32_t),
-                               hipMemcpyHostToDevice, P.up));
+        q->t->has_parents = false;
+        PostEntry &e = post[k];
+        std::memset(static_cast<void *>(&e), 0, sizeof(e));
+        e.ms.t = view(q->t);
+        e.ms.m = model_view(&q->m, q->d_trans);
+        e.ms.m.key = q->ticket;   // unique and nonzero: a later query may reuse this transition buffer
+        e.ms.fr[0] = q->t->frontier[0];
+        e.ms.fr[1] = q->t->frontier[1];
+        e.ms.levels = P.h_levels_dev[slot];
+        e.ms.cap = q->m.state_cap;
+        e.ms.max_levels = kServeMaxLevels;
+        e.zero = TableZero{reinterpret_cast<uint4 *>(q->t->bucket), q->t->capacity / 2,
+                           reinterpret_cast<TableStatus *>(q->t->status)};
+        e.trans = q->d_trans;
+        e.trans_at = (uint32_t)t_at;
+        e.n_trans = (uint32_t)packed.size();
+        e.slot = slot;
+        std::memcpy(e.root, q->init.data(), q->W * sizeof(uint32_t));
+        t_at += packed.size();
+        max_chunks = std::max<uint64_t>(max_chunks, q->t->capacity / 2);
     }
+    LHS_HIP(hipMemcpyAsync(P.d_stage, s->h_stage, upload, hipMemcpyHostToDevice, P.up));
+    const uint32_t gx = (uint32_t)std::min<uint64_t>((max_chunks + 1023) / 1024, std::max<uint32_t>(64, 2048 / n));
+    hipLaunchKernelGGL(k_serve_post, dim3(gx, n), dim3(256), 0, P.up, (const PostEntry *)at<PostEntry>(P.d_stage, o_post),
+                       (const uint2 *)at<uint2>(P.d_stage, o_trans), P.d_ms, P.d_roots, P.d_box, P.d_ctl,
+                       (unsigned long long)P.posted);
+    LHS_HIP(hipGetLastError());
     // the tail last: a workgroup that sees it finds every entry below it
     P.posted += n;
     *at<unsigned long long>(s->h_stage, o_tail) = P.posted;
@@ -1116,10 +1084,10 @@ lhs_status persist_launch(reach_server *s) {
             per_cu < 1)
             return LHS_EDEVICE;
         const uint32_t grid = (uint32_t)ncu * (uint32_t)std::max(1, per_cu - 1);
-        hipLaunchKernelGGL(k_serve_reopen, dim3(1), dim3(1), 0, s->stream, P.d_qs, P.d_box);
+        hipLaunchKernelGGL(k_serve_reopen, dim3(1), dim3(1), 0, s->stream, P.d_box);
         hipLaunchKernelGGL((k_serve<decltype(G)::value, decltype(L)::value, decltype(R)>), dim3(grid), dim3(kExpandBlock), lds,
-                           s->stream, (const ModelState *)P.d_ms, P.d_mp, P.d_lv, P.d_qs, P.d_ring, P.d_box,
-                           P.h_done_dev, (const uint32_t *)P.d_roots, tcap);
+                           s->stream, (const ModelState *)P.d_ms, P.d_bm, P.d_tickets, P.d_ctl, P.d_box,
+                           P.h_done_dev, (const uint32_t *)P.d_roots, s->opts.max_active, tcap);
         return hipGetLastError() == hipSuccess ? LHS_OK : LHS_EDEVICE;
     });
     if (rc != LHS_OK)
@@ -1145,23 +1113,16 @@ lhs_status persist_collect(reach_server *s, std::vector<Query *> &finished) {
         if (slot >= P.slot_q.size() || !P.slot_q[slot])
             return LHS_EDEVICE;
         Query *q = P.slot_q[slot];
-        LHS_HIP(hipMemcpyAsync(P.h_prog, P.d_mp + slot, sizeof(ModelProgress), hipMemcpyDeviceToHost, P.up));
-        LHS_HIP(hipMemcpyAsync(P.h_lv, P.d_levels[slot], nl * sizeof(unsigned long long), hipMemcpyDeviceToHost,
-                               P.up));
-        LHS_HIP(hipMemcpyAsync(P.h_tst, q->t->status, sizeof(DevStatus), hipMemcpyDeviceToHost, P.up));
-        LHS_HIP(hipStreamSynchronize(P.up));
-        const ModelProgress &M = *P.h_prog;
-        q->levels.assign(P.h_lv, P.h_lv + nl);
-        q->total = M.total;
-        q->edges = M.edges;
-        q->dead = M.deadlocks;
-        q->capped = (int)M.capped;
-        q->wait_hits = P.h_tst->wait_hits;
-        q->status = err ? (lhs_status)err : (M.overflow ? LHS_EINVAL : LHS_OK);
+        q->levels.assign(P.h_levels[slot], P.h_levels[slot] + nl);
+        q->total = r.total;
+        q->edges = r.edges;
+        q->dead = r.deadlocks;
+        q->capped = (int)r.capped;
+        q->wait_hits = r.wait_hits;
+        q->status = err ? (lhs_status)err : (r.overflow ? LHS_EINVAL : LHS_OK);
         P.slot_q[slot] = nullptr;
         P.free_slots.push_back(slot);
         --P.live;
-        P.outstanding -= q->tiles_bound;
         q->slot = 0xFFFFFFFFu;
         finished.push_back(q);
     }
@@ -1176,11 +1137,11 @@ lhs_status persist_after_launch(reach_server *s, std::vector<Query *> &finished)
     lhs_status rc = persist_collect(s, finished);
     if (rc != LHS_OK)
         return rc;
-    LHS_HIP(hipMemcpyAsync(P.h_qs, P.d_qs, sizeof(QueueState), hipMemcpyDeviceToHost, P.up));
+    LHS_HIP(hipMemcpyAsync(P.h_ctl, P.d_ctl, sizeof(BoardCtl), hipMemcpyDeviceToHost, P.up));
     LHS_HIP(hipStreamSynchronize(P.up));
-    if (!P.h_qs->error)
+    if (!P.h_ctl->error)
         return LHS_OK;
-    const lhs_status err = (lhs_status)P.h_qs->error;
+    const lhs_status err = (lhs_status)P.h_ctl->error;
     for (uint32_t i = 0; i < P.slot_q.size(); ++i)
         if (Query *q = P.slot_q[i]) {
             q->status = err;
@@ -1189,7 +1150,6 @@ lhs_status persist_after_launch(reach_server *s, std::vector<Query *> &finished)
             finished.push_back(q);
         }
     P.live = 0;
-    P.outstanding = 0;
     return persist_reset(s);
 }
 
@@ -1205,10 +1165,10 @@ void persist_worker(reach_server *s) {
                 s->cv_work.wait(lk);
             if (s->stop && s->queue.empty() && P.live == 0 && !P.running)
                 return;
-            // first come first served, while a slot, room in the work queue
-            // and the budget allow; a query wider than the running launch's
-            // LDS, or with words its rows cannot hold, waits for the next
-            // launch (and holds the queries behind it)
+            // first come first served, while a slot and the budget allow; a
+            // query wider than the running launch's LDS, or with words its
+            // rows cannot hold, waits for the next launch (and holds the
+            // queries behind it)
             bool drain = false;
             while (!s->queue.empty() && admitted.size() < P.free_slots.size()) {
                 Query *q = s->queue.front();
@@ -1216,9 +1176,6 @@ void persist_worker(reach_server *s) {
                     drain = true;
                     break;
                 }
-                q->tiles_bound = queue_bound(q);
-                if (P.outstanding + q->tiles_bound > kServeCells / 2)
-                    break;
                 if (!acquire_table(s, q)) {
                     if (P.live == 0 && admitted.empty() && s->pool.empty()) {
                         s->queue.pop_front();
@@ -1287,7 +1244,6 @@ void persist_worker(reach_server *s) {
                     finished.push_back(q);
                 }
             P.live = 0;
-            P.outstanding = 0;
             (void)persist_reset(s);
         }
         const double t1 = now_s();
@@ -1552,8 +1508,7 @@ static lhs_status reach_server_submit_impl(reach_server *s, const reach_model *m
             return LHS_EBUDGET;
     }
     q->limit = m->state_cap ? (uint32_t)std::min<uint64_t>(m->state_cap - 1, 0xFFFFFFFFull) : 0xFFFFFFFFu;
-    // the persistent work queue holds a full level of every query on the GPU
-    if (s->persistent && queue_bound(q.get()) > kServeCells / 2)
+    if (s->persistent && q->capacity >= kServeCapacity)
         return LHS_EINVAL;
     q->levels.push_back(1);
     std::lock_guard<std::mutex> lk(s->mu);
