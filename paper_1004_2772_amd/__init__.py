@@ -419,7 +419,7 @@ def _model_struct(model, cap):
 
 
 def _result(r: ReachResultC) -> ReachResult:
-    levels = [int(r.level_counts[i]) for i in range(r.n_levels)]
+    levels = r.level_counts[:r.n_levels] if r.n_levels else []
     return ReachResult(total=r.total_states, n_levels=r.n_levels, level_counts=levels,
                        edges=r.edges, deadlocks=r.deadlocks, capped=bool(r.capped),
                        wait_hits=r.wait_hits, gpu_ms=r.gpu_ms)
@@ -467,10 +467,7 @@ def reach_explore(model, cap: int | None = None, capacity: int = 0, table: Table
     r = ReachResultC()
     _check(lib().reach_explore(ctypes.byref(m), ctypes.byref(o), ctypes.byref(r)), "reach_explore")
     try:
-        levels = [int(r.level_counts[i]) for i in range(r.n_levels)]
-        return ReachResult(total=r.total_states, n_levels=r.n_levels, level_counts=levels,
-                           edges=r.edges, deadlocks=r.deadlocks, capped=bool(r.capped),
-                           wait_hits=r.wait_hits, gpu_ms=r.gpu_ms)
+        return _result(r)
     finally:
         lib().reach_result_free(ctypes.byref(r))
         del keep
@@ -493,7 +490,7 @@ def reach_explore_noalloc(model, table: Table, cap: int | None = None, max_level
                                        ctypes.byref(r), _stream_handle(stream)), "reach_explore_noalloc")
     del keep
     return ReachResult(total=r.total_states, n_levels=r.n_levels,
-                       level_counts=[int(x) for x in levels[: r.n_levels]], edges=r.edges,
+                       level_counts=levels[: r.n_levels].tolist(), edges=r.edges,
                        deadlocks=r.deadlocks, capped=bool(r.capped), wait_hits=r.wait_hits, gpu_ms=r.gpu_ms)
 
 

@@ -92,10 +92,9 @@ struct BatchModel {
 
 namespace lhs {
 
-lhs_status explore_levels(lhs_table *t, const TableView &tv, const ModelView &mv, bool bytes, uint64_t cap,
-                          LevelsArea *d, LevelsArea *h, hipStream_t s, LevelsRun &run) {
-    const size_t head = offsetof(LevelsArea, levels);
-    std::memset(static_cast<void *>(h), 0, head);
+void levels_area(LevelsArea *h, const LevelsArea *d, lhs_table *t, const TableView &tv, const ModelView &mv,
+                 uint64_t cap, const LevelsRun &run) {
+    std::memset(static_cast<void *>(h), 0, offsetof(LevelsArea, levels));
     h->ctl.remaining = 1;
     h->tickets[0] = make_ticket((run.n_front + kExpandBlock - 1) / kExpandBlock, run.cur, kExpandBlock, 0);
     ModelState &M = h->ms;
@@ -103,7 +102,7 @@ lhs_status explore_levels(lhs_table *t, const TableView &tv, const ModelView &mv
     M.m = mv;
     M.fr[0] = t->frontier[0];
     M.fr[1] = t->frontier[1];
-    M.levels = d->levels;
+    M.levels = const_cast<unsigned long long *>(d->levels);
     M.cap = cap;
     M.max_levels = kBoardLevels;
     M.handover = kBoardHandover;
@@ -113,7 +112,15 @@ lhs_status explore_levels(lhs_table *t, const TableView &tv, const ModelView &mv
     B.cur = run.cur;
     B.n_levels = 1;
     B.total = run.total;
-    LHS_HIP(hipMemcpyAsync(d, h, head, hipMemcpyHostToDevice, s));
+}
+
+lhs_status explore_levels(lhs_table *t, const TableView &tv, const ModelView &mv, bool bytes, uint64_t cap,
+                          LevelsArea *d, LevelsArea *h, hipStream_t s, LevelsRun &run,
+                          const std::function<lhs_status()> &before_sync) {
+    if (!run.uploaded) {
+        levels_area(h, d, t, tv, mv, cap, run);
+        LHS_HIP(hipMemcpyAsync(d, h, offsetof(LevelsArea, levels), hipMemcpyHostToDevice, s));
+    }
     const uint32_t tps = tps_expand(t);
     const uint32_t tcap = trans_lds_entries(mv.P, mv.L, mv.K);
     const size_t lds = expand_lds_bytes(mv.W, tcap, tps, bytes);
@@ -131,7 +138,10 @@ lhs_status explore_levels(lhs_table *t, const TableView &tv, const ModelView &mv
     if (rc != LHS_OK)
         return rc;
     LHS_HIP(hipMemcpyAsync(h, d, sizeof(LevelsArea), hipMemcpyDeviceToHost, s));
+    if ((rc = before_sync()) != LHS_OK)
+        return rc;
     LHS_HIP(hipStreamSynchronize(s));
+    const BoardModel &B = h->bm;
     if (h->ctl.error)
         return (lhs_status)h->ctl.error;
     if (B.status_error)

@@ -204,6 +204,8 @@ inline uint32_t div_magic(uint32_t W) {
 lhs_status launch_find_or_put(lhs_table *t, const uint32_t *d_states, uint64_t n,
                               uint8_t *d_seen, uint32_t *d_index, hipStream_t s);
 lhs_status launch_zero_u64(uint64_t *p, uint64_t n, hipStream_t s);
+// A table's status with its striped counters added in.
+DevStatus sum_status(const TableStatus &ts);
 lhs_status read_status(lhs_table *t, DevStatus *out);
 lhs_status alloc_table(uint64_t capacity, uint32_t state_words, const lhs_config *cfg, lhs_table **out);
 

@@ -315,16 +315,21 @@ lhs_status launch_zero_u64(uint64_t *p, uint64_t n, hipStream_t s) {
     return hipGetLastError() == hipSuccess ? LHS_OK : LHS_EDEVICE;
 }
 
+DevStatus sum_status(const TableStatus &ts) {
+    DevStatus st = ts.st;
+    for (const CounterLine &c : ts.stripe) {
+        st.wait_hits += c.waits;
+        st.cas_failures += c.cas_failures;
+        st.lines += c.lines;
+    }
+    return st;
+}
+
 lhs_status read_status(lhs_table *t, DevStatus *out) {
     LHS_HIP(hipStreamSynchronize(t->last_stream));
     TableStatus ts;
     LHS_HIP(hipMemcpy(&ts, t->status, sizeof(ts), hipMemcpyDeviceToHost));
-    *out = ts.st;
-    for (const CounterLine &c : ts.stripe) {
-        out->wait_hits += c.waits;
-        out->cas_failures += c.cas_failures;
-        out->lines += c.lines;
-    }
+    *out = sum_status(ts);
     return LHS_OK;
 }
 

@@ -449,14 +449,16 @@ SegFront seg_dense(const uint32_t *buf, uint32_t size, uint64_t n) {
 // A level of at most this many states goes back to a persistent launch.
 constexpr uint64_t kBoardReturn = 1u << 15;
 
-// Host-driven level loop on table t (already sized, W matching); with a
-// levels area, small levels run in persistent launches.
+// Host-driven level loop on table t (already sized, W matching).  Small
+// levels run in persistent launches; the first one's area is on the device.
+// before_end() is called before each wait that may be the last, with all work
+// queued.
 lhs_status explore_host_loop(lhs_table *t, const reach_model *m, const uint2 *d_trans,
                              uint32_t max_levels, hipStream_t s, reach_result *r,
-                             uint32_t *d_init, bool parents, LevelsArea *d_pre, LevelsArea *h_pre) {
-    const ModelView mv = model_view(m, d_trans);
+                             uint32_t *d_init, bool parents, const TableView &tv, const ModelView &mv,
+                             LevelsArea *d_pre, LevelsArea *h_pre,
+                             const std::function<lhs_status()> &before_end) {
     const bool bytes = rows_fit_bytes(m);
-    const TableView tv = bfs_view(t, parents);
     std::vector<uint64_t> levels;
     // s0 is level 0: insert it with the batched find-or-put; its slot is the
     // first frontier (the seen byte lands in the other frontier buffer).
@@ -472,7 +474,6 @@ lhs_status explore_host_loop(lhs_table *t, const reach_model *m, const uint2 *d_
     const uint32_t size = seg_size(t);
     SegFront f = seg_root(t->frontier[0], size);
     int capped = 0;
-    hipLaunchKernelGGL(k_zero_level, dim3(1), dim3(64), 0, s, t->level, t->segs);
     bool finished = false;
     // levels that cannot fill the GPU run in one persistent launch each time
     // they come up in a row: from level `levels.size() - 1`, dense in
@@ -482,7 +483,8 @@ lhs_status explore_host_loop(lhs_table *t, const reach_model *m, const uint2 *d_
         run.n_front = (uint32_t)levels.back();
         run.cur = cur;
         run.total = total;
-        const lhs_status rc = explore_levels(t, tv, mv, bytes, m->state_cap, d_pre, h_pre, s, run);
+        run.uploaded = levels.size() == 1;
+        const lhs_status rc = explore_levels(t, tv, mv, bytes, m->state_cap, d_pre, h_pre, s, run, before_end);
         if (rc != LHS_OK)
             return rc;
         levels.insert(levels.end(), run.levels.begin(), run.levels.end());
@@ -497,9 +499,13 @@ lhs_status explore_host_loop(lhs_table *t, const reach_model *m, const uint2 *d_
         f = seg_dense(t->frontier[cur], size, levels.back());
         return LHS_OK;
     };
-    if (d_pre && (rc = small_levels()) != LHS_OK)
+    if ((rc = small_levels()) != LHS_OK)
         return rc;
+    if (!finished)
+        hipLaunchKernelGGL(k_zero_level, dim3(1), dim3(64), 0, s, t->level, t->segs);
+    bool waited = true;   // for everything, and before_end() was called
     while (!finished) {
+        waited = false;
         uint32_t limit = 0xFFFFFFFFu;
         if (m->state_cap)
             limit = (uint32_t)std::min<uint64_t>(m->state_cap - total, 0xFFFFFFFFull);
@@ -534,16 +540,21 @@ lhs_status explore_host_loop(lhs_table *t, const reach_model *m, const uint2 *d_
         total += n_next;
         f = next;
         cur ^= 1;
-        if (d_pre && n_next <= kBoardReturn) {
+        if (n_next <= kBoardReturn) {
             hipLaunchKernelGGL(k_dense_front, dim3((uint32_t)(n_next + 255) / 256), dim3(256), 0, s, f,
                                t->frontier[cur ^ 1]);
             LHS_HIP(hipGetLastError());
             cur ^= 1;
             if ((rc = small_levels()) != LHS_OK)
                 return rc;
+            waited = true;
         }
     }
-    LHS_HIP(hipStreamSynchronize(s));
+    if (!waited) {
+        if ((rc = before_end()) != LHS_OK)
+            return rc;
+        LHS_HIP(hipStreamSynchronize(s));
+    }
     r->total_states = total;
     r->edges = edges;
     r->deadlocks = dead;
@@ -740,8 +751,9 @@ static lhs_status reach_explore_impl(const reach_model *m, const reach_opts *o, 
     // model upload through the device's workspace: one copy, no allocation
     Carve c;
     const size_t o_trans = c.take<uint2>(packed.size()), o_init = c.take<uint32_t>(W);
-    const size_t upload = c.off, o_ctx = c.take<GraphCtx>(1), o_actl = c.take<AsyncCtl>(1),
-                 o_pre = c.take<LevelsArea>(1);
+    // the last part uploaded is the head of the levels area
+    const size_t o_pre = c.take<LevelsArea>(1), upload = o_pre + offsetof(LevelsArea, levels),
+                 o_ctx = c.take<GraphCtx>(1), o_actl = c.take<AsyncCtl>(1), o_status = c.take<TableStatus>(1);
     Workspace &ws = workspace(dev);
     std::unique_lock<std::mutex> lock(ws.mu);
     rc = ensure_bfs_buffers(t);
@@ -757,9 +769,13 @@ static lhs_status reach_explore_impl(const reach_model *m, const reach_opts *o, 
         rc = ws_reserve(ws, c.off, c.off);
     uint2 *d_trans = at<uint2>(ws.dev, o_trans);
     uint32_t *d_init = at<uint32_t>(ws.dev, o_init);
+    const TableView tv = bfs_view(t, parents);
+    const ModelView mv = model_view(m, d_trans);
     if (rc == LHS_OK) {
         std::memcpy(at<void>(ws.host, o_trans), packed.data(), packed.size() * sizeof(uint2));
         std::memcpy(at<void>(ws.host, o_init), m->init, W * sizeof(uint32_t));
+        levels_area(at<LevelsArea>(ws.host, o_pre), at<LevelsArea>(ws.dev, o_pre), t, tv, mv, m->state_cap,
+                    LevelsRun());
         if (hipMemcpyAsync(ws.dev, ws.host, upload, hipMemcpyHostToDevice, s) != hipSuccess)
             rc = LHS_EDEVICE;
     }
@@ -769,24 +785,31 @@ static lhs_status reach_explore_impl(const reach_model *m, const reach_opts *o, 
     }
     if (rc == LHS_OK) {
         (void)hipEventRecord(ws.ev[0], s);
+        // the end of the exploration's time, and its status to the host
+        bool finished = false;
+        auto finish = [&]() -> lhs_status {
+            finished = true;
+            LHS_HIP(hipEventRecord(ws.ev[1], s));
+            LHS_HIP(hipMemcpyAsync(at<void>(ws.host, o_status), t->status, sizeof(TableStatus),
+                                   hipMemcpyDeviceToHost, s));
+            return LHS_OK;
+        };
         if (async)
             rc = explore_async(t, m, d_trans, s, r, d_init, at<AsyncCtl>(ws.dev, o_actl),
                                at<AsyncCtl>(ws.host, o_actl), parents);
         else if (opts.flags & REACH_F_GRAPH)
             rc = explore_graph(t, m, d_trans, max_levels, s, r, d_init, at<GraphCtx>(ws.host, o_ctx), parents);
         else
-            rc = explore_host_loop(t, m, d_trans, max_levels, s, r, d_init, parents, at<LevelsArea>(ws.dev, o_pre),
-                                   at<LevelsArea>(ws.host, o_pre));
-        (void)hipEventRecord(ws.ev[1], s);
-        if (hipEventSynchronize(ws.ev[1]) == hipSuccess) {
+            rc = explore_host_loop(t, m, d_trans, max_levels, s, r, d_init, parents, tv, mv,
+                                   at<LevelsArea>(ws.dev, o_pre), at<LevelsArea>(ws.host, o_pre), finish);
+        // the level loop has queued both and waited already
+        if (rc == LHS_OK && !finished && (finish() != LHS_OK || hipStreamSynchronize(s) != hipSuccess))
+            rc = LHS_EDEVICE;
+        if (rc == LHS_OK) {
             float ms = 0;
             (void)hipEventElapsedTime(&ms, ws.ev[0], ws.ev[1]);
             r->gpu_ms = ms;
-        }
-        if (rc == LHS_OK) {
-            DevStatus st;
-            if (read_status(t, &st) == LHS_OK)
-                r->wait_hits = st.wait_hits;
+            r->wait_hits = sum_status(*at<TableStatus>(ws.host, o_status)).wait_hits;
         }
     }
     t->has_parents = parents && rc == LHS_OK;

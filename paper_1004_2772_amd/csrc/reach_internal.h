@@ -1,6 +1,7 @@
 // Device view of a model and helpers shared by the reachability units.
 #pragma once
 
+#include <functional>
 #include <vector>
 
 #include "internal.h"
@@ -84,19 +85,25 @@ lhs_status ensure_bfs_buffers(lhs_table *t);
 // persistent launch (board.h) from the level described in `run`, until one
 // exceeds kBoardHandover states: small levels then cost their chain of memory
 // round trips each, not a launch and a host round trip.  The level's frontier
-// must be dense in frontier[run.cur].
+// must be dense in frontier[run.cur].  The area's head is laid out in h
+// (levels_area) and uploaded with the model (run.uploaded) or here;
+// before_sync() is called, once everything is queued, before the wait for it.
 struct LevelsArea;
 struct LevelsRun {
     uint32_t n_front = 1;           // in: the level's states
     uint32_t cur = 0;               // its frontier buffer; out: the last level's
     uint64_t total = 1;             // states so far
+    bool uploaded = false;          // in: the area's head is on the device
     std::vector<uint64_t> levels;   // out: counts of the levels found
     uint64_t edges = 0, deadlocks = 0, wait_hits = 0;
     bool handed = false;            // stopped after a level above the threshold
     bool capped = false;
 };
+void levels_area(LevelsArea *h, const LevelsArea *d, lhs_table *t, const TableView &tv, const ModelView &mv,
+                 uint64_t cap, const LevelsRun &run);
 lhs_status explore_levels(lhs_table *t, const TableView &tv, const ModelView &mv, bool bytes, uint64_t cap,
-                          LevelsArea *d_area, LevelsArea *h_area, hipStream_t s, LevelsRun &run);
+                          LevelsArea *d_area, LevelsArea *h_area, hipStream_t s, LevelsRun &run,
+                          const std::function<lhs_status()> &before_sync);
 uint64_t auto_capacity(const reach_model *m);
 // The view a BFS on t expands with: predecessor records when requested.
 TableView bfs_view(lhs_table *t, bool parents);
