@@ -289,11 +289,24 @@ lhs_status done_offsets(lhs_table *t, std::vector<uint64_t> &offsets, uint32_t *
 
 namespace lhs {
 
+// Lanes per operation of a call of n operations.  One lane each (64 in a
+// wavefront) is the tuned choice of large tables and calls; while eight lanes
+// each still have every operation in flight at once, a call ends with its
+// longest chain of probes, and a group's probe is the shorter one: 2^22 slots
+// of 8 words 95 % full, 200 to 64000 operations 11.5 to 24.8 us with one lane
+// and 8.5 to 16.1 us with eight (half full 8.6 both; 256000 operations 40.6
+// and 42.2 us, half full 15.2 and 19.5 us).  Lanes that the caller has chosen
+// stay.
+static uint32_t tps_of_call(const lhs_table *t, uint64_t n) {
+    const uint32_t tps = tps_find_or_put(t);
+    return t->tuned && tps == 1 && n <= (uint64_t)t->ncu * (2048 / 8) ? 8u : tps;
+}
+
 lhs_status launch_find_or_put(lhs_table *t, const uint32_t *d_states, uint64_t n, uint8_t *d_seen,
                               uint32_t *d_index, hipStream_t s) {
     if (!n)
         return LHS_OK;
-    const uint32_t tps = tps_find_or_put(t);
+    const uint32_t tps = tps_of_call(t, n);
     const uint32_t rows = tps > 1 ? fop_tile_rows(tps, t->W, n, (uint32_t)t->ncu) : kBlock;
     // G == 1 needs only the row tile; G > 1 also hashes and results
     const size_t lds = (size_t)rows * ((t->W | 1u) + (tps > 1 ? 4u : 0u)) * sizeof(uint32_t);
@@ -400,7 +413,10 @@ lhs_status lhs_create(uint64_t capacity, uint32_t state_words, lhs_table **out) 
     if (!out || state_words < 1 || state_words > 32)
         return LHS_EINVAL;
     const lhs_config cfg = tuned_config(LHS_TUNE_TABLE, state_words, capacity);
-    return lhs_create_ex(capacity, state_words, &cfg, out);
+    const lhs_status rc = lhs_create_ex(capacity, state_words, &cfg, out);
+    if (rc == LHS_OK)
+        (*out)->tuned = true;
+    return rc;
 }
 
 lhs_status lhs_create_ex(uint64_t capacity, uint32_t state_words, const lhs_config *cfg,
@@ -465,6 +481,7 @@ lhs_status lhs_set_threads_per_state(lhs_table *t, uint32_t tps) {
         return LHS_EINVAL;
     t->tps_fop = tps;
     t->tps_exp = tps;
+    t->tuned = false;
     return LHS_OK;
 }
 

@@ -321,3 +321,28 @@ def test_tile_row_edges(lhs, W, tps):
         t.check()
         check_stream_batches(o_id, distinct, seen.cpu().numpy(), idx.cpu().numpy().view(np.uint32), bounds)
         assert t.count() == distinct
+
+
+@pytest.mark.parametrize("W", [1, 9, 32])
+def test_call_size_lanes(lhs, W):
+    """Call sizes around the line where a tuned table's calls change from
+    eight lanes per operation to one, on a table that ends nearly full."""
+    import torch
+    line = torch.cuda.get_device_properties(0).multi_processor_count * 256
+    sizes = [line + 1, line, 65, line - 1]
+    print(f"\n[fop] lanes by call size W={W} sizes={sizes}", flush=True)
+    rows, order = gen.dup_stream(500 + W, sum(sizes) * 5 // 8, W, 2)
+    stream = gen.gather(rows, order)[: sum(sizes)]
+    o_seen, o_id, distinct = oracle.stream(stream)
+    dev = dev_u32(stream)
+    seen = torch.empty(len(stream), dtype=torch.uint8, device="cuda")
+    idx = torch.empty(len(stream), dtype=torch.int32, device="cuda")
+    with lhs.Table(1 << max(10, (distinct - 1).bit_length()), W) as t:
+        bounds, at = [], 0
+        for n in sizes:
+            t.find_or_put(dev[at:at + n], seen[at:at + n], idx[at:at + n])
+            bounds.append((at, at + n))
+            at += n
+        t.check()
+        check_stream_batches(o_id, distinct, seen.cpu().numpy(), idx.cpu().numpy().view(np.uint32), bounds)
+        assert t.count() == distinct
