@@ -50,6 +50,7 @@ struct ModelState {
     ModelView m;
     uint32_t *fr[2];
     unsigned long long *levels;   // [max_levels] level counts (coherent stores)
+    unsigned long long *host_levels;   // server: where they go at the end (pinned)
     unsigned long long cap;
     uint32_t max_levels;
     uint32_t handover;            // stop after a level of more states (0 = never)
@@ -93,6 +94,12 @@ __device__ __forceinline__ uint32_t ticket_next(unsigned long long t) { return (
 constexpr uint32_t kSmallLevel = 32768;
 constexpr uint32_t kMinTileRows = 32;
 constexpr uint32_t kFewModels = 8;
+// While at most kFewModels models are unfinished, workgroups of a number from
+// kFewGrid on wait kSleepyNaps naps (40 us) between polls: one workgroup per
+// CU takes these models' levels soonest, and 768 more that poll slow them
+// down (3 models of 64: 3.69 -> 3.34 ms, 6: 4.1 -> 3.65 ms).
+constexpr uint32_t kFewGrid = 256;
+constexpr uint32_t kSleepyNaps = 96;   // of 1024 cycles
 static_assert(kExpandBlock == 256 && kMinTileRows == 32, "rows of a ticket: 32, 64, 128 or 256");
 
 // A level of at most this many states stays with the workgroup that finished
@@ -128,18 +135,15 @@ struct BoardItem {
 
 // How the driver differs between the batch and the server:
 //   kServe                the server: models come and go during the launch
-//   kNapShift, kNap       an idle workgroup's wait between polls: 1 + (idle
-//                         workgroups >> kNapShift) naps of 64 kNap cycles
 //   model(ms, i, key)     model i's constants (block-wide call)
 //   idle_check(...)       server: what an idle workgroup does besides looking
 //                         for tiles (lane 0): 0 nothing, 1 admit, 2 leave
 //   admit(M, B, i)        server: model i's level 0 (block-wide call)
 //   level(M, k, n)        store a level's count (thread 0)
 //   beat()                server: a sign of progress, at each level handed out
-//   finished(...)         thread 0: model i is finished
+//   finished(M, i, own)   model i is finished (block-wide call)
 struct BatchDriver {
     static constexpr bool kServe = false;
-    static constexpr uint32_t kNapShift = 5, kNap = 4;
     __device__ const ModelState &model(const ModelState *ms, uint32_t i, unsigned long long) { return ms[i]; }
     __device__ uint32_t idle_check(BoardCtl *, uint32_t, uint32_t, uint32_t, uint32_t &) { return 0; }
     __device__ void admit(const ModelState &, BoardModel &, uint32_t) {}
@@ -148,7 +152,7 @@ struct BatchDriver {
     }
     __device__ void beat() {}
     template <class Own>
-    __device__ void finished(uint32_t, const Own &, uint32_t, uint32_t, uint32_t, unsigned long long) {}
+    __device__ void finished(const ModelState &, uint32_t, const Own &) {}
 };
 
 // Take a tile (one wavefront, all lanes; `h` a lane-uniform random state).
@@ -158,12 +162,12 @@ struct BatchDriver {
 // try for each tile; and it waits the longer between polls the more are idle:
 // all polls read the same few lines, which the working workgroups' tickets and
 // counts need too, and a workgroup that has just finished a tile looks again
-// at once in any case.  768 idle workgroups that polled every 0.4 us took a
-// third of the server's time (147-level queries: 11.5 -> 8.5 ms, 60 of a few
-// thousand states each: 6.7 -> 3.4 ms) and some of the batch's (8.1 -> 7.7).
-// The single-model levels, whose 255 idle workgroups see all of a level's
-// tiles at once, lose with longer naps (437 -> 500 us at 2.4 us), so the
-// batch's are short.
+// at once in any case.  With 768 idle workgroups that polled every 0.4 us, the
+// server's 147-level queries took 11.5 ms and now take 8.5, 60 of a few
+// thousand states each 6.7 and 3.4 ms; the 64-model batch 8.1 and 7.6 ms.
+// The batch's naps are the shorter ones: a single model's levels, whose 255
+// idle workgroups see all of a level's tiles at once, lose with longer ones
+// (437 -> 500 us at 2.4 us).
 template <class Driver>
 __device__ inline void board_take(Driver &drv, const ModelState *ms, BoardModel *bm, unsigned long long *tickets,
                                   BoardCtl *ctl, uint32_t n, uint32_t &h, BoardItem *out) {
@@ -181,6 +185,7 @@ __device__ inline void board_take(Driver &drv, const ModelState *ms, BoardModel 
         const unsigned long long tk = i < slots ? ld_coherent(tickets + i) : 0ull;
         const uint32_t remaining = ld_coherent(&ctl->remaining), error = ld_coherent(&ctl->error);
         const uint32_t idlers = ld_coherent(&ctl->idle);
+        const uint32_t quota = remaining <= kFewModels ? kFewGrid : 0xFFFFFFFFu;
         if ((!kServe && remaining == 0u) || error != 0u)
             break;
         const uint32_t tiles = ticket_tiles(tk), avail = tiles - min(ticket_next(tk), tiles);
@@ -191,7 +196,7 @@ __device__ inline void board_take(Driver &drv, const ModelState *ms, BoardModel 
             bool go = true;
             if (idle) {
                 const uint32_t all = wave_sum(min(avail, 1u << 16));
-                go = r % max(idlers, 1u) < 2u * all;
+                go = r % max(min(idlers, quota), 1u) < 2u * all;
             }
             if (go) {
                 const uint32_t k = r % (uint32_t)__popcll(mask);
@@ -221,11 +226,11 @@ __device__ inline void board_take(Driver &drv, const ModelState *ms, BoardModel 
                 atomicAdd(&ctl->idle, 1u);
         }
         polls += 1u + (kServe ? 0u : idlers >> 8);   // counts time: naps grow with the idle workgroups
-        const uint32_t wait = 1u + (idlers >> Driver::kNapShift);
+        const uint32_t near = min(idlers, quota), far = 1u + (idlers >> 4);
         if constexpr (kServe) {
             uint32_t act = 0, slot = 0;
             if (lane == 0)
-                act = drv.idle_check(ctl, polls, remaining, wait, slot);
+                act = drv.idle_check(ctl, polls, remaining, blockIdx.x >= quota ? kSleepyNaps / 2 : far, slot);
             act = (uint32_t)__builtin_amdgcn_readfirstlane((int)act);
             if (act == 2u)
                 break;
@@ -237,17 +242,21 @@ __device__ inline void board_take(Driver &drv, const ModelState *ms, BoardModel 
             }
             slots = min(ld_coherent(&ctl->slots), n);
             // the last query gone: wake up for the next one soon
-            const uint32_t naps = remaining ? wait : min(polls, 8u) / 2u + 1u;
+            const uint32_t naps = remaining == 0u           ? min(polls, 8u)
+                                  : blockIdx.x >= quota      ? kSleepyNaps
+                                  : remaining <= kFewModels ? 2u
+                                                            : 2u * far;
             for (uint32_t k = 0; k < naps; ++k)
-                __builtin_amdgcn_s_sleep(Driver::kNap);
+                __builtin_amdgcn_s_sleep(16);
         } else {
             if (polls > kBarrierSpinLimit) {
                 if (lane == 0)
                     atomicCAS(&ctl->error, 0u, (uint32_t)LHS_ESTALL);
                 break;
             }
-            for (uint32_t k = 0; k < wait; ++k)
-                __builtin_amdgcn_s_sleep(Driver::kNap);
+            const uint32_t naps = blockIdx.x >= quota ? 4u * kSleepyNaps : 1u + (near >> 5);
+            for (uint32_t k = 0; k < naps; ++k)
+                __builtin_amdgcn_s_sleep(4);
         }
     }
     if (idle && lane == 0)
@@ -278,6 +287,8 @@ struct BoardOwn {
     uint32_t n_next, limit;         // its states, and the new states it may add
     uint32_t tiles, rows;           // its tiles, of `rows` states (0: the model is finished)
     uint32_t solo;                  // it stays with this workgroup
+    uint32_t finished, err, over, overflow;   // the model has ended, and how
+    unsigned long long waits;
 };
 
 // Whether a level of n_next states found after own.n_levels levels stays
@@ -298,6 +309,7 @@ __device__ inline void board_next(Driver &drv, const ModelState &M, BoardModel &
                                   bool solo, uint32_t remaining, uint32_t idle) {
     bool done = false;
     uint32_t overflow = 0;
+    own.finished = 0;
     own.n_next = n_next;
     own.tiles = 0;
     own.solo = 0;
@@ -350,8 +362,11 @@ __device__ inline void board_next(Driver &drv, const ModelState &M, BoardModel &
     st_coherent(&B.n_levels, own.n_levels);
     wait_vm_complete();
     if (done) {
-        atomicSub(&ctl->remaining, 1u);
-        drv.finished(i, own, err, over ? 1u : 0u, overflow, waits);
+        own.finished = 1;
+        own.err = err;
+        own.over = over;
+        own.overflow = overflow;
+        own.waits = waits;
     } else {
         drv.beat();
         if (own.tiles > 1)
@@ -513,6 +528,11 @@ __device__ __forceinline__ void board_run(Driver &drv, uint32_t *smem, const Mod
             s_it.limit = s_own.limit;
         }
         __syncthreads();
+        if (s_own.finished) {
+            drv.finished(M, i, s_own);
+            if (tid == 0)
+                atomicSub(&ctl->remaining, 1u);
+        }
         if (s_own.tiles && s_it.exit)
             break;
         solo_levels = s_own.solo && solo ? solo_levels + 1 : 0;

@@ -182,10 +182,9 @@ __global__ __launch_bounds__(kExpandBlock, LS == 8 ? 4 : 1) void k_step(BatchSlo
 //    upload and one kernel on its upload stream, which also appends the slot
 //    to box->admit_slot; then it raises box->admit_tail, by a copy.  An idle
 //    workgroup takes the admission, inserts s0 and runs level 0.
-//  * Completion.  The workgroup that finishes a query posts its result to a
-//    ring of records in pinned host memory (system scope, the sequence word
-//    last, after the query's level counts, also in pinned memory, are
-//    complete).
+//  * Completion.  The workgroup that finishes a query copies its level counts
+//    to pinned host memory and posts its result to a ring of records there
+//    (system scope, the sequence word last).
 //  * Lifetime.  After a while without work, with no query admitted and
 //    unfinished, a workgroup leaves and closes the launch to admissions
 //    (box->closing); every other workgroup leaves once no query is left.
@@ -209,7 +208,7 @@ constexpr uint32_t kAdmitRing = 2048;      // admission entries (> 2 x max activ
 constexpr uint32_t kDoneRing = 2048;       // completion records (> 2 x max active)
 constexpr uint64_t kServeCapacity = 1ull << 30;   // a served table has fewer slots
 constexpr uint32_t kServeMaxLevels = 1u << 16; // levels of one served query
-constexpr uint32_t kIdleLeave = 384;       // checks (~5 ms) finding no query on the GPU
+constexpr uint32_t kIdleLeave = 320;       // checks (~5 ms) finding no query on the GPU
                                            // before a workgroup leaves
 constexpr uint32_t kStallChecks = 1u << 19; // an idle workgroup's checks (~3 s) without any level
                                            // finished while queries are unfinished: the launch
@@ -260,7 +259,6 @@ __device__ __forceinline__ void st_system(T *p, T v) {
 template <uint32_t LS>
 struct ServeDriver {
     static constexpr bool kServe = true;
-    static constexpr uint32_t kNapShift = 4, kNap = 32;
     ServeBox *box;
     DoneRec *done;
     const uint32_t *roots;
@@ -295,9 +293,11 @@ struct ServeDriver {
             return 0;
         const bool closing = ld_coherent(&box->closing) != 0u;
         const unsigned long long ah = ld_coherent(&box->admit_head);
-        // acquire: the host's writes of the slot's constants, s0 and
-        // admission entry precede the tail it raised
-        if (!closing && ah < __hip_atomic_load(&box->admit_tail, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_SYSTEM)) {
+        if (!closing && ah < ld_system(&box->admit_tail)) {
+            // the writes of the slot's constants, s0 and admission entry
+            // precede the tail; not an acquire at every poll, which would
+            // empty the XCD's caches each time
+            __atomic_thread_fence(__ATOMIC_ACQUIRE);
             __hip_atomic_fetch_add(&ctl->remaining, 1u, __ATOMIC_SEQ_CST, __HIP_MEMORY_SCOPE_AGENT);
             if (__hip_atomic_load(&box->closing, __ATOMIC_SEQ_CST, __HIP_MEMORY_SCOPE_AGENT) == 0u &&
                 atomicCAS(&box->admit_head, ah, ah + 1ull) == ah) {
@@ -353,7 +353,7 @@ struct ServeDriver {
                 st_coherent(&B.lc.deadlocks, 0ull);
                 st_coherent(&B.tiles_done, 0u);
                 st_coherent(&B.key, M.m.key);
-                st_system(M.levels, 1ull);
+                st_coherent(M.levels, 1ull);
             }
             wait_vm_complete();
         }
@@ -361,25 +361,32 @@ struct ServeDriver {
     }
 
     __device__ void level(const ModelState &M, uint32_t k, uint32_t n) {
-        st_system(M.levels + k, (unsigned long long)n);
+        st_coherent(M.levels + k, (unsigned long long)n);
     }
     __device__ void beat() { atomicAdd(&box->beat, 1u); }
 
-    // Post the finished query's completion record (one thread).
+    // Post the finished query's level counts and completion record
+    // (block-wide).  Only here are stores to host memory waited for: one at
+    // each level cost 4 us of each.
     template <class Own>
-    __device__ void finished(uint32_t slot, const Own &own, uint32_t err, uint32_t capped, uint32_t overflow,
-                             unsigned long long waits) {
+    __device__ void finished(const ModelState &M, uint32_t slot, const Own &own) {
+        for (uint32_t k = threadIdx.x; k < own.n_levels; k += blockDim.x)
+            st_system(M.host_levels + k, ld_coherent(M.levels + k));
+        __threadfence_system();
+        __syncthreads();
+        if (threadIdx.x != 0)
+            return;
         const unsigned long long pos = atomicAdd(&box->done_tail, 1ull);
         DoneRec *r = done + (pos % kDoneRing);
         st_system(&r->slot, slot);
-        st_system(&r->error, err);
+        st_system(&r->error, own.err);
         st_system(&r->n_levels, own.n_levels);
-        st_system(&r->capped, capped);
-        st_system(&r->overflow, overflow);
+        st_system(&r->capped, own.over);
+        st_system(&r->overflow, own.overflow);
         st_system(&r->total, own.total);
         st_system(&r->edges, own.edges);
         st_system(&r->deadlocks, own.deadlocks);
-        st_system(&r->wait_hits, waits);
+        st_system(&r->wait_hits, own.waits);
         __hip_atomic_store(&r->seq, pos + 1ull, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
         beat();
     }
@@ -517,9 +524,9 @@ struct Persist {
     BoardCtl *d_ctl = nullptr;
     ServeBox *d_box = nullptr;
     uint32_t *d_roots = nullptr;                  // [slot][32]
-    // [slot] -> level counts in pinned memory (written by the device), on
-    // first use, and their device addresses
-    std::vector<unsigned long long *> h_levels, h_levels_dev;
+    // [slot] -> on first use: level counts in pinned memory (written when the
+    // query ends), their device addresses, and the counts on the device
+    std::vector<unsigned long long *> h_levels, h_levels_dev, d_levels;
     void *d_stage = nullptr;                      // device copy of the admissions' staging
     size_t cap_d_stage = 0;
     DoneRec *h_done = nullptr;                    // pinned; written by the device
@@ -923,6 +930,7 @@ lhs_status persist_init(reach_server *s) {
     P.slot_q.assign(n, nullptr);
     P.h_levels.assign(n, nullptr);
     P.h_levels_dev.assign(n, nullptr);
+    P.d_levels.assign(n, nullptr);
     for (uint32_t i = n; i-- > 0;)
         P.free_slots.push_back(i);
     return persist_reset(s);
@@ -940,6 +948,8 @@ void persist_free(reach_server *s) {
     for (auto p : P.h_levels)
         if (p)
             (void)hipHostFree(p);
+    for (auto p : P.d_levels)
+        (void)hipFree(p);
     for (void *h : {(void *)P.h_done, (void *)P.h_ctl, (void *)P.h_word})
         if (h)
             (void)hipHostFree(h);
@@ -1000,17 +1010,20 @@ lhs_status persist_post(reach_server *s, const std::vector<Query *> &qs) {
         q->slot = slot;
         ++P.live;
         if (!P.h_levels[slot]) {
+            constexpr size_t lv = kServeMaxLevels * sizeof(unsigned long long);
+            unsigned long long *h = nullptr, *d = nullptr;
             void *dev = nullptr;
-            if (hipHostMalloc(&P.h_levels[slot], kServeMaxLevels * sizeof(unsigned long long),
-                              hipHostMallocCoherent) != hipSuccess ||
-                hipHostGetDevicePointer(&dev, P.h_levels[slot], 0) != hipSuccess) {
+            if (hipMalloc(&d, lv) != hipSuccess || hipHostMalloc(&h, lv, hipHostMallocCoherent) != hipSuccess ||
+                hipHostGetDevicePointer(&dev, h, 0) != hipSuccess) {
                 (void)hipGetLastError();
-                if (P.h_levels[slot])
-                    (void)hipHostFree(P.h_levels[slot]);
-                P.h_levels[slot] = nullptr;
+                (void)hipFree(d);
+                if (h)
+                    (void)hipHostFree(h);
                 return LHS_ENOMEM;
             }
+            P.h_levels[slot] = h;
             P.h_levels_dev[slot] = static_cast<unsigned long long *>(dev);
+            P.d_levels[slot] = d;
         }
         pack_model(&q->m, packed);
         const size_t bytes = packed.size() * sizeof(uint2);
@@ -1033,7 +1046,8 @@ lhs_status persist_post(reach_server *s, const std::vector<Query *> &qs) {
         e.ms.m.key = q->ticket;   // unique and nonzero: a later query may reuse this transition buffer
         e.ms.fr[0] = q->t->frontier[0];
         e.ms.fr[1] = q->t->frontier[1];
-        e.ms.levels = P.h_levels_dev[slot];
+        e.ms.levels = P.d_levels[slot];
+        e.ms.host_levels = P.h_levels_dev[slot];
         e.ms.cap = q->m.state_cap;
         e.ms.max_levels = kServeMaxLevels;
         e.zero = TableZero{reinterpret_cast<uint4 *>(q->t->bucket), q->t->capacity / 2,
