@@ -412,8 +412,8 @@ def main():
         per_edge, per_exp = spec_bytes_per_op(m.W), 4 * m.W + 4
         bfs_bytes = res.edges * per_edge + expanded * per_exp + (res.total - 1) * 4
         bfs_gbs = bfs_bytes / (gms / 1e3) / 1e9
-        bfs["roofline"] = {"bound": "hbm", "kernel": "k_expand (the whole exploration, its first levels in "
-                                                     "k_batch_persistent)",
+        bfs["roofline"] = {"bound": "hbm", "kernel": "k_expand (the whole exploration, its small levels in "
+                                                     "k_levels)",
                            "bytes_per_edge": per_edge, "bytes_per_expanded_state": per_exp,
                            "bytes_per_new_state": 4, "algorithmic_bytes": bfs_bytes,
                            "achieved": round(bfs_gbs, 1), "peak": 8000.0, "unit": "GB/s",
