@@ -41,7 +41,17 @@
 
 namespace lhs {
 
-constexpr uint32_t kBarrierSpinLimit = 1u << 24;   // bound on an idle workgroup's polls
+// An idle workgroup's wait is bounded by the time since the launch last gave a
+// sign of progress (BoardCtl::beat: a level handed out, 32 levels run alone, a
+// model finished), on the GPU's constant 100 MHz clock.  Not by its polls: a
+// poll takes 1 to 40 us, by the naps after it and by how many poll.  The
+// longest stretch without a beat is that of an operation on a full table,
+// which probes every line before it reports EFULL: 1.4 us a line, 2.9 s at
+// 2^24 slots in lines of 8.  So a model that overflows a table of up to 2^27
+// slots ends with EFULL, and a chain of any number of levels ends.
+constexpr uint64_t kWallHz = 100000000;
+constexpr uint64_t kStallTicks = 30 * kWallHz;
+constexpr uint32_t kBeatPolls = 16;   // polls between an idle workgroup's looks at the beat
 
 // Per-model constants (written by the host before the launch, or before the
 // server admits the model).
@@ -56,12 +66,13 @@ struct ModelState {
     uint32_t handover;            // stop after a level of more states (0 = never)
 };
 
-// Shared by all workgroups of a launch; idle ones poll this line.
+// Shared by all workgroups of a launch; idle ones poll its first line.
 struct alignas(128) BoardCtl {
     uint32_t remaining;   // unfinished models
     uint32_t error;
     uint32_t idle;        // workgroups without a tile
     uint32_t slots;       // server: tickets in use are below this
+    alignas(128) uint32_t beat;   // signs of progress (kStallTicks)
 };
 
 // One model's level and progress: written by whichever workgroup finalises a
@@ -140,17 +151,15 @@ struct BoardItem {
 //                         for tiles (lane 0): 0 nothing, 1 admit, 2 leave
 //   admit(M, B, i)        server: model i's level 0 (block-wide call)
 //   level(M, k, n)        store a level's count (thread 0)
-//   beat()                server: a sign of progress, at each level handed out
 //   finished(M, i, own)   model i is finished (block-wide call)
 struct BatchDriver {
     static constexpr bool kServe = false;
     __device__ const ModelState &model(const ModelState *ms, uint32_t i, unsigned long long) { return ms[i]; }
-    __device__ uint32_t idle_check(BoardCtl *, uint32_t, uint32_t, uint32_t, uint32_t &) { return 0; }
+    __device__ uint32_t idle_check(BoardCtl *, uint32_t, uint32_t, uint32_t &) { return 0; }
     __device__ void admit(const ModelState &, BoardModel &, uint32_t) {}
     __device__ void level(const ModelState &M, uint32_t k, uint32_t n) {
         st_coherent(M.levels + k, (unsigned long long)n);
     }
-    __device__ void beat() {}
     template <class Own>
     __device__ void finished(const ModelState &, uint32_t, const Own &) {}
 };
@@ -173,7 +182,8 @@ __device__ inline void board_take(Driver &drv, const ModelState *ms, BoardModel 
                                   BoardCtl *ctl, uint32_t n, uint32_t &h, BoardItem *out) {
     constexpr bool kServe = Driver::kServe;
     const uint32_t lane = __lane_id();
-    uint32_t polls = 0, scanned = 0;
+    uint32_t polls = 0, scanned = 0, beat = 0;
+    uint64_t since = 0;   // when this workgroup last saw the beat change
     h = h * 1664525u + 1013904223u;
     uint32_t slots = kServe ? min(ld_coherent(&ctl->slots), n) : n;
     uint32_t w0 = slots > 64 ? (h >> 8) % ((slots + 63) / 64) * 64 : 0;   // any window first
@@ -225,12 +235,19 @@ __device__ inline void board_take(Driver &drv, const ModelState *ms, BoardModel 
             if (lane == 0)
                 atomicAdd(&ctl->idle, 1u);
         }
-        polls += 1u + (kServe ? 0u : idlers >> 8);   // counts time: naps grow with the idle workgroups
-        const uint32_t near = min(idlers, quota), far = 1u + (idlers >> 4);
+        if (++polls % kBeatPolls == 0) {   // not in a short wait: the look delays the next poll
+            const uint32_t b = ld_coherent(&ctl->beat);
+            const uint64_t now = wall_clock64();
+            if (polls == kBeatPolls || b != beat || remaining == 0u)
+                since = now;
+            else if (now - since > kStallTicks && lane == 0)
+                atomicCAS(&ctl->error, 0u, (uint32_t)LHS_ESTALL);
+            beat = b;
+        }
         if constexpr (kServe) {
             uint32_t act = 0, slot = 0;
             if (lane == 0)
-                act = drv.idle_check(ctl, polls, remaining, blockIdx.x >= quota ? kSleepyNaps / 2 : far, slot);
+                act = drv.idle_check(ctl, polls, remaining, slot);
             act = (uint32_t)__builtin_amdgcn_readfirstlane((int)act);
             if (act == 2u)
                 break;
@@ -245,16 +262,11 @@ __device__ inline void board_take(Driver &drv, const ModelState *ms, BoardModel 
             const uint32_t naps = remaining == 0u           ? min(polls, 8u)
                                   : blockIdx.x >= quota      ? kSleepyNaps
                                   : remaining <= kFewModels ? 2u
-                                                            : 2u * far;
+                                                            : 2u + 2u * (idlers >> 4);
             for (uint32_t k = 0; k < naps; ++k)
                 __builtin_amdgcn_s_sleep(16);
         } else {
-            if (polls > kBarrierSpinLimit) {
-                if (lane == 0)
-                    atomicCAS(&ctl->error, 0u, (uint32_t)LHS_ESTALL);
-                break;
-            }
-            const uint32_t naps = blockIdx.x >= quota ? 4u * kSleepyNaps : 1u + (near >> 5);
+            const uint32_t naps = blockIdx.x >= quota ? 4u * kSleepyNaps : 1u + (min(idlers, quota) >> 5);
             for (uint32_t k = 0; k < naps; ++k)
                 __builtin_amdgcn_s_sleep(4);
         }
@@ -368,9 +380,9 @@ __device__ inline void board_next(Driver &drv, const ModelState &M, BoardModel &
         own.overflow = overflow;
         own.waits = waits;
     } else {
-        drv.beat();
         if (own.tiles > 1)
             st_coherent(tickets + i, make_ticket(own.tiles, own.cur, own.rows, 1u));
+        atomicAdd(&ctl->beat, 1u);
     }
 }
 
@@ -516,8 +528,8 @@ __device__ __forceinline__ void board_run(Driver &drv, uint32_t *smem, const Mod
                 }
                 if (spilled)
                     st_coherent(&B.lc.n_next, 0u);
-                if (kServe && (solo_levels & 31u) == 31u)
-                    drv.beat();
+                if ((solo_levels & 31u) == 31u)
+                    atomicAdd(&ctl->beat, 1u);
                 board_next(drv, M, B, tickets, i, ctl, s_own, found, false, 0u, stay, remaining, idle);
                 s_it.exit = error;
             }
@@ -530,8 +542,10 @@ __device__ __forceinline__ void board_run(Driver &drv, uint32_t *smem, const Mod
         __syncthreads();
         if (s_own.finished) {
             drv.finished(M, i, s_own);
-            if (tid == 0)
+            if (tid == 0) {
+                atomicAdd(&ctl->beat, 1u);
                 atomicSub(&ctl->remaining, 1u);
+            }
         }
         if (s_own.tiles && s_it.exit)
             break;

@@ -210,9 +210,6 @@ constexpr uint64_t kServeCapacity = 1ull << 30;   // a served table has fewer sl
 constexpr uint32_t kServeMaxLevels = 1u << 16; // levels of one served query
 constexpr uint32_t kIdleLeave = 320;       // checks (~5 ms) finding no query on the GPU
                                            // before a workgroup leaves
-constexpr uint32_t kStallChecks = 1u << 19; // an idle workgroup's checks (~3 s) without any level
-                                           // finished while queries are unfinished: the launch
-                                           // has stalled
 
 struct ServeBox {
     unsigned long long admit_tail;   // admissions posted (host copies)
@@ -221,8 +218,6 @@ struct ServeBox {
     uint32_t stop;                   // host copy: leave once idle
     uint32_t closing;                // set by the first workgroup to leave; the
                                      // host clears it before the next launch
-    uint32_t beat;                   // levels finished (any launch)
-    uint32_t pad;
     uint32_t admit_slot[kAdmitRing]; // slot of admission k, at k % kAdmitRing
 };
 
@@ -264,9 +259,7 @@ struct ServeDriver {
     const uint32_t *roots;
     ModelState *held;        // LDS: the constants of slot *held_slot's query
     uint32_t *held_slot;     // LDS
-    // lane 0 of the polling wavefront: checks without a query on the GPU, and
-    // without a beat while there are some
-    uint32_t quiet = 0, stall = 0, last_beat = 0;
+    uint32_t quiet = 0;      // lane 0 of the polling wavefront: checks without a query on the GPU
 
     // The constants are read again only when the slot holds another query.
     __device__ const ModelState &model(const ModelState *ms, uint32_t i, unsigned long long key) {
@@ -286,9 +279,9 @@ struct ServeDriver {
     // leave sets `closing`, then checks `remaining`.  At least one sees the
     // other, so no query is admitted to a launch whose workgroups have begun
     // to leave.
-    __device__ uint32_t idle_check(BoardCtl *ctl, uint32_t polls, uint32_t remaining, uint32_t naps, uint32_t &slot) {
+    __device__ uint32_t idle_check(BoardCtl *ctl, uint32_t polls, uint32_t remaining, uint32_t &slot) {
         if (polls == 1u)
-            quiet = stall = 0;
+            quiet = 0;
         if (polls >= 16u && (polls & 3u))
             return 0;
         const bool closing = ld_coherent(&box->closing) != 0u;
@@ -307,13 +300,6 @@ struct ServeDriver {
             atomicSub(&ctl->remaining, 1u);
         } else if (remaining != 0u) {
             quiet = 0;
-            // bounded: with queries unfinished, some level finishes every
-            // few milliseconds at most
-            const uint32_t b = ld_coherent(&box->beat);
-            stall = b == last_beat ? stall + (1u + naps) / 2u : 0u;   // counts time
-            last_beat = b;
-            if (stall > kStallChecks)
-                atomicCAS(&ctl->error, 0u, (uint32_t)LHS_ESTALL);
         } else if (++quiet >= kIdleLeave || closing || ld_system(&box->stop) != 0u) {
             // a read-modify-write even when closing is already seen set (the
             // host may have set it): it takes part in the order the
@@ -363,7 +349,6 @@ struct ServeDriver {
     __device__ void level(const ModelState &M, uint32_t k, uint32_t n) {
         st_coherent(M.levels + k, (unsigned long long)n);
     }
-    __device__ void beat() { atomicAdd(&box->beat, 1u); }
 
     // Post the finished query's level counts and completion record
     // (block-wide).  Only here are stores to host memory waited for: one at
@@ -388,7 +373,6 @@ struct ServeDriver {
         st_system(&r->deadlocks, own.deadlocks);
         st_system(&r->wait_hits, own.waits);
         __hip_atomic_store(&r->seq, pos + 1ull, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-        beat();
     }
 };
 
@@ -466,13 +450,12 @@ __global__ void k_serve_init(unsigned long long *tickets, BoardModel *bm, uint32
         ctl->error = 0;
         ctl->idle = 0;
         ctl->slots = 0;
+        ctl->beat = 0;
         box->admit_tail = posted;
         box->admit_head = posted;
         box->done_tail = done_head;
         box->stop = 0;
         box->closing = 0;
-        box->beat = 0;
-        box->pad = 0;
     }
 }
 
