@@ -502,7 +502,8 @@ __device__ __forceinline__ void board_run(Driver &drv, uint32_t *smem, const Mod
             if (spilled)
                 flush_new_slots<true>(nbuf, M.fr[cur ^ 1u], &B.lc, 0xFFFFFFFFu);
             const uint32_t found = spilled ? s_pushed : s_nnew;
-            const bool stay = !spilled && solo_next(M, s_own, found);
+            const bool failed = kServe && s_failed != 0;   // the query ends with the table's error
+            const bool stay = !spilled && !failed && solo_next(M, s_own, found);
             if (!spilled)
                 for (uint32_t j = tid; j < found; j += kExpandBlock) {
                     if (stay)
@@ -520,7 +521,9 @@ __device__ __forceinline__ void board_run(Driver &drv, uint32_t *smem, const Mod
                 s_acc_dead = 0;
                 s_nnew = 0;
                 flush_counters(M.t.status);
-                uint32_t remaining = 0, idle = 0, error = 0;
+                uint32_t remaining = 0, idle = 0, error = 0, err = 0;
+                if (failed)
+                    err = ld_coherent(&M.t.status->error);
                 if (!stay || (solo_levels & 31u) == 31u) {
                     remaining = ld_coherent(&ctl->remaining);
                     idle = ld_coherent(&ctl->idle);
@@ -530,7 +533,7 @@ __device__ __forceinline__ void board_run(Driver &drv, uint32_t *smem, const Mod
                     st_coherent(&B.lc.n_next, 0u);
                 if ((solo_levels & 31u) == 31u)
                     atomicAdd(&ctl->beat, 1u);
-                board_next(drv, M, B, tickets, i, ctl, s_own, found, false, 0u, stay, remaining, idle);
+                board_next(drv, M, B, tickets, i, ctl, s_own, found, false, err, stay, remaining, idle);
                 s_it.exit = error;
             }
         }

@@ -155,6 +155,9 @@ static __shared__ uint32_t s_nnew, s_nbase, s_abort, s_eager;
 static __shared__ uint32_t s_pushed;
 // Set when a wait for a frontier entry ran out (AWAIT): the launch stops.
 static __shared__ uint32_t s_stall;
+// Set when an operation of the tile failed (CL): its query ends with the
+// table's error.
+static __shared__ uint32_t s_failed;
 // Exploration without level barriers: its count of open states, and how
 // many of this workgroup's new states (s_pushed + s_nnew) it already holds.
 static __shared__ unsigned long long *s_open;
@@ -431,7 +434,10 @@ __device__ __forceinline__ uint2 ld_trans(const uint2 *p) {
 // LHS_ESTALL and an aborted tile).  Appends in the middle of the tile count
 // their states as open first (flush_new_slots, COUNT_OPEN).
 // CL: slot lines are read with coherent loads (tables reused within one
-// launch, the persistent server).
+// launch, the persistent server).  A tile whose table reports an error is not
+// expanded, and a tile ends with the pass in which an operation failed
+// (s_failed): the query has ended, and on a full table every further new
+// state would cost a walk over all lines.
 // hold (a level that stays with its workgroup): the tile's new states stay in
 // nbuf (unless it fills up, see s_pushed) and its counts in LDS, nothing is
 // appended and no abort is looked for; held: the frontier's slots in LDS,
@@ -481,6 +487,8 @@ __device__ __forceinline__ bool expand_tile(uint32_t *smem, const TableView &t, 
         // SEG: the level's count is this workgroup's estimate (the cursors
         // are read only near the cap)
         count_now = SEG ? s_seg_est : __hip_atomic_load(&lc->n_next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if constexpr (CL)
+            abort_now |= ld_coherent(&t.status->error);
     }
     bool staged = tid < rows;
     uint64_t slot = 0;
@@ -502,6 +510,7 @@ __device__ __forceinline__ bool expand_tile(uint32_t *smem, const TableView &t, 
     succ_cnt[tid] = 0;
     if (tid == 0) {
         s_tail = 0;
+        s_failed = 0;
         s_abort = abort_now;
         s_eager = limit != 0xFFFFFFFFu && (uint64_t)count_now + kEagerRoom > limit;
     }
@@ -628,6 +637,9 @@ __device__ __forceinline__ bool expand_tile(uint32_t *smem, const TableView &t, 
                 find_or_put<G, LS, Succ, CL>(t, Succ::decode(smem, make_uint2(d0[o], d1[o])), hq[o], line,
                                                 active, slot, code, cnt);
             }
+            if constexpr (CL)
+                if (active && code >= kFull)
+                    s_failed = 1;
             const bool is_new = active && leader && code == kNew;
             if (t.parent && is_new) {
                 // predecessor record: the frontier slot of the expanded row
@@ -649,7 +661,7 @@ __device__ __forceinline__ bool expand_tile(uint32_t *smem, const TableView &t, 
         __syncthreads();
         if (s_eager || s_nnew > (hold ? kHoldFront : kNewBuf) - kBlock)
             flush_new();
-        return s_abort != 0;
+        return s_abort != 0 || (CL && s_failed != 0);
     };
     // successor (p, k) of tile row st
     auto row_of = [&](uint32_t st) { return reinterpret_cast<const R *>(tile + st * stride); };

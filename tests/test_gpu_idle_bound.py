@@ -77,3 +77,23 @@ def test_batch_long_chain(lhs):
     r = lhs.reach_explore_batch([m], capacity=1 << 22, max_levels=1 << 22)[0]
     assert (r.total, r.n_levels, r.edges, r.deadlocks) == (n, n, n - 1, 1)
     assert r.level_counts == [1] * n
+
+
+def test_served_overflow_costs_one_walk(lhs):
+    """A query that overflows its table in a level that one workgroup runs
+    alone.  The level is 78 states, four of which find no slot; the next would
+    be 66 states, none of which does.  Each of those costs a probe of all 2^17
+    lines, so the query has to end with the first level."""
+    cap, dims = 1 << 20, (51, 91, 226)
+    # the last levels of a box: 1, 3, 6, ... states from its far corner
+    last = [k * (k + 1) // 2 for k in range(1, 13)]
+    assert last[-2:] == [66, 78] and sum(last) - (np.prod(dims) - cap) == 74
+    with lhs.Server(cfg=lhs.config(8, "double", 0, 1)) as srv, \
+            lhs.Table(cap, 4, lhs.config(8, "double", 0, 1)) as t:
+        t.set_counters(1)
+        with pytest.raises(lhs.LhsError) as e:
+            srv.wait(srv.submit(box_model(dims), table=t))
+        assert e.value.name == "LHS_EFULL"
+        lines = t.info()["lines_probed"]
+    print(f"\n[idle] overflow of 2^20 slots: {lines} lines probed", flush=True)
+    assert lines < 66 * (cap // 8)
