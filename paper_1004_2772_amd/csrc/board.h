@@ -64,6 +64,8 @@ struct ModelState {
     unsigned long long cap;
     uint32_t max_levels;
     uint32_t handover;            // stop after a level of more states (0 = never)
+    uint32_t words;               // some word of its states may not fit a byte
+    uint32_t pad;
 };
 
 // Shared by all workgroups of a launch; idle ones poll its first line.
@@ -304,9 +306,10 @@ struct BoardOwn {
 };
 
 // Whether a level of n_next states found after own.n_levels levels stays
-// with its workgroup.
-__device__ __forceinline__ bool solo_next(const ModelState &M, const BoardOwn &own, uint32_t n_next) {
-    return n_next != 0 && n_next <= kSoloStates && own.n_levels + 1 < M.max_levels &&
+// with its workgroup (whose tiles hold at most area_rows states).
+__device__ __forceinline__ bool solo_next(const ModelState &M, const BoardOwn &own, uint32_t n_next,
+                                          uint32_t area_rows) {
+    return n_next != 0 && n_next <= min(kSoloStates, area_rows) && own.n_levels + 1 < M.max_levels &&
            (!M.cap || M.cap - own.total > (uint64_t)n_next + kSoloRoom);
 }
 
@@ -318,7 +321,7 @@ __device__ __forceinline__ bool solo_next(const ModelState &M, const BoardOwn &o
 template <class Driver>
 __device__ inline void board_next(Driver &drv, const ModelState &M, BoardModel &B, unsigned long long *tickets,
                                   uint32_t i, BoardCtl *ctl, BoardOwn &own, uint32_t n_next, bool over, uint32_t err,
-                                  bool solo, uint32_t remaining, uint32_t idle) {
+                                  bool solo, uint32_t remaining, uint32_t idle, uint32_t area_rows) {
     bool done = false;
     uint32_t overflow = 0;
     own.finished = 0;
@@ -356,7 +359,7 @@ __device__ inline void board_next(Driver &drv, const ModelState &M, BoardModel &
     }
     unsigned long long waits = 0;
     if (!done) {
-        own.rows = board_tile_rows(remaining, idle, n_next);
+        own.rows = min(board_tile_rows(remaining, idle, n_next), area_rows);
         own.tiles = (n_next + own.rows - 1) / own.rows;
         st_coherent(&B.n_front, n_next);
         st_coherent(&B.limit, own.limit);
@@ -386,12 +389,36 @@ __device__ inline void board_next(Driver &drv, const ModelState &M, BoardModel &
     }
 }
 
+// Rows of W words that fit a tile area of area_words: a power of two from
+// kMinTileRows to kExpandBlock.  A byte row of Wmax words takes at least a
+// quarter of W <= Wmax words, and a stride of one more at most: 32 rows fit
+// wherever 256 byte rows do.
+__host__ __device__ constexpr uint32_t word_rows(uint32_t area_words, uint32_t W) {
+    uint32_t rows = kExpandBlock;
+    while (rows > kMinTileRows && rows * row_stride<uint32_t>(W) > area_words)
+        rows /= 2;
+    return rows;
+}
+constexpr bool word_rows_fit() {
+    for (uint32_t wmax = 1; wmax <= 32; ++wmax)
+        for (uint32_t w = 1; w <= wmax; ++w)
+            if (word_rows(kExpandBlock * row_stride<uint8_t>(wmax), w) * row_stride<uint32_t>(w) >
+                kExpandBlock * row_stride<uint8_t>(wmax))
+                return false;
+    return true;
+}
+static_assert(word_rows_fit(), "a word query always has a tile in a byte launch");
+
 // One launch: all levels of the n models (server: of the queries in n slots).
+// area_words (server, byte rows): the launch's tile area.  A query whose words
+// do not fit bytes joins such a launch with word rows and as many of them as
+// the area holds.
 template <int G, uint32_t LS, class R, class Driver>
 __device__ __forceinline__ void board_run(Driver &drv, uint32_t *smem, const ModelState *__restrict__ ms,
                                           BoardModel *bm, unsigned long long *tickets, BoardCtl *ctl, uint32_t n,
-                                          uint32_t tcap) {
+                                          uint32_t tcap, uint32_t area_words = 0) {
     constexpr bool kServe = Driver::kServe;
+    constexpr bool kBoth = kServe && sizeof(R) == 1;   // word queries among byte ones
     __shared__ BoardItem s_it;
     __shared__ BoardOwn s_own;
     __shared__ uint32_t s_fin, s_over;
@@ -436,13 +463,27 @@ __device__ __forceinline__ void board_run(Driver &drv, uint32_t *smem, const Mod
         const uint32_t rows = s_it.rows, tiles = mode == kTake ? ticket_tiles(s_it.ticket) : s_own.tiles;
         const uint64_t base = mode == kTake ? (uint64_t)s_it.tile * ticket_rows(s_it.ticket) : 0u;
         const uint32_t limit = solo ? 0xFFFFFFFFu : s_it.limit;
-        uint32_t *nbuf = expand_nbuf<G, R>(smem, M.m.W, tcap), *lds_front = nbuf + kHoldFront;
+        bool words = false;
+        uint32_t area_rows = kExpandBlock;
+        if constexpr (kBoth) {
+            words = __builtin_amdgcn_readfirstlane((int)M.words) != 0;
+            if (words)
+                area_rows = word_rows(area_words, (uint32_t)__builtin_amdgcn_readfirstlane((int)M.m.W));
+        }
+        uint32_t *nbuf = words ? expand_nbuf<G, uint32_t>(smem, M.m.W, tcap, area_rows)
+                               : expand_nbuf<G, R>(smem, M.m.W, tcap);
+        uint32_t *lds_front = nbuf + kHoldFront;
         // a solo level's frontier is in LDS from the second one on
         const uint32_t *held = solo && solo_levels ? lds_front : nullptr;
         if (tid == 0)
             s_pushed = 0;
-        expand_tile<G, LS, R, true, false, false, false, kServe>(smem, M.t, M.m, M.fr[cur], base, rows, M.fr[cur ^ 1u],
-                                                                 &B.lc, limit, tcap, SegOut{}, solo, held);
+        if (words)
+            expand_tile<G, LS, uint32_t, true, false, false, false, kServe>(
+                smem, M.t, M.m, M.fr[cur], base, rows, M.fr[cur ^ 1u], &B.lc, limit, tcap, SegOut{}, solo, held,
+                area_rows);
+        else
+            expand_tile<G, LS, R, true, false, false, false, kServe>(
+                smem, M.t, M.m, M.fr[cur], base, rows, M.fr[cur ^ 1u], &B.lc, limit, tcap, SegOut{}, solo, held);
         if (!solo) {
             // this workgroup's stores of the tile are complete before it
             // counts the tile as done
@@ -492,7 +533,7 @@ __device__ __forceinline__ void board_run(Driver &drv, uint32_t *smem, const Mod
                 st_coherent(&B.lc.deadlocks, 0ull);
                 st_coherent(&B.tiles_done, 0u);
                 board_next(drv, M, B, tickets, i, ctl, s_own, n_next, s_over != 0, err,
-                           solo_next(M, s_own, n_next) && !s_over && !err, remaining, idle);
+                           solo_next(M, s_own, n_next, area_rows) && !s_over && !err, remaining, idle, area_rows);
                 s_it.exit = error;
             }
         } else {
@@ -503,7 +544,7 @@ __device__ __forceinline__ void board_run(Driver &drv, uint32_t *smem, const Mod
                 flush_new_slots<true>(nbuf, M.fr[cur ^ 1u], &B.lc, 0xFFFFFFFFu);
             const uint32_t found = spilled ? s_pushed : s_nnew;
             const bool failed = kServe && s_failed != 0;   // the query ends with the table's error
-            const bool stay = !spilled && !failed && solo_next(M, s_own, found);
+            const bool stay = !spilled && !failed && solo_next(M, s_own, found, area_rows);
             if (!spilled)
                 for (uint32_t j = tid; j < found; j += kExpandBlock) {
                     if (stay)
@@ -533,7 +574,8 @@ __device__ __forceinline__ void board_run(Driver &drv, uint32_t *smem, const Mod
                     st_coherent(&B.lc.n_next, 0u);
                 if ((solo_levels & 31u) == 31u)
                     atomicAdd(&ctl->beat, 1u);
-                board_next(drv, M, B, tickets, i, ctl, s_own, found, false, err, stay, remaining, idle);
+                board_next(drv, M, B, tickets, i, ctl, s_own, found, false, err, stay, remaining, idle,
+                           area_rows);
                 s_it.exit = error;
             }
         }

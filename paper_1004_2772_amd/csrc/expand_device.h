@@ -187,10 +187,20 @@ __device__ __forceinline__ void expand_begin() {
     }
 }
 
-// The new-state buffer in the expansion's LDS layout.
+// The new-state buffer in the expansion's LDS layout (area_rows: see
+// expand_tile).
 template <int G, class R>
-__device__ __forceinline__ uint32_t *expand_nbuf(uint32_t *smem, uint32_t W, uint32_t tcap) {
-    return smem + expand_lds_words<R>(W, tcap, G) - kNewBuf;
+__device__ __forceinline__ uint32_t *expand_nbuf(uint32_t *smem, uint32_t W, uint32_t tcap,
+                                                 uint32_t area_rows = kExpandBlock) {
+    return smem + expand_lds_words<R>(W, tcap, G) - kNewBuf - (kExpandBlock - area_rows) * row_stride<R>(W);
+}
+
+// One per wavefront; the same for every element type of the rows, so that a
+// kernel with two of them holds it once.
+template <uint32_t LS>
+__device__ __forceinline__ WaveScratch<LS> *wave_scratch() {
+    __shared__ WaveScratch<LS> ws[kExpandBlock / 64];
+    return ws;
 }
 
 // Append the buffered new slots to next[] with one atomic on the level's
@@ -443,6 +453,7 @@ __device__ __forceinline__ uint2 ld_trans(const uint2 *p) {
 // appended and no abort is looked for; held: the frontier's slots in LDS,
 // instead of front[].
 // R: the element type of the tile's LDS rows (uint8_t with G = 1 only).
+// area_rows: the rows that the layout has room for; rows is at most that.
 template <int G, uint32_t LS, class R, bool COHERENT = false, bool DEFER = false, bool DEFER_COUNTS = DEFER,
           bool AWAIT = false, bool CL = false, bool SEG = false>
 __device__ __forceinline__ bool expand_tile(uint32_t *smem, const TableView &t, const ModelView &m,
@@ -450,13 +461,13 @@ __device__ __forceinline__ bool expand_tile(uint32_t *smem, const TableView &t, 
                                             uint32_t rows, uint32_t *__restrict__ next,
                                             LevelCounters *lc, uint32_t limit, uint32_t tcap,
                                             const SegOut &so = SegOut{}, bool hold = false,
-                                            const uint32_t *held = nullptr) {
+                                            const uint32_t *held = nullptr, uint32_t area_rows = kExpandBlock) {
     constexpr uint32_t kBlock = kExpandBlock;
     static_assert(sizeof(R) == 4 || G == 1, "byte rows: one lane per operation");
     using Succ = SuccVec<R>;
     const uint32_t W = m.W, stride = row_stride<R>(W);
     uint32_t *tile = smem;
-    uint2 *tr_lds = reinterpret_cast<uint2 *>(tile + kBlock * stride);
+    uint2 *tr_lds = reinterpret_cast<uint2 *>(tile + area_rows * stride);
     uint64_t *masks = reinterpret_cast<uint64_t *>(tr_lds + tcap);
     uint32_t *queue = reinterpret_cast<uint32_t *>(masks);     // wide models only
     uint32_t *succ_cnt = reinterpret_cast<uint32_t *>(masks) + kMaskArea;
@@ -467,11 +478,16 @@ __device__ __forceinline__ bool expand_tile(uint32_t *smem, const TableView &t, 
     uint64_t my_h = 0;           // G == 1: this lane's successor of the pass
     uint32_t my_d0 = 0, my_d1 = 0;
     __shared__ uint32_t s_tail, s_wtot[kBlock / 64];
-    __shared__ WaveScratch<LS> ws[kBlock / 64];
+    WaveScratch<LS> *ws = wave_scratch<LS>();
 
     constexpr uint32_t NG = kBlock / G;
     LaneCounters cnt;
-    const uint32_t tid = threadIdx.x, gi = tid / G;
+    // In the server's kernel what is derived from it stays in the tile, for
+    // the registers' sake, instead of being hoisted out of the main loop.
+    uint32_t own_tid = threadIdx.x;
+    if constexpr (CL)
+        asm volatile("" : "+v"(own_tid));
+    const uint32_t tid = own_tid, gi = tid / G;
     const bool leader = (tid & (G - 1)) == 0;
     const uint32_t PK = m.P * m.K;
     const uint32_t PLK = m.P * m.L * m.K;

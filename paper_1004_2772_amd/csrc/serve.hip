@@ -381,7 +381,7 @@ __global__ __launch_bounds__(kExpandBlock, LS == 8 ? 4 : 1) void k_serve(const M
                                                                         unsigned long long *tickets, BoardCtl *ctl,
                                                                         ServeBox *box, DoneRec *done,
                                                                         const uint32_t *roots, uint32_t n_slots,
-                                                                        uint32_t tcap) {
+                                                                        uint32_t tcap, uint32_t area_words) {
     extern __shared__ uint32_t smem[];
     __shared__ ModelState s_M;
     __shared__ uint32_t s_M_slot;
@@ -389,7 +389,7 @@ __global__ __launch_bounds__(kExpandBlock, LS == 8 ? 4 : 1) void k_serve(const M
         s_M_slot = 0xFFFFFFFFu;
     __syncthreads();
     ServeDriver<LS> drv{box, done, roots, &s_M, &s_M_slot};
-    board_run<G, LS, R>(drv, smem, ms, bm, tickets, ctl, n_slots, tcap);
+    board_run<G, LS, R>(drv, smem, ms, bm, tickets, ctl, n_slots, tcap, area_words);
 }
 
 // Before a launch: admissions reopen.
@@ -499,7 +499,6 @@ struct Persist {
     hipEvent_t ev_end = nullptr;       // recorded after each launch
     bool running = false;
     uint32_t launch_W = 0;             // widest vector the running launch's LDS holds
-    bool launch_bytes = false;         // ... in rows of bytes
     uint64_t launches = 0;
     ModelState *d_ms = nullptr;
     BoardModel *d_bm = nullptr;
@@ -1033,6 +1032,7 @@ lhs_status persist_post(reach_server *s, const std::vector<Query *> &qs) {
         e.ms.host_levels = P.h_levels_dev[slot];
         e.ms.cap = q->m.state_cap;
         e.ms.max_levels = kServeMaxLevels;
+        e.ms.words = !q->bytes_rows;
         e.zero = TableZero{reinterpret_cast<uint4 *>(q->t->bucket), q->t->capacity / 2,
                            reinterpret_cast<TableStatus *>(q->t->status)};
         e.trans = q->d_trans;
@@ -1084,7 +1084,8 @@ lhs_status persist_launch(reach_server *s) {
         hipLaunchKernelGGL(k_serve_reopen, dim3(1), dim3(1), 0, s->stream, P.d_box);
         hipLaunchKernelGGL((k_serve<decltype(G)::value, decltype(L)::value, decltype(R)>), dim3(grid), dim3(kExpandBlock), lds,
                            s->stream, (const ModelState *)P.d_ms, P.d_bm, P.d_tickets, P.d_ctl, P.d_box,
-                           P.h_done_dev, (const uint32_t *)P.d_roots, s->opts.max_active, tcap);
+                           P.h_done_dev, (const uint32_t *)P.d_roots, s->opts.max_active, tcap,
+                           kExpandBlock * row_stride<decltype(R)>(maxW));
         return hipGetLastError() == hipSuccess ? LHS_OK : LHS_EDEVICE;
     });
     if (rc != LHS_OK)
@@ -1093,7 +1094,6 @@ lhs_status persist_launch(reach_server *s) {
     P.running = true;
     P.close_sent = false;
     P.launch_W = maxW;
-    P.launch_bytes = bytes;
     ++P.launches;
     return LHS_OK;
 }
@@ -1163,13 +1163,12 @@ void persist_worker(reach_server *s) {
             if (s->stop && s->queue.empty() && P.live == 0 && !P.running)
                 return;
             // first come first served, while a slot and the budget allow; a
-            // query wider than the running launch's LDS, or with words its
-            // rows cannot hold, waits for the next launch (and holds the
-            // queries behind it)
+            // query wider than the running launch's LDS waits for the next
+            // launch (and holds the queries behind it)
             bool drain = false;
             while (!s->queue.empty() && admitted.size() < P.free_slots.size()) {
                 Query *q = s->queue.front();
-                if (P.running && (q->W > P.launch_W || (P.launch_bytes && !q->bytes_rows))) {
+                if (P.running && q->W > P.launch_W) {
                     drain = true;
                     break;
                 }
