@@ -26,3 +26,19 @@ def test_library_calls_before_torch_in_a_fresh_process():
     r = subprocess.run([sys.executable, "-c", SCRIPT], cwd=ROOT, capture_output=True, text=True, timeout=300,
                        env=dict(os.environ, PYTHONPATH=ROOT + os.pathsep + os.environ.get("PYTHONPATH", "")))
     assert r.returncode == 0 and r.stdout.strip().endswith("ok"), r.stdout[-2000:] + r.stderr[-4000:]
+
+
+def test_calls_run_on_the_current_stream():
+    """Without a stream given, a call takes torch's current one: the default,
+    one made current, and the default again; a given stream stands."""
+    import torch
+
+    import paper_1004_2772_amd as lhs
+
+    side = torch.cuda.Stream()
+    assert lhs._stream_handle(None) == torch.cuda.default_stream().cuda_stream
+    with torch.cuda.stream(side):
+        assert lhs._stream_handle(None) == torch.cuda.current_stream().cuda_stream == side.cuda_stream
+        assert lhs._stream_handle(torch.cuda.default_stream()) == torch.cuda.default_stream().cuda_stream
+    assert lhs._stream_handle(None) == torch.cuda.default_stream().cuda_stream
+    assert lhs._stream_handle(side) == side.cuda_stream
