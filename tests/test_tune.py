@@ -183,3 +183,20 @@ def test_autotune_reselect_keeps_format(tmp_path):
     doc = autotune.reselect(str(p))
     assert lhs.tune_load(str(p), device=doc["device"]) == len(doc["entries"])
     lhs.tune_clear()
+
+
+def test_committed_table_is_the_rules_choice():
+    """Every entry of the tuning table in the package is what the selection
+    rule makes of the times recorded in it."""
+    from paper_1004_2772_amd import autotune
+    with open(lhs.TUNE_PATH_DEFAULT) as f:
+        doc = json.load(f)
+    for e in doc["entries"]:
+        if e["kind"] == "table":
+            want, score = autotune.choose(e["stream_ms"], e["bfs_ms"])
+            got = (e["line_slots"], e["probe"], e["tps_find_or_put"], e["tps_expand"])
+        else:
+            (ls, probe, te, _), score = autotune.choose(e["batch_ms"], None)
+            want, got = (ls, probe, te), (e["line_slots"], e["probe"], e["tps_expand"])
+        assert got == want, (e["kind"], e["W"], e["log2_capacity"])
+        assert e["score"] == round(score, 4)
