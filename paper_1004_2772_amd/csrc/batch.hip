@@ -96,6 +96,7 @@ void levels_area(LevelsArea *h, const LevelsArea *d, lhs_table *t, const TableVi
                  uint64_t cap, const LevelsRun &run) {
     std::memset(static_cast<void *>(h), 0, offsetof(LevelsArea, levels));
     h->ctl.remaining = 1;
+    h->ctl.stall_ms = stall_ms(t->lines);
     h->tickets[0] = make_ticket((run.n_front + kExpandBlock - 1) / kExpandBlock, run.cur, kExpandBlock, 0);
     ModelState &M = h->ms;
     M.t = tv;
@@ -312,8 +313,10 @@ static lhs_status reach_explore_batch_impl(const reach_model *const *models, uin
         max_chunks = std::max<uint64_t>(max_chunks, b.t->capacity / 2);
     }
     if (!host_loop) {
-        at<BoardCtl>(H, o_ctl)->remaining = n;
+        BoardCtl &ctl = *at<BoardCtl>(H, o_ctl);
+        ctl.remaining = n;
         for (uint32_t i = 0; i < n; ++i) {
+            ctl.stall_ms = std::max(ctl.stall_ms, stall_ms(bm[i].t->lines));
             ModelState &M = at<ModelState>(H, o_ms)[i];
             M.t = u_slots[i].t;
             M.m = u_slots[i].m;

@@ -47,10 +47,13 @@ namespace lhs {
 // poll takes 1 to 40 us, by the naps after it and by how many poll.  The
 // longest stretch without a beat is that of an operation on a full table,
 // which probes every line before it reports EFULL: 1.4 us a line, 2.9 s at
-// 2^24 slots in lines of 8.  So a model that overflows a table of up to 2^27
-// slots ends with EFULL, and a chain of any number of levels ends.
-constexpr uint64_t kWallHz = 100000000;
-constexpr uint64_t kStallTicks = 30 * kWallHz;
+// 2^24 slots in lines of 8 (5.5 us a line if all 2^18 resident lanes do so, at
+// the 48 G random lines a second that this GPU reads).
+// So the bound is 30 s and 8 us for each line of the launch's largest table: a
+// model that overflows ends with EFULL, and a chain of any number of levels
+// ends.
+constexpr uint64_t kWallKHz = 100000;
+__host__ __device__ inline uint32_t stall_ms(uint64_t lines) { return (uint32_t)(30000 + lines / 125); }
 constexpr uint32_t kBeatPolls = 16;   // polls between an idle workgroup's looks at the beat
 
 // Per-model constants (written by the host before the launch, or before the
@@ -74,7 +77,8 @@ struct alignas(128) BoardCtl {
     uint32_t error;
     uint32_t idle;        // workgroups without a tile
     uint32_t slots;       // server: tickets in use are below this
-    alignas(128) uint32_t beat;   // signs of progress (kStallTicks)
+    alignas(128) uint32_t beat;   // signs of progress
+    uint32_t stall_ms;            // an idle workgroup's wait without one
 };
 
 // One model's level and progress: written by whichever workgroup finalises a
@@ -242,7 +246,7 @@ __device__ inline void board_take(Driver &drv, const ModelState *ms, BoardModel 
             const uint64_t now = wall_clock64();
             if (polls == kBeatPolls || b != beat || remaining == 0u)
                 since = now;
-            else if (now - since > kStallTicks && lane == 0)
+            else if (now - since > ld_coherent(&ctl->stall_ms) * kWallKHz && lane == 0)
                 atomicCAS(&ctl->error, 0u, (uint32_t)LHS_ESTALL);
             beat = b;
         }

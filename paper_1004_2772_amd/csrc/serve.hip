@@ -428,6 +428,7 @@ __global__ __launch_bounds__(256) void k_serve_post(const PostEntry *entries, co
         if (tid == 0) {
             box->admit_slot[(posted + blockIdx.y) % kAdmitRing] = e.slot;
             atomicMax(&ctl->slots, e.slot + 1u);
+            atomicMax(&ctl->stall_ms, stall_ms((uint64_t)e.ms.t.line_mask + 1));
         }
         zero_status(e.zero.status);
     }
@@ -455,6 +456,7 @@ __global__ void k_serve_init(unsigned long long *tickets, BoardModel *bm, uint32
         ctl->idle = 0;
         ctl->slots = 0;
         ctl->beat = 0;
+        ctl->stall_ms = stall_ms(0);
         box->admit_tail = posted;
         box->admit_head = posted;
         box->done_tail = done_head;
