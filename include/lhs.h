@@ -78,7 +78,9 @@ typedef struct lhs_config {
     uint32_t probe;           /* lhs_probe                                     */
     uint32_t tps_find_or_put; /* GPU lanes per operation in lhs_find_or_put:
                                  1, 4, 8, 16, or 0 = 4 (see
-                                 lhs_set_threads_per_state)                    */
+                                 lhs_set_threads_per_state).  A table made by
+                                 lhs_create whose tuning entry says 1 runs 8
+                                 in calls of up to 256 operations per CU       */
     uint32_t tps_expand;      /* the same for BFS expansion; 0 = 1             */
 } lhs_config;
 
@@ -178,7 +180,7 @@ typedef struct lhs_info {
     uint32_t error;        /* sticky lhs_status of device failures           */
     uint32_t probe;        /* lhs_probe                                      */
     uint32_t tps_find_or_put; /* lanes per operation in effect (defaults
-                                 resolved)                                   */
+                                 resolved; see lhs_config for small calls)   */
     uint32_t tps_expand;
     uint64_t lines_probed; /* lines examined by find-or-puts while counted
                               (lhs_set_counters); the paper's probe count     */
@@ -423,10 +425,11 @@ lhs_status reach_deadlock_slots(lhs_table *t, uint32_t *h_slots, uint32_t max, u
 /* Explore n models (1..1024) together: every model has its own table region
  * (slots, rows, frontiers) and results identical to reach_explore on it
  * alone, so models of different sizes and widths share the GPU.  By default
- * the whole exploration is one persistent launch: its workgroups take
- * (model, tile) items from a device work queue, and the workgroup that
- * finishes a model's last tile of a level finalises that level and queues
- * the next one, so models advance independently.  REACH_F_HOST_LOOP instead
+ * the whole exploration is one persistent launch: its workgroups take tiles
+ * of any model's current level by its ticket, and the workgroup that finishes
+ * a level's last tile finalises that level and writes the next one's ticket
+ * (or runs the next level alone, if it is narrow), so models advance
+ * independently.  REACH_F_HOST_LOOP instead
  * runs one launch per step in which every unfinished model advances one
  * level.  All tables of a batch share one line width and lanes per state
  * (internal tables: the tuning table's "batch" choice; given tables must
@@ -449,12 +452,15 @@ lhs_status reach_explore_batch(const reach_model *const *models, uint32_t n, con
  *
  * A server owns a worker thread and a HIP stream on the device that was
  * current at reach_server_create.  By default one persistent launch serves
- * every query on the GPU: its workgroups take (query, tile) items from a
- * device work queue, the workgroup that finishes a query's level advances
+ * every query on the GPU: its workgroups take tiles of any query's current
+ * level by its ticket, the workgroup that finishes a query's level advances
  * that query alone, new queries are posted to the running launch (an idle
  * workgroup inserts s0 and starts it at once) and finished ones are
  * reported through completion records in host memory, so a query starts and
- * ends without waiting for a kernel boundary.  The launch ends once idle
+ * ends without waiting for a kernel boundary.  A query whose state vector is
+ * wider than all queries on the GPU when the launch began waits for the next
+ * launch, and the queries behind it do.  A query that overflows its table
+ * ends alone, with LHS_EFULL.  The launch ends once idle
  * and is started again when work arrives.  REACH_SERVER_F_ROUNDS instead
  * works in rounds of four BFS level steps run by the device alone (every
  * step expands the current level of every active query in one launch), and
@@ -506,8 +512,8 @@ lhs_status reach_server_create(const reach_server_opts *o, reach_server **out);
 /* Queue a query; the model (host memory) is copied, the caller may free it
  * on return.  *ticket identifies the query.  LHS_EBUDGET if its table can
  * never fit the budget, LHS_EINVAL for an invalid model (or, on a
- * persistent server, a table of more than 2^30 slots: the work queue holds a
- * full level of every query on the GPU). */
+ * persistent server, a table of 2^30 slots or more: such tables are for the
+ * rounds). */
 lhs_status reach_server_submit(reach_server *s, const reach_model *m, uint64_t *ticket);
 
 /* reach_server_submit on a table of the caller's (NULL = the pool, as

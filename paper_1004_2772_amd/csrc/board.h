@@ -112,7 +112,8 @@ constexpr uint32_t kSmallLevel = 32768;
 constexpr uint32_t kMinTileRows = 32;
 constexpr uint32_t kFewModels = 8;
 // While at most kFewModels models are unfinished, workgroups of a number from
-// kFewGrid on wait kSleepyNaps naps (40 us) between polls: one workgroup per
+// kFewGrid (the CUs of the whole GPU; a partition of it has no such workgroups
+// to put to sleep) on wait kSleepyNaps naps (40 us) between polls: one workgroup per
 // CU takes these models' levels soonest, and 768 more that poll slow them
 // down (3 models of 64: 3.69 -> 3.34 ms, 6: 4.1 -> 3.65 ms).
 constexpr uint32_t kFewGrid = 256;

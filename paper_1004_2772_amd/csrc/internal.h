@@ -32,8 +32,8 @@ struct lhs_table {
     uint32_t line_slots = 16;  // slots per probed line (8, 16, 32)
     uint32_t probe = 0;        // lhs_probe
     uint32_t tps_fop = 0;      // lanes cooperating on one operation (1, 4, 8,
-    bool tuned = false;   // its lanes come from the tuning table (tps_of_call)
     uint32_t tps_exp = 0;      // 16) in find-or-put / BFS; 0 = default
+    bool tuned = false;        // ... come from the tuning table (tps_of_call)
     uint32_t counters = 0;     // LHS_COUNT_* requested by lhs_set_counters
     uint32_t merge = 0;        // lhs_merge mode of explorations (lhs_set_merge)
     uint32_t workers = 0;      // cap on exploration workgroups (0 = all resident)

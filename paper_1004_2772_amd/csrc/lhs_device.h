@@ -56,7 +56,7 @@ struct DevStatus {
 // 2^20 slots: 98 us on one address, 42 us striped; 2^20 rows of 8 words into
 // 2^22 slots 224 and 90 us.
 struct alignas(128) CounterLine {
-    unsigned long long waits, cas_failures, lines, merged;
+    unsigned long long waits, cas_failures, lines;
 };
 constexpr uint32_t kStripes = 64;
 struct TableStatus {
@@ -635,9 +635,10 @@ __device__ __forceinline__ void wave_lds_sync() {
 // cache) instead of branching around its load: a load under a divergent
 // branch is waited for before the next one is issued, which made a snapshot
 // of 64 lines four round trips and a compare of 64 rows eight.  Measured with
-// the loads branched around and together: a table of 2^28 slots built from
-// 2^26 rows of 16 words 5.24 and 4.87 ms, the 12-process search to 2^27
-// states 24.6 and 22.6 ms, the 64-model batch 11.3 and 10.3 ms.
+// the loads branched around and together: the 12-process search to 2^27
+// states 24.6 and 22.6 ms, the 64-model batch 11.3 and 10.3 ms; a table of
+// 2^28 slots built from 2^26 rows of 16 words, which HBM traffic bounds, 5.48
+// and 5.40 ms.
 
 // One part of a line snapshot: the lines of ranks [0, nn) by NQ load
 // instructions of LPQ lines each.
@@ -661,7 +662,9 @@ __device__ __forceinline__ void coop_line_part(WaveScratch<LS> *ws, const uint64
                            ((uint32_t)((s0 & ~kDone) == mk) << 2) |
                            ((uint32_t)((s1 & ~kDone) == mk) << 3) |
                            ((uint32_t)(s0 >> 62) & 1u) << 4 | (((uint32_t)(s1 >> 62) & 1u) << 5);
-        ws->res[r[q] * C + c] = (uint8_t)b;   // lanes of one entry write the same byte
+        // lanes that repeat an entry may have read another state of its line;
+        // either byte is a snapshot of the line's two slots
+        ws->res[r[q] * C + c] = (uint8_t)b;
     }
 }
 

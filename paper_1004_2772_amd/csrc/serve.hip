@@ -206,7 +206,9 @@ __global__ __launch_bounds__(kExpandBlock, LS == 8 ? 4 : 1) void k_step(BatchSlo
 // whose new tables no longer wait for the launch to end: 22 -> 9 ms.
 constexpr uint32_t kAdmitRing = 2048;      // admission entries (> 2 x max active)
 constexpr uint32_t kDoneRing = 2048;       // completion records (> 2 x max active)
-constexpr uint64_t kServeCapacity = 1ull << 30;   // a served table has fewer slots
+// A served table has fewer slots; larger ones, whose queries fill the GPU by
+// themselves, are for the rounds.
+constexpr uint64_t kServeCapacity = 1ull << 30;
 constexpr uint32_t kServeMaxLevels = 1u << 16; // levels of one served query
 constexpr uint32_t kIdleLeave = 320;       // checks (~5 ms) finding no query on the GPU
                                            // before a workgroup leaves
@@ -1132,8 +1134,8 @@ lhs_status persist_collect(reach_server *s, std::vector<Query *> &finished) {
     return LHS_OK;
 }
 
-// After a launch ended: a queue failure ends every query on the GPU and
-// starts the device state afresh.
+// After a launch ended: one that stalled ends every query on the GPU, and the
+// device state starts afresh.
 lhs_status persist_after_launch(reach_server *s, std::vector<Query *> &finished) {
     Persist &P = s->ps;
     P.running = false;
