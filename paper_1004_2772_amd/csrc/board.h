@@ -130,16 +130,25 @@ constexpr uint32_t kSoloRoom = 1u << 17;
 
 // Rows per tile of a level.  Once at most kFewModels models remain and at
 // least half the workgroups are idle, a level of at most kSmallLevel states
-// is cut into tiles of down to kMinTileRows states, about one per idle
-// workgroup: the deepest models' narrow levels, run after the rest of the
-// batch has finished, then spread over the idle GPU instead of one full
-// tile's latency chain per workgroup.  Otherwise tiles stay full (less
+// is cut into tiles of down to kMinTileRows states, about one per workgroup
+// that is there to take it: the deepest models' narrow levels, run after the
+// rest of the batch has finished, then spread over the idle GPU instead of one
+// full tile's latency chain per workgroup.  Otherwise tiles stay full (less
 // per-tile work while the GPU is busy).
+// There are the workgroups below kFewGrid, the others being asleep, and the
+// other models' levels take theirs too: their wide levels seldom come at the
+// same moment, so a level counts on twice its share.  One tile per idle
+// workgroup, sleeping or not, made more and shorter tiles than were taken at
+// once (batches of 3, 7, 8, 9 and 16 models: that, one per workgroup below
+// kFewGrid, and one per twice the share): 3.28, 2.67, 2.68 ms; 2.20, 1.79,
+// 1.72; 1.45, 1.36, 1.39; 4.31, 3.71, 3.48; 4.99, 4.39, 4.15.  With full
+// tiles while more than four models remain: 3.28, 1.78, 1.66, 3.48, 4.35.
 __device__ __forceinline__ uint32_t board_tile_rows(uint32_t remaining, uint32_t idle, uint32_t n_states) {
     if (n_states > kSmallLevel || remaining > kFewModels || idle < gridDim.x / 2)
         return kExpandBlock;
+    const uint32_t takers = 2u * min(idle, kFewGrid) / (1u + remaining);
     uint32_t rows = kMinTileRows;
-    while (rows < kExpandBlock && (uint64_t)rows * (idle + 1) < n_states)
+    while (rows < kExpandBlock && (uint64_t)rows * (takers + 1) < n_states)
         rows <<= 1;
     return rows;
 }
