@@ -19,9 +19,10 @@ def lhs():
     return m
 
 
-def padded(m, W):
-    """The model with variables added that nothing reads or writes."""
-    return gen.Model(m.P, m.L, W - m.P, m.D, m.K, m.trans,
+def padded(m, W, L):
+    """The model with variables and local states added that nothing uses."""
+    trans = np.concatenate([m.trans, np.repeat(m.trans[:, -1:], L - m.L, axis=1)], axis=1)
+    return gen.Model(m.P, L, W - m.P, m.D, m.K, np.ascontiguousarray(trans),
                      np.concatenate([m.init, np.zeros(W - m.W, dtype=np.uint32)]), m.cap, m.name)
 
 
@@ -45,17 +46,21 @@ def word_model(P, S, cap=0):
 
 
 # (widest vector of the byte launch, P, S of the word query): tiles of 256,
-# 128, 64 and 32 of its rows fit the launch; one query is cut off by a cap.
-@pytest.mark.parametrize("wmax,P,S,cap", [(5, 2, 1, 0), (5, 2, 3, 0), (31, 2, 29, 0), (31, 3, 13, 30000),
-                                          (20, 2, 18, 0), (12, 3, 9, 30000)])
-def test_word_query_joins_byte_launch(lhs, wmax, P, S, cap):
+# 128, 64 and 32 of its rows fit the launch; some queries are cut off by a cap.
+# The launch has room in LDS for the transitions of its own byte query, L * 16:
+# with 120 local states also for the word query's 1800.  23 processes have more
+# than 64 pairs of process and transition, which are found in another way.
+@pytest.mark.parametrize("wmax,P,S,cap,L", [(5, 2, 1, 0, 5), (5, 2, 3, 0, 120), (31, 2, 29, 0, 5),
+                                            (31, 3, 13, 30000, 5), (20, 2, 18, 0, 120), (12, 3, 9, 30000, 5),
+                                            (31, 23, 8, 30000, 5), (24, 23, 1, 30000, 120)])
+def test_word_query_joins_byte_launch(lhs, wmax, P, S, cap, L):
     m = word_model(P, S, cap)
     want = result_fields(oracle.reach(m))
     print(f"\n[serve] word query W={P + S} in a byte launch of W={wmax}: {want['total']} states in "
           f"levels of at most {max(want['level_counts'])}", flush=True)
     with lhs.Server(capacity=1 << 21, cfg=lhs.config(8, "double", 0, 1)) as srv:
         # some 0.2 s of one-state levels, in rows of bytes
-        first = srv.submit(padded(counter_model(4, 9), wmax))
+        first = srv.submit(padded(counter_model(4, 9), wmax, L))
         while srv.stats()["steps"] == 0:
             pass
         byte, word, again = srv.submit(gen.cyclic_model(1, 100)), srv.submit(m), srv.submit(m)
